@@ -135,8 +135,11 @@ typedef struct fk_data {
 
 /* Launch plan of the path kernel (see fk_plan_autotune).  Zero fields take defaults:
  * block 256; blocks_per_cu the kernel's occupancy (the grid is cut to no more
- * wavefronts than there are chunks); chunk 128, or for horizons of at most 64
- * steps: in fk_interface_solve (and the plain pass of fk_interface_solve_cv)
+ * wavefronts than there are chunks); chunk 128, or for horizons of at most 32
+ * steps (64 if t <= 0.05) in fk_interface_solve and the mesh-gradient form of
+ * fk_interface_solve_cv 64 r paths for the r that finishes first on a grid of
+ * 24 wavefronts per CU; for other horizons of at most 64 steps: in
+ * fk_interface_solve (and the plain pass of fk_interface_solve_cv)
  * the largest of 256, 512, 1024, 2048 that leaves at least 8 chunks per
  * resident wavefront (28 per CU), 256 with a node mask, and 256 in the network
  * forms of fk_interface_solve_cv; for longer horizons in the control-variate

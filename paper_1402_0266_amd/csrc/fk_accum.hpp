@@ -148,6 +148,26 @@ __device__ __forceinline__ long long q2_small(float s) {
     return __double_as_longlong(t) - 0x4330000000000000ll;   // bits of 2^52
 }
 
+// A path's values added to its node's sums in HBM directly; a path with a
+// value that is not finite or beyond kGlobalBound (finite = false) is counted
+// as bad.
+template <int NV>
+__device__ __forceinline__ void acc_direct(NodeAcc *const *acc, uint32_t out, const float (&v)[NV], bool finite) {
+    if (finite) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const double d = (double)v[i];
+            NodeAcc &A = acc[i >> 1][out];
+            const int c = i & 1;
+            add_split(A.sum[2 * c], __double2ll_rn(d * kQ1));
+            add_split(A.sum[2 * c + 1], (long long)__double2ull_rn(d * d * kQ2));   // s^2 is exact in FP64
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NV; i += 2) atomicAdd(&acc[i >> 1][out].bad, 1u);
+    }
+}
+
 // A finished path (divergent: only finishing lanes call it).  v[NV]: its
 // values relative to the node's shift; tag: its chunk's tag; out: its
 // output row; steps: the Euler-Maruyama steps it took.  The path that
@@ -170,18 +190,8 @@ __device__ __forceinline__ bool acc_path(AccSlot<NV> *slots, NodeAcc *const *acc
             atomicAdd(&S.m[2 * i], (unsigned long long)q1_small(v[i]));
             atomicAdd(&S.m[2 * i + 1], (unsigned long long)q2_small(v[i]));
         }
-    } else if (finite) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const double d = (double)v[i];
-            NodeAcc &A = acc[i >> 1][out];
-            const int c = i & 1;
-            add_split(A.sum[2 * c], __double2ll_rn(d * kQ1));
-            add_split(A.sum[2 * c + 1], (long long)__double2ull_rn(d * d * kQ2));   // s^2 is exact in FP64
-        }
     } else {
-#pragma unroll
-        for (int i = 0; i < NV; i += 2) atomicAdd(&acc[i >> 1][out].bad, 1u);
+        acc_direct<NV>(acc, out, v, finite);
     }
     bool closed = false;
     if (mine) {

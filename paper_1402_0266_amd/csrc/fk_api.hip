@@ -279,6 +279,36 @@ int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
     return 256;
 }
 
+// Fixed steps with the discrete exit test, at most 64 of them, and not so
+// long a horizon that lanes whose paths have left wait for most of it.  Both
+// kernels on 1521 nodes x 4096 paths of two bumps (refilling / lockstep, us):
+// 8 steps 338 / 118 at t = 1e-3, 337 / 104 at t = 0.3; 20 steps 370 / 231
+// and 348 / 212; 64 steps 842 / 676 at t = 1e-3, 807 / 680 at t = 0.05 (a
+// path takes 59% of the steps), 634 / 678 at t = 0.1 (42%), 404 / 614 at
+// t = 0.3.
+bool lockstep_paths(int64_t K, double t, int score_mode) {
+    return (K <= 32 || (K <= 64 && t <= 0.05)) && score_mode != FK_SCORE_EXPONENTIAL && score_mode != FK_SCORE_BRIDGE;
+}
+
+int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
+    // a chunk of r rounds of 64 paths costs about r + 1/4 rounds; the chunks
+    // go round robin over the wavefronts (24 per CU).  A masked solve's node
+    // count is known on the device only: an eighth is assumed.
+    const int64_t waves = 24LL * n_cu, rounds = (n_paths + 63) / 64;
+    if (masked) n_nodes = (n_nodes + 7) / 8;
+    int best = 1;
+    double least = 1e300;
+    for (int r = 1; r <= 32; ++r) {
+        const int64_t chunks = n_nodes * ((rounds + r - 1) / r);
+        const double cost = (double)((chunks + waves - 1) / waves) * (r + 0.25);
+        if (cost <= least) {
+            least = cost;
+            best = r;
+        }
+    }
+    return 64 * best;
+}
+
 int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu) {
     // 64 chunks per CU: at least eight per resident wavefront of the
     // network kernels (two waves per SIMD)
@@ -304,26 +334,35 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     const bool timed = allow_timing && g_timing.enabled;
     hipError_t e;
     const int64_t cpn = (S.n_paths + S.plan.chunk - 1) / S.plan.chunk;
-    if ((e = launch_counters_init(S.counters, (uint32_t)(S.n_nodes * cpn), stream)) != hipSuccess)
-        return hip_fail(e, "zero counters");
-    if ((e = launch_zero_u32((uint32_t *)S.args.acc, (int)(acc_bytes(S.n_nodes) / 4), stream)) != hipSuccess)
-        return hip_fail(e, "zero estimator sums");
+    PathArgs a = S.args;
+    TableArgs t{};
     if (S.tables) {
-        // node tables from the device coordinates (they also set the chunk count)
-        TableArgs t = *S.tables;
+        t = *S.tables;
         t.counters = S.counters;
         t.cpn = (uint32_t)cpn;
-        if ((e = launch_tables(t, stream)) != hipSuccess) return hip_fail(e, "node table kernels");
     }
-    PathArgs a = S.args;
-    if (S.total_steps) {
-        if ((e = launch_zero_u32((uint32_t *)S.total_steps, 2, stream)) != hipSuccess)
-            return hip_fail(e, "zero total_steps");
-        a.total_steps = (unsigned long long *)S.total_steps;
+    if (S.lockstep) {
+        // one kernel for the tables and the cleared sums; the step count is
+        // summed over the nodes at the end
+        if ((e = launch_short_tables(t, (unsigned long long *)S.total_steps, stream)) != hipSuccess)
+            return hip_fail(e, "node table kernel");
+        a.masked = t.mask ? 1u : 0u;
     } else {
-        // nobody asked for the count: short horizons skip it (the kernels
-        // skip a null count), others keep it in the counters block
-        a.total_steps = S.first_by_index ? nullptr : (unsigned long long *)(S.counters + 2);
+        if ((e = launch_counters_init(S.counters, (uint32_t)(S.n_nodes * cpn), stream)) != hipSuccess)
+            return hip_fail(e, "zero counters");
+        if ((e = launch_zero_u32((uint32_t *)S.args.acc, (int)(acc_bytes(S.n_nodes) / 4), stream)) != hipSuccess)
+            return hip_fail(e, "zero estimator sums");
+        // node tables from the device coordinates (they also set the chunk count)
+        if (S.tables && (e = launch_tables(t, stream)) != hipSuccess) return hip_fail(e, "node table kernels");
+        if (S.total_steps) {
+            if ((e = launch_zero_u32((uint32_t *)S.total_steps, 2, stream)) != hipSuccess)
+                return hip_fail(e, "zero total_steps");
+            a.total_steps = (unsigned long long *)S.total_steps;
+        } else {
+            // nobody asked for the count: short horizons skip it (the kernels
+            // skip a null count), others keep it in the counters block
+            a.total_steps = S.first_by_index ? nullptr : (unsigned long long *)(S.counters + 2);
+        }
     }
     a.queue = S.counters;
     a.n_paths = (uint32_t)S.n_paths;
@@ -333,21 +372,24 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     a.tile_shift = (uint32_t)__builtin_ctz((unsigned)S.plan.node_tile);
     int bpc = S.plan.blocks_per_cu;
     const bool expo = a.score_mode == FK_SCORE_EXPONENTIAL;
-    const int occ = expo ? expo_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.plan.block)
-                         : path_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.uniform,
-                                                         a.score_mode == FK_SCORE_BRIDGE, S.first_by_index,
-                                                         S.plan.block);
+    const int occ = S.lockstep ? short_kernel_max_blocks_per_cu(S.kind, S.time_mode, false, S.plan.block)
+                    : expo     ? expo_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.plan.block)
+                               : path_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.uniform,
+                                                               a.score_mode == FK_SCORE_BRIDGE, S.first_by_index,
+                                                               S.plan.block);
     if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
     const int grid = cap_grid(n_cu * bpc, a.total_chunks, S.plan.block);
     if ((e = timing_mark(timed, 0, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    e = expo ? launch_expo_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
-             : launch_paths(S.kind, S.time_mode, S.uniform, S.first_by_index, a, grid, S.plan.block, stream);
+    e = S.lockstep ? launch_short_paths(S.kind, S.time_mode, a, nullptr, grid, S.plan.block, stream)
+        : expo     ? launch_expo_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
+                   : launch_paths(S.kind, S.time_mode, S.uniform, S.first_by_index, a, grid, S.plan.block, stream);
     if (e != hipSuccess) return hip_fail(e, "path kernel launch");
     if ((e = timing_mark(timed, 1, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     FinalArgs f = S.fin;
     f.acc = a.acc;
     f.n_paths = S.n_paths;
     f.n_out = S.n_nodes;
+    if (S.lockstep) f.total_steps = (unsigned long long *)S.total_steps;
     if ((e = launch_finalize(f, stream)) != hipSuccess) return hip_fail(e, "finalize kernel launch");
     if ((e = timing_mark(timed, 2, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (timed) g_timing.recorded = true;
@@ -498,15 +540,18 @@ int fk_interface_solve(const fk_density *w, const fk_data *d, const double *pts,
     S.time_mode = w->time_mode;
     S.uniform = (level.dt_last == level.dt && level.cbm_last == level.cbm);
     S.plan = pl;
-    // Short paths (a mesh step of a few tens of sub-steps): each wavefront's
-    // first chunk by its grid index, and by default short_chunk paths per
-    // grab, which cuts the wavefronts' fixed costs per path; long ones 128,
-    // for the balance of the tail.
-    S.first_by_index = level.K <= 64 && d->score_mode != FK_SCORE_EXPONENTIAL;
-    if ((!plan || plan->chunk == 0) && S.first_by_index) {
+    // Few steps (a mesh step's sub-steps): the short-horizon kernel, or with
+    // a horizon over which paths leave the square, each wavefront's first
+    // chunk by its grid index and by default short_chunk paths per grab,
+    // which cuts the wavefronts' fixed costs per path.  Otherwise 128, for
+    // the balance of the tail.
+    S.lockstep = lockstep_paths(level.K, t, d->score_mode);
+    S.first_by_index = !S.lockstep && level.K <= 64 && d->score_mode != FK_SCORE_EXPONENTIAL;
+    if ((!plan || plan->chunk == 0) && (S.lockstep || S.first_by_index)) {
         int n_cu = 0;
         if ((rc = device_cus(&n_cu)) != FK_OK) return rc;
-        S.plan.chunk = short_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
+        S.plan.chunk = S.lockstep ? lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr)
+                                  : short_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
     }
     S.n_nodes = n_nodes;
     S.n_paths = n_paths;

@@ -684,22 +684,6 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
     if (lane == 0 && st != 0ull && a.total_steps) atomicAdd(a.total_steps, st);
 }
 
-// Gradient of the bilinear interpolant of a nodal grid at (x, y) (the cell
-// grid_bilinear uses); differences taken in FP64.
-__device__ __forceinline__ void grid_gradient(const double *g, int n, float x, float y, float &gx, float &gy) {
-    const float fx = x * (float)n, fy = y * (float)n;
-    int i = (int)floorf(fx), j = (int)floorf(fy);
-    i = min(max(i, 0), n - 1);
-    j = min(max(j, 0), n - 1);
-    const float ax = fx - (float)i, ay = fy - (float)j;
-    const double *r0 = g + (int64_t)j * (n + 1);
-    const double *r1 = r0 + (n + 1);
-    const float d0x = (float)(r0[i + 1] - r0[i]), d1x = (float)(r1[i + 1] - r1[i]);
-    const float d0y = (float)(r1[i] - r0[i]), d1y = (float)(r1[i + 1] - r0[i + 1]);
-    gx = (float)n * fmaf(ay, d1x - d0x, d0x);
-    gy = (float)n * fmaf(ax, d1y - d0y, d0y);
-}
-
 // Per cell (i, j) of the grid initial data, the FP32 terms grid_gradient
 // forms from the four corner values: (d0x, d1x - d0x, d0y, d1y - d0y) for
 // xi at tab[2 c] and for eta at tab[2 c + 1], c = j n + i.  The gradient
@@ -717,18 +701,6 @@ __global__ void grad_table_kernel(const double *gxi, const double *geta, int n, 
         const float d0y = (float)(r1[i] - r0[i]), d1y = (float)(r1[i + 1] - r0[i + 1]);
         tab[2 * c + comp] = make_float4(d0x, d1x - d0x, d0y, d1y - d0y);
     }
-}
-
-__device__ __forceinline__ void table_gradient(const float4 *tab, int n, int comp, float x, float y, float &gx,
-                                               float &gy) {
-    const float fx = x * (float)n, fy = y * (float)n;
-    int i = (int)floorf(fx), j = (int)floorf(fy);
-    i = min(max(i, 0), n - 1);
-    j = min(max(j, 0), n - 1);
-    const float ax = fx - (float)i, ay = fy - (float)j;
-    const float4 t = tab[2 * ((int64_t)j * n + i) + comp];
-    gx = (float)n * fmaf(ay, t.y, t.x);
-    gy = (float)n * fmaf(ax, t.w, t.z);
 }
 
 // One Euler-Maruyama step with its Brownian part (wx, wy); with BRIDGE the
@@ -951,15 +923,6 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
 // is g - sum_j G_j . dB_j.  No network: lanes need no common evaluation
 // points, so they start new paths at once, and each path's blocks sit at
 // fixed offsets from its start (schedule-independent results).
-struct MggArgs {
-    uint32_t stride_iters;       // the stride in iterations (2 steps each)
-    NodeAcc *acc_cv;             // [n_out] sums of the CV scores
-    float2 *cv_scores;           // [n_out * n_paths], absolute, or nullptr
-    const float4 *gtab;          // per-cell gradient table (grad_table_kernel), or NULL: read the grids
-    const float4 *gofs;          // [n_out] a gradient added to the mesh's at every block of the node's
-                                 // paths (the network's at the node: the grid base with the network
-                                 // taken only at the path's start), or NULL
-};
 
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE>
 __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, const MggArgs c) {
@@ -1950,6 +1913,13 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     const bool shift = (d->init_kind == FK_DATA_IDENTITY && d->bdry_kind == FK_DATA_IDENTITY);
     const bool uniform = (level.dt_last == level.dt && level.cbm_last == level.cbm);
     const bool mg = (form != FK_CV_DYNKIN);
+    // The grid base with a stride of at least the horizon takes the network
+    // only at each path's start: that is the node kernel's gradient, and the
+    // grid-control kernel adds it to the mesh's at every block (bitwise the
+    // same arithmetic as the network kernel, without its evaluation points).
+    const bool base_at_start = grid_base && (int64_t)stride >= (int64_t)level.K;
+    // the mesh-gradient control over a short horizon
+    const bool lockstep = (grid_ctl || base_at_start) && lockstep_paths(level.K, t, d->score_mode);
     // network forms on short paths (a mesh step's sub-steps): 256 per grab
     // by default (the network-control mesh step went from 29.9 to 22.6 ms on
     // the 768-cell run against 128); the grid control keeps 128.  Larger
@@ -1957,17 +1927,12 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     // Longer horizons: 32 to 128 by the path count, so that a solve with a
     // few hundred paths per node still spreads over every wavefront (the
     // Dynkin solve at 163 paths per node: 9.7 ms with 32, 11.7 with 128).
-    if ((!plan || plan->chunk == 0) && !grid_ctl && level.K <= 64) pl.chunk = 256;
+    if ((!plan || plan->chunk == 0) && lockstep) pl.chunk = lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
+    else if ((!plan || plan->chunk == 0) && !grid_ctl && level.K <= 64) pl.chunk = 256;
     else if ((!plan || plan->chunk == 0) && level.K > 64) pl.chunk = few_paths_chunk(n_nodes, n_paths, n_cu);
     const int64_t cpn = (n_paths + pl.chunk - 1) / pl.chunk;
     hipError_t e;
     uint32_t *counters = (uint32_t *)(ws + lay.counters);
-    if ((e = launch_zero_u32(counters, 64, stream)) != hipSuccess) return hip_fail(e, "zero counters");
-    // the plain and the CV sums lie back to back
-    if ((e = launch_zero_u32((uint32_t *)(ws + lay.acc), (int)((lay.total - lay.acc) / 4), stream)) != hipSuccess)
-        return hip_fail(e, "zero estimator sums");
-    if (total_steps && (e = launch_zero_u32((uint32_t *)total_steps, 2, stream)) != hipSuccess)
-        return hip_fail(e, "zero total_steps");
     // node tables from the device coordinates; the CV estimates have zero
     // shift (the Dynkin form's, u_hat at the node, is written by the node kernel)
     TableArgs tab{};
@@ -1986,7 +1951,18 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     tab.shift = shift ? 1 : 0;
     tab.sort = level.K > 64 ? 1 : 0;
     tab.horizon = (float)t;
-    if ((e = launch_tables(tab, stream)) != hipSuccess) return hip_fail(e, "node table kernels");
+    if (lockstep) {
+        if ((e = launch_short_tables(tab, (unsigned long long *)total_steps, stream)) != hipSuccess)
+            return hip_fail(e, "node table kernel");
+    } else {
+        if ((e = launch_zero_u32(counters, 64, stream)) != hipSuccess) return hip_fail(e, "zero counters");
+        // the plain and the CV sums lie back to back
+        if ((e = launch_zero_u32((uint32_t *)(ws + lay.acc), (int)((lay.total - lay.acc) / 4), stream)) != hipSuccess)
+            return hip_fail(e, "zero estimator sums");
+        if (total_steps && (e = launch_zero_u32((uint32_t *)total_steps, 2, stream)) != hipSuccess)
+            return hip_fail(e, "zero total_steps");
+        if ((e = launch_tables(tab, stream)) != hipSuccess) return hip_fail(e, "node table kernels");
+    }
 
     // per-node u_hat and integrand at the start
     CvNodeArgs na{};
@@ -2005,12 +1981,6 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         (e = cv_dispatch<CvNodeF>(w->kind, w->time_mode, true, na, (const uint16_t *)cv->s.bf, ts2, stream)) !=
             hipSuccess)
         return hip_fail(e, "node kernel launch");
-    // The grid base with a stride of at least the horizon takes the network
-    // only at each path's start: that is the node kernel's gradient, and the
-    // grid-control kernel adds it to the mesh's at every block (bitwise the
-    // same arithmetic as the network kernel, without its evaluation points).
-    const bool base_at_start = grid_base && (int64_t)stride >= (int64_t)level.K;
-
     PathArgs a{};
     SolveLaunch S{};
     S.args = a;
@@ -2051,10 +2021,14 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         c.acc_cv = acc_cv;
         c.gtab = grid_table(d, workspace, workspace_bytes, lay.total, stream, &e);
         if (e != hipSuccess) return hip_fail(e, "gradient table kernel launch");
-        const int occ = cv_dispatch<MggOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE);
+        const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, true, 256)
+                                 : cv_dispatch<MggOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE);
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
-        if ((e = cv_dispatch<MggLaunchF>(w->kind, w->time_mode, uniform, a, c, cap_grid(n_cu * bpc, a.total_chunks, 256), stream)) != hipSuccess)
-            return hip_fail(e, "control-variate path kernel launch");
+        const int grid = cap_grid(n_cu * bpc, a.total_chunks, 256);
+        a.masked = mask ? 1u : 0u;
+        e = lockstep ? launch_short_paths(w->kind, w->time_mode, a, &c, grid, 256, stream)
+                     : cv_dispatch<MggLaunchF>(w->kind, w->time_mode, uniform, a, c, grid, stream);
+        if (e != hipSuccess) return hip_fail(e, "control-variate path kernel launch");
     } else {
         MgArgs c{};
         c.bf = cv->s.bf;
@@ -2086,6 +2060,7 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     f.se_xi = se_xi;
     f.se_eta = se_eta;
     f.mask = mask;
+    if (lockstep) f.total_steps = (unsigned long long *)total_steps;
     if ((e = launch_finalize(f, stream)) != hipSuccess) return hip_fail(e, "finalize kernel launch");
     if ((e = timing_record(2, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (plain_xi && plain_eta && plain_se_xi && plain_se_eta) {
@@ -2099,9 +2074,11 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         P.kind = w->kind;
         P.time_mode = w->time_mode;
         P.uniform = uniform;
-        P.first_by_index = level.K <= 64;
+        P.lockstep = lockstep_paths(level.K, t, d->score_mode);
+        P.first_by_index = !P.lockstep && level.K <= 64;
         if ((rc = resolve_plan(nullptr, &P.plan)) != FK_OK) return rc;
-        if (P.first_by_index) P.plan.chunk = short_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
+        if (P.lockstep) P.plan.chunk = lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
+        else if (P.first_by_index) P.plan.chunk = short_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
         P.n_nodes = n_nodes;
         P.n_paths = n_paths;
         P.counters = counters;

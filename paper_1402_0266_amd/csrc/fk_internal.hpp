@@ -87,6 +87,20 @@ struct PathArgs {
     uint32_t total_chunks;           // host bound on the work chunks (grid size); the kernels
                                      // read the launch's own count from queue[kCtrTotal]
     uint32_t tile_shift;             // chunk order: interleave the chunks of 2^tile_shift nodes (0: node by node)
+    uint32_t masked;                 // short-horizon kernel: the chunk count is counters[kCtrActive] cpn (else
+                                     // total_chunks)
+};
+
+// The mesh-gradient control of the martingale form (kernels in fk_cv.hip and
+// fk_short.hip).
+struct MggArgs {
+    uint32_t stride_iters;       // the stride in iterations (2 steps each)
+    NodeAcc *acc_cv;             // [n_out] sums of the CV scores
+    float2 *cv_scores;           // [n_out * n_paths], absolute, or nullptr
+    const float4 *gtab;          // per-cell gradient table (grad_table_kernel), or NULL: read the grids
+    const float4 *gofs;          // [n_out] a gradient added to the mesh's at every block of the node's
+                                 // paths (the network's at the node: the grid base with the network
+                                 // taken only at the path's start), or NULL
 };
 
 // The estimator's last step: node sums -> means, standard errors, steps.
@@ -98,6 +112,7 @@ struct FinalArgs {
     double *xi, *eta, *se_xi, *se_eta;
     int64_t *steps;                  // or nullptr
     const uint8_t *mask;             // nodes solved (others' outputs untouched), or nullptr: all
+    unsigned long long *total_steps; // the nodes' steps are added to it, or nullptr
 };
 
 // Node tables of a single-level solve built on the device from its node
@@ -149,7 +164,8 @@ struct SolveLaunch {
     FinalArgs fin;       // outputs; sizes filled by enqueue_solve
     int kind, time_mode;
     bool uniform;
-    bool first_by_index;  // short horizons: each wavefront's first chunk by its grid index
+    bool first_by_index;  // few steps: each wavefront's first chunk by its grid index
+    bool lockstep;        // short horizons: the kernel of fk_short.hip (lockstep_paths)
     const TableArgs *tables;  // device-built tables (filled in by enqueue_solve), or nullptr: host tables
     fk_plan plan;
     int64_t n_nodes, n_paths;
@@ -175,6 +191,11 @@ int check_chunks(int64_t n_nodes, int64_t n_paths, const fk_plan &pl);
 // 2048 that still leaves 8 chunks per resident wavefront (28 per CU); 256
 // for masked solves.  The chunk only changes the schedule, never a result.
 int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
+// Whether a solve takes the short-horizon kernel (fk_short.hip).
+bool lockstep_paths(int64_t K, double t, int score_mode);
+// Its default chunk: 64 r paths for the r that finishes first when every
+// resident wavefront takes an equal number of chunks.
+int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // Default grab of the network and gradient-table forms on long horizons:
 // the largest of 128, 64, 32 paths that leaves at least 64 chunks per CU
 // (few paths per node leave the grid part-empty with larger grabs).
@@ -219,6 +240,14 @@ hipError_t launch_paths(int kind, int time_mode, bool uniform, bool first_by_ind
 hipError_t launch_finalize(const FinalArgs &a, hipStream_t s);
 // Device node tables (three small kernels; after the counters and sums are zeroed).
 hipError_t launch_tables(const TableArgs &t, hipStream_t s);
+// Node tables of the short-horizon kernel, cleared sums included, in the
+// caller's node order (one kernel; with a mask, two): sets
+// counters[kCtrActive], and *total_steps (or nullptr) to 0.
+hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_steps, hipStream_t s);
+// The short-horizon path kernel; mesh: the mesh-gradient control, or nullptr (plain).
+hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, const MggArgs *mesh, int grid, int block,
+                              hipStream_t s);
+int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, int block);
 // Zeroes a launch's 64 counter words and sets counters[kCtrTotal] (host tables).
 hipError_t launch_counters_init(uint32_t *counters, uint32_t total_chunks, hipStream_t s);
 // Bytes of the per-node estimator sums of n_out rows.

@@ -182,6 +182,57 @@ hipError_t launch_tables(const TableArgs &t, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Node tables of the short-horizon kernel (fk_short.hip): the sums cleared,
+// the nodes in the caller's order (their paths all cost about the same), or
+// with a mask the wanted ones packed.  A node outside the square keeps its
+// place, marked by a NaN low part: without a mask a node's slot is its index,
+// so nothing is counted.
+__global__ void short_table_kernel(const TableArgs t, unsigned long long *total_steps) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) {
+        *t.levels_out = t.level;
+        if (total_steps) *total_steps = 0ull;
+        if (!t.mask) t.counters[kCtrActive] = (uint32_t)t.n;
+    }
+    bool take = false, ok = false;
+    double x = 0.0, y = 0.0;
+    if (i < t.n) {
+        take = node_wanted(t, i, x, y, ok);
+        OutDev o{};
+        o.shift_x = t.shift ? (double)(float)x : 0.0;
+        o.shift_y = t.shift ? (double)(float)y : 0.0;
+        o.K = t.level.K;
+        t.outs_out[i] = o;
+        if (t.outs_zero_out) {
+            o.shift_x = o.shift_y = 0.0;
+            t.outs_zero_out[i] = o;
+        }
+        NodeAcc z{};
+        z.bad = take && !ok ? 1u : 0u;
+        t.acc[i] = z;
+        if (t.acc2) t.acc2[i] = z;
+    }
+    uint32_t slot = (uint32_t)i;
+    if (t.mask) slot = wave_bucket_add(t.counters + kCtrActive, take, 0);
+    if (!take) return;
+    NodeDev nd{};
+    nd.x = ok ? (float)x + 0.f : 0.5f;   // + 0: no -0 (the kernel's exit test)
+    nd.y = ok ? (float)y + 0.f : 0.5f;
+    nd.xlo = ok ? (float)(x - (double)nd.x) : __builtin_nanf("");
+    nd.ylo = ok ? (float)(y - (double)nd.y) : 0.f;
+    nd.nid = (uint32_t)i;
+    nd.level = 0;
+    nd.out = (uint64_t)i;
+    t.nodes_out[slot] = nd;
+}
+
+hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_steps, hipStream_t s) {
+    hipError_t e;
+    if (t.mask && (e = launch_counters_init(t.counters, 0u, s)) != hipSuccess) return e;
+    const unsigned blocks = (unsigned)std::max<int64_t>(1, (t.n + 255) / 256);
+    hipLaunchKernelGGL(short_table_kernel, dim3(blocks), dim3(256), 0, s, t, total_steps);
+    return hipGetLastError();
+}
 
 // BRIDGE: the Brownian-bridge crossing test after every step that stays
 // inside (score mode FK_SCORE_BRIDGE).  FIRST_BY_INDEX (short horizons): a
@@ -566,27 +617,34 @@ size_t acc_bytes(int64_t n_out) { return sizeof(NodeAcc) * (size_t)(n_out > 0 ? 
 
 __global__ void __launch_bounds__(256) fk_finalize_kernel(const FinalArgs f) {
     const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= f.n_out) return;
-    if (f.mask && !f.mask[o]) return;
-    const NodeAcc &A = f.acc[o];
-    const double N = (double)f.n_paths;
-    double mean[2], se[2];
+    if (o < f.n_out && (!f.mask || f.mask[o])) {
+        const NodeAcc &A = f.acc[o];
+        const double N = (double)f.n_paths;
+        double mean[2], se[2];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const double s1 = split_to_double(A.sum[2 * c]) * (1.0 / kQ1);
-        const double s2 = split_to_double(A.sum[2 * c + 1]) * (1.0 / kQ2);
-        const double m = s1 / N;
-        const double var = fmax((s2 - s1 * m) / (N - 1.0), 0.0);
-        mean[c] = m;
-        se[c] = sqrt(var / N);
+        for (int c = 0; c < 2; ++c) {
+            const double s1 = split_to_double(A.sum[2 * c]) * (1.0 / kQ1);
+            const double s2 = split_to_double(A.sum[2 * c + 1]) * (1.0 / kQ2);
+            const double m = s1 / N;
+            const double var = fmax((s2 - s1 * m) / (N - 1.0), 0.0);
+            mean[c] = m;
+            se[c] = sqrt(var / N);
+        }
+        const bool bad = A.bad != 0u;
+        const double nan = __builtin_nan("");
+        f.xi[o] = bad ? nan : f.outs[o].shift_x + mean[0];
+        f.eta[o] = bad ? nan : f.outs[o].shift_y + mean[1];
+        f.se_xi[o] = bad ? nan : se[0];
+        f.se_eta[o] = bad ? nan : se[1];
+        if (f.steps) f.steps[o] = (int64_t)A.steps;
     }
-    const bool bad = A.bad != 0u;
-    const double nan = __builtin_nan("");
-    f.xi[o] = bad ? nan : f.outs[o].shift_x + mean[0];
-    f.eta[o] = bad ? nan : f.outs[o].shift_y + mean[1];
-    f.se_xi[o] = bad ? nan : se[0];
-    f.se_eta[o] = bad ? nan : se[1];
-    if (f.steps) f.steps[o] = (int64_t)A.steps;
+    if (!f.total_steps) return;   // the launch's argument
+    // the launch's step count, one atomic per wavefront of nodes (the sums of
+    // nodes that were not solved are zero)
+    unsigned long long st = o < f.n_out ? f.acc[o].steps : 0ull;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) st += __shfl_xor(st, off, 64);
+    if ((threadIdx.x & 63u) == 0 && st != 0ull) atomicAdd(f.total_steps, st);
 }
 
 hipError_t launch_finalize(const FinalArgs &f, hipStream_t s) {

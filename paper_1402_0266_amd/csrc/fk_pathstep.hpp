@@ -146,6 +146,35 @@ __device__ __forceinline__ float grid_bilinear(const double *g, int n, float x, 
     return (1.f - ay) * ((1.f - ax) * v00 + ax * v01) + ay * ((1.f - ax) * v10 + ax * v11);
 }
 
+// Gradient of the bilinear interpolant of a nodal grid at (x, y) (the cell
+// grid_bilinear uses); differences taken in FP64.
+__device__ __forceinline__ void grid_gradient(const double *g, int n, float x, float y, float &gx, float &gy) {
+    const float fx = x * (float)n, fy = y * (float)n;
+    int i = (int)floorf(fx), j = (int)floorf(fy);
+    i = min(max(i, 0), n - 1);
+    j = min(max(j, 0), n - 1);
+    const float ax = fx - (float)i, ay = fy - (float)j;
+    const double *r0 = g + (int64_t)j * (n + 1);
+    const double *r1 = r0 + (n + 1);
+    const float d0x = (float)(r0[i + 1] - r0[i]), d1x = (float)(r1[i + 1] - r1[i]);
+    const float d0y = (float)(r1[i] - r0[i]), d1y = (float)(r1[i + 1] - r0[i + 1]);
+    gx = (float)n * fmaf(ay, d1x - d0x, d0x);
+    gy = (float)n * fmaf(ax, d1y - d0y, d0y);
+}
+
+// The same gradient of component comp from the per-cell table (fk_cv.hip,
+// grad_table_kernel).
+__device__ __forceinline__ void table_gradient(const float4 *tab, int n, int comp, float x, float y, float &gx,
+                                               float &gy) {
+    const float fx = x * (float)n, fy = y * (float)n;
+    int i = (int)floorf(fx), j = (int)floorf(fy);
+    i = min(max(i, 0), n - 1);
+    j = min(max(j, 0), n - 1);
+    const float ax = fx - (float)i, ay = fy - (float)j;
+    const float4 t = tab[2 * ((int64_t)j * n + i) + comp];
+    gx = (float)n * fmaf(ay, t.y, t.x);
+    gy = (float)n * fmaf(ax, t.w, t.z);
+}
 
 // Work chunks of a wavefront in the control-variate kernels (wave-uniform).
 // A wavefront's first chunk is its own index in the grid, so a launch starts
