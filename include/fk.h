@@ -376,9 +376,10 @@ void fk_batch_destroy(fk_batch_t b);
  * dt_mesh = +INFINITY solves the steady (elliptic) system of eq. (2),
  * Laplacian_h u + b . grad_h u = 0; xi_n / eta_n are then not read (may be
  * NULL).
- * Each sub-domain system is solved by banded LU without pivoting, in FP64
- * (unknowns numbered along the shorter side first, so the half-bandwidth is
- * min(mx, my) - 1); xi and eta share the factorisation.  Requires
+ * Each sub-domain system is solved by Gaussian elimination without pivoting,
+ * in FP64: nested dissection, or banded LU where its fronts would be too
+ * large (long sub-domains whose shorter side is above 64 cells); xi and eta
+ * share the factorisation.  Requires
  * |b| h / 2 < 1 (checked from the density's bound; FK_E_UNSUPPORTED
  * otherwise) and min(mx, my) <= 128 (FK_E_UNSUPPORTED).  A grid density
  * (FK_DENSITY_GRID) must be sampled on this mesh's grid (grid_n == N, else
@@ -396,7 +397,9 @@ void fk_batch_destroy(fk_batch_t b);
  *   xi_out, eta_out    device [(N+1)^2] FP64: the new mesh (boundary, interface
  *                      and sub-domain interiors); must not alias xi_n / eta_n
  *   workspace          device, subdomain_workspace_bytes_rect(px, py, N)
- *                      bytes, 256-B aligned (0 for an unsupported layout)
+ *                      bytes, 256-B aligned (0 for an unsupported layout); a
+ *                      smaller one that holds the banded LU is accepted and
+ *                      solved by it
  * FK_E_INVAL for px, py < 1, N outside [2, 65535], px or py not dividing N,
  * sub-domains under 2 cells a side, NULL arrays.
  */

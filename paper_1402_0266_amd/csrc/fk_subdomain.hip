@@ -10,13 +10,15 @@
 // diagonally dominant while |b| h / 2 < 1).  Plus the mesh-quality reduction.
 //
 // MI355X mapping: the unit square's N x N grid is split into px x py
-// sub-domains of mx x my cells.  A sub-domain's interior unknowns are
-// numbered along the shorter side first (the fast index), so its matrix is
-// banded with half-bandwidth q = the number of unknowns on that side, and
-// the fill of the LU stays in the band.  Large sub-domains are eliminated
-// from both ends at once (twisted: two workgroups meet at a separator line,
-// whose dense system one workgroup then solves).  The elimination window
-// lives in registers: one wavefront, a column per lane, for q < 32
+// sub-domains of mx x my cells.  The systems are solved by nested dissection
+// (fk_dissect.hip); sub-domains too long and wide for its fronts, and
+// workspaces too small for it, take the banded LU of this file: a
+// sub-domain's interior unknowns are numbered along the shorter side first
+// (the fast index), so its matrix is banded with half-bandwidth q = the
+// number of unknowns on that side, and the fill of the LU stays in the band.
+// Large sub-domains are eliminated from both ends at once (twisted: two
+// workgroups meet at a separator line, whose dense system one workgroup then
+// solves).  The elimination window lives in registers: one wavefront, a column per lane, for q < 32
 // (subdomain_lu_wave_kernel); otherwise 256 lanes as a 16 x 16 grid of
 // register tiles (subdomain_lu_tile_kernel).  Finished U rows go to the
 // workspace, and one wavefront per end back-substitutes.
@@ -29,6 +31,7 @@
 #include <type_traits>
 
 #include "fk.h"
+#include "fk_dissect.hpp"
 #include "fk_internal.hpp"
 
 namespace fk {
@@ -1190,6 +1193,30 @@ __global__ void __launch_bounds__(64) twisted_back_wave_kernel(const SubArgs a) 
     }
 }
 
+// Every unknown's drift terms (cx, cy) of its coefficients and right-hand
+// sides, x fastest, for the nested dissection (fk_dissect.hip).
+__global__ void __launch_bounds__(256) nd_assemble_kernel(const SubArgs a, double2 *cf, double2 *rh, int64_t total) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= total) return;
+    const int qx = a.mx - 1, qy = a.my - 1, N1 = a.N + 1;
+    const int n = qx * qy, sd = (int)(r / n), o = (int)(r - (int64_t)sd * n), y = o / qx, x = o - y * qx;
+    int i0, j0;
+    sub_origin(a, sd, i0, j0);
+    const int gi = i0 + 1 + x, gj = j0 + 1 + y;
+    double bx, by;
+    node_drift_f64(a, gi, gj, bx, by);
+    const double cxr = a.half_d_over_h * bx, cyr = a.half_d_over_h * by;
+    const double cE = -a.c - cxr, cW = -a.c + cxr, cN = -a.c - cyr, cS = -a.c + cyr;
+    const int64_t g = (int64_t)gj * N1 + gi;
+    double fx = a.steady ? 0.0 : a.xi_n[g], fy = a.steady ? 0.0 : a.eta_n[g];
+    if (x == qx - 1) { fx -= cE * a.xi_out[g + 1]; fy -= cE * a.eta_out[g + 1]; }
+    if (x == 0) { fx -= cW * a.xi_out[g - 1]; fy -= cW * a.eta_out[g - 1]; }
+    if (y == qy - 1) { fx -= cN * a.xi_out[g + N1]; fy -= cN * a.eta_out[g + N1]; }
+    if (y == 0) { fx -= cS * a.xi_out[g - N1]; fy -= cS * a.eta_out[g - N1]; }
+    cf[r] = make_double2(cxr, cyr);
+    rh[r] = make_double2(fx, fy);
+}
+
 // Dirichlet data of the output grids: outer boundary and interface nodes.
 __global__ void dirichlet_kernel(const SubArgs a, const double *iface_xi, const double *iface_eta, int64_t n_iface,
                                  int bdry_kind, const double *edge_cells, double *xi_out, double *eta_out) {
@@ -1352,12 +1379,27 @@ static int u_stride(int qf) {
 // Workspace: U rows, y values, row coefficients and right-hand sides (two
 // copies per sub-domain: natural and reversed order), the separator blocks,
 // and the edge integrals.
-static size_t sub_ws_bytes(const SubGeom &g, int N) {
+static size_t band_ws_bytes(const SubGeom &g, int N) {
     const size_t n = (size_t)g.n, us = (size_t)u_stride(g.qf);
     const size_t blocks = (size_t)g.px * g.py;
     return align256(blocks * n * us * sizeof(double)) + align256(blocks * 2 * n * sizeof(double)) +
            align256(2 * blocks * 4 * n * sizeof(double)) + align256(2 * blocks * 2 * n * sizeof(double)) +
            align256(blocks * sep_stride(g.qf) * sizeof(double)) + align256(4 * (size_t)N * sizeof(double));
+}
+
+// Workspace of the nested dissection: the edge integrals, every unknown's
+// drift terms and right-hand sides, and the tree's buffer.
+static size_t nd_ws_bytes(const SubGeom &g, int N, const NdTree &t) {
+    const size_t blocks = (size_t)g.px * g.py;
+    return align256(4 * (size_t)N * sizeof(double)) + 2 * align256(blocks * (size_t)g.n * sizeof(double2)) +
+           align256((size_t)t.doubles * sizeof(double));
+}
+
+// What a caller is asked for: room for either elimination.
+static size_t sub_ws_bytes(const SubGeom &g, int N) {
+    NdTree t;
+    const size_t band = band_ws_bytes(g, N);
+    return nd_tree(g.mx - 1, g.my - 1, (int64_t)g.px * g.py, &t) ? std::max(band, nd_ws_bytes(g, N, t)) : band;
 }
 
 // Twisted elimination (two workgroups per sub-domain) from this many
@@ -1485,8 +1527,11 @@ int subdomain_solve_rect(const fk_density *w, double t_w, double dt_mesh, int32_
     const int64_t n_iface = geo.n_iface;
     if ((!steady && (!xi_n || !eta_n)) || !xi_out || !eta_out || (n_iface > 0 && (!iface_xi || !iface_eta)))
         return fail(FK_E_INVAL, "NULL array");
-    const size_t need = sub_ws_bytes(geo, N);
-    if (!workspace || workspace_bytes < need) return fail(FK_E_NOMEM, "workspace too small: need %zu bytes", need);
+    // a workspace of the banded elimination's size is enough (the dissection
+    // takes a little more for some narrow bands)
+    const size_t need = band_ws_bytes(geo, N);
+    if (!workspace || workspace_bytes < need)
+        return fail(FK_E_NOMEM, "workspace too small: need %zu bytes", sub_ws_bytes(geo, N));
     if (((uintptr_t)workspace & 255u) != 0) return fail(FK_E_INVAL, "workspace must be 256-byte aligned");
     const double h = 1.0 / N;
     if (w->kind == FK_DENSITY_GRID && w->grid_n != N)
@@ -1538,6 +1583,14 @@ int subdomain_solve_rect(const fk_density *w, double t_w, double dt_mesh, int32_
     a.sbuf = (double *)ws;
     ws += align256(blocks * sep_stride(geo.qf) * sizeof(double));
     double *edge_cells = (double *)ws;
+    // nested dissection, unless its fronts would be too large (long, wide
+    // sub-domains) or the workspace too small for it; a few sub-domains of
+    // one leaf take the banded LU, which is one launch fewer (3 x 3 unknowns
+    // in 256 sub-domains: 19.5 us against 21.6; in 1024: 38.4 against 20.8)
+    NdTree tree;
+    const bool dissect = nd_tree(geo.mx - 1, geo.my - 1, (int64_t)blocks, &tree) &&
+                         nd_ws_bytes(geo, N, tree) <= workspace_bytes && (tree.depth > 0 || blocks > 256);
+    if (dissect) edge_cells = (double *)workspace;
     a.N = N;
     a.px = px;
     a.py = py;
@@ -1570,6 +1623,28 @@ int subdomain_solve_rect(const fk_density *w, double t_w, double dt_mesh, int32_
     hipLaunchKernelGGL(dirichlet_kernel, dim3((unsigned)((nthr + 255) / 256)), dim3(256), 0, stream, a, iface_xi,
                        iface_eta, n_iface, (int)bdry_kind, (const double *)edge_cells, xi_out, eta_out);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "dirichlet kernel launch");
+    if (dissect) {
+        const int64_t unknowns = (int64_t)blocks * geo.n;
+        const size_t node = align256((size_t)unknowns * sizeof(double2));
+        char *p = (char *)workspace + align256(4 * (size_t)N * sizeof(double));
+        NdArgs nd{};
+        nd.cf = (const double2 *)p;
+        nd.rh = (const double2 *)(p + node);
+        nd.buf = (double *)(p + 2 * node);
+        nd.c = a.c;
+        nd.xi_out = xi_out;
+        nd.eta_out = eta_out;
+        nd.diag = a.diag0 + 4.0 * a.c;
+        nd.N = N;
+        nd.px = px;
+        nd.mx = geo.mx;
+        nd.my = geo.my;
+        hipLaunchKernelGGL(nd_assemble_kernel, dim3((unsigned)((unknowns + 255) / 256)), dim3(256), 0, stream, a,
+                           (double2 *)nd.cf, (double2 *)nd.rh, unknowns);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "sub-domain assembly kernel launch");
+        if ((e = nd_solve(tree, nd, (int)blocks, stream)) != hipSuccess) return hip_fail(e, "sub-domain kernel launch");
+        return FK_OK;
+    }
     // two workgroups per sub-domain, meeting at the slow line qs/2
     a.twisted = (geo.n >= kTwistedMinN && geo.qs >= 3) ? 1 : 0;
     a.sep = (geo.qs / 2) * geo.qf;
