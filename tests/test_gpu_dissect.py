@@ -34,6 +34,7 @@ def _cuda(a):
     (1, 1, 2), (1, 1, 3), (2, 3, 6),      # one unknown; two by two; two by one
     (1, 1, 4), (1, 1, 5), (4, 3, 12),     # 9, 16 and 6 unknowns: a leaf, two leaves
     (2, 2, 10), (3, 5, 60),               # 4 x 4; 19 x 11
+    (20, 20, 40), (18, 18, 72),           # many sub-domains of one leaf (few are banded)
     (16, 1, 32), (1, 16, 48),             # strips one and two unknowns wide
     (2, 2, 26), (5, 3, 60), (8, 8, 96),   # odd and even halves, few and many sub-domains
     (2, 1, 100), (3, 3, 99), (1, 1, 127), (1, 1, 128),
