@@ -2,8 +2,8 @@
 // (George 1973) in its multifrontal form.
 //
 // A sub-domain's grid of unknowns is a box.  A box is split by a grid line
-// across its longer side, both halves likewise, down to leaves of at most
-// kLeaf unknowns.  With 5-point rows, a box's unknowns couple to the rest of
+// across its longer side, both halves likewise, down to leaves of a few
+// (nd_leaf) unknowns.  With 5-point rows, a box's unknowns couple to the rest of
 // the grid only through the unknowns on the lines around it (no corners), so
 // going up the tree each box eliminates its separator (a leaf: all it has)
 // from a dense front over
@@ -28,19 +28,23 @@
 // 16-byte read per register row and column), and every lane applies both to
 // its tile.
 //
-// Measured, 8 x 8 sub-domains of 95 x 95 unknowns: 0.67 ms against 3.98 ms for
-// the banded LU from both ends (4512 dependent pivots, 128 workgroups); the
-// fronts of the ten levels take 64, 53, 45, 50 (one wavefront each, bound by
-// instructions: ~1000 a front, and by the 1.1 GB of Schur complements and kept
-// rows), 50, 70, 72, 58, 49 and 43 us (bound by the chain of pivots, ~0.9 us a
-// pair), the way down 18 and 91 us.  2 x 2 of 19 x 19: 73 us against 190.
+// Measured, 8 x 8 sub-domains of 95 x 95 unknowns: 0.66 ms against 3.98 ms for
+// the banded LU from both ends (4512 dependent pivots, 128 workgroups).  The
+// fronts of the ten levels take 66, 52, 45, 50 us (one wavefront each, bound
+// by instructions -- about 1000 a front -- and by 1.1 GB of Schur complements
+// and kept rows), 50, 70, 73, 51, 47 and 40 us (bound by the chain of pivots,
+// 0.8 us a pair); the way down 18 and 86 us.  2 x 2 sub-domains of 19 x 19
+// with their edge data: 56 us against 192 us.
 #include "fk_dissect.hpp"
 
 #include <algorithm>
 
 namespace fk {
 
-constexpr int kLeaf = 12;    // most unknowns of a leaf
+// Most unknowns of a leaf: few with many sub-domains (the work counts: 12
+// against 30 took 240 us off the lowest levels of 64 x 95 x 95), more with few
+// (the levels count: 20 against 12 took one of six off 4 x 19 x 19).
+constexpr int nd_leaf(int64_t blocks) { return blocks >= 32 ? 12 : 20; }
 
 // Box [x0, x1) x [y0, y1) of a sub-domain's unknowns (empty if a side is not
 // positive).
@@ -435,7 +439,7 @@ bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t) {
         if (l >= kNdMaxLevels || l > 16) return false;
         int most = 0;
         for (int i = 0; i < n; ++i) most = std::max(most, cur[i].w * cur[i].h);
-        const bool leaf = most <= kLeaf;
+        const bool leaf = most <= nd_leaf(blocks);
         int s = 0, b = 0;
         for (int i = 0; i < n; ++i) {
             const Kind &k = cur[i];
@@ -509,10 +513,12 @@ hipError_t nd_solve(const NdTree &t, const NdArgs &a, int blocks, hipStream_t s)
     for (int l = t.depth; l >= 0; --l) {
         const int f = t.lv[l].s + t.lv[l].b;
         const int64_t fronts = (int64_t)blocks << l;
-        // many fronts: as few lanes each as hold it (the work per lane
-        // outweighs the pivots' fixed cost); few: small tiles, so that a
-        // pivot takes little time
-        const int ln = fronts > 256 ? (f <= 64 ? 8 : f <= 144 ? 16 : 32) : (f <= 48 ? 16 : 32);
+        // many small fronts: a wavefront each (the work per lane outweighs the
+        // pivots' fixed cost); else 256 lanes, which take a pair of pivots
+        // sooner than 1024 do (every wavefront repeats the pivots'
+        // reciprocals; 95 pivots: 40 us against 43, 47 in a front of 142: 47
+        // against 49) as long as the tile fits their registers
+        const int ln = fronts > 256 && f <= 64 ? 8 : f <= 144 ? 16 : 32;
         if ((e = nd_launch(ln, (f + ln - 1) / ln, t, a, (unsigned)fronts, l, s)) != hipSuccess) return e;
     }
     // down: the upper levels by one workgroup per sub-domain, the boxes

@@ -237,16 +237,38 @@ __global__ void density_sample_kernel(const SubArgs a, int n, double *out) {
     out[t] = density_f64(a, ox, oy, (double)(t % n1) / n, (double)(t / n1) / n);
 }
 
-// int_0^{i/N} w / int_0^1 w along edge e, from the cell integrals (summed in
-// a fixed order).
+// int_0^{i/N} w / int_0^1 w along edge e, for each thread's own i, from the N
+// cell integrals (a workgroup of 256 threads; all call it): each thread sums a
+// run of cells, one wavefront scans the runs (both in a fixed order), and a
+// node's part is the runs before it plus the cells of its run before it.
 __device__ double edge_fraction(const double *cells, int N, int e, int i) {
-    double part = 0.0, total = 0.0;
-    for (int c = 0; c < N; ++c) {
-        const double v = cells[e * N + c];
-        if (c < i) part += v;
-        total += v;
+    __shared__ double run[257];
+    const int t = threadIdx.x, per = (N + 255) / 256;
+    double v = 0.0;
+    for (int c = t * per; c < min(N, (t + 1) * per); ++c) v += cells[e * N + c];
+    if (t == 0) run[0] = 0.0;
+    run[t + 1] = v;
+    __syncthreads();
+    if (t < 64) {
+        double q[4];
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = s += run[4 * t + k + 1];
+        double before = s;   // inclusive scan of the lanes' sums
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double up = __shfl_up(before, off, 64);
+            if (t >= off) before += up;
+        }
+        before -= s;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) run[4 * t + k + 1] = before + q[k];
     }
-    return part / total;
+    __syncthreads();
+    const int r = min(i, N) / per;
+    double part = run[r];
+    for (int c = r * per; c < min(i, N); ++c) part += cells[e * N + c];
+    return part / run[256];
 }
 
 // Lane `l` of a wave-uniform index: its FP64 value, in scalar registers.
@@ -1221,37 +1243,36 @@ __global__ void __launch_bounds__(256) nd_assemble_kernel(const SubArgs a, doubl
 __global__ void dirichlet_kernel(const SubArgs a, const double *iface_xi, const double *iface_eta, int64_t n_iface,
                                  int bdry_kind, const double *edge_cells, double *xi_out, double *eta_out) {
     const int N = a.N, px = a.px, mx = a.mx, my = a.my;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int N1 = N + 1;
-    const int64_t n_bd = 4 * (int64_t)N;
-    if (t < n_bd) {
-        // boundary nodes walked as four edges of N nodes each
-        const int side = (int)(t / N), o = (int)(t % N);
+    // the first 4 nb workgroups take the four edges (N nodes each: the corner
+    // at its start and no other), the rest the interface nodes
+    const int nb = (N + 255) / 256;
+    if ((int)blockIdx.x < 4 * nb) {
+        const int side = blockIdx.x / nb, o = (blockIdx.x % nb) * 256 + threadIdx.x;
         int i, j;
         if (side == 0) { i = o; j = 0; }
         else if (side == 1) { i = N; j = o; }
         else if (side == 2) { i = N - o; j = N; }
         else { i = 0; j = N - o; }
-        const int64_t g = (int64_t)j * N1 + i;
-        double xv = 0.0, ev = 0.0;
-        if (bdry_kind == FK_DATA_IDENTITY) {
-            xv = (double)i / N;
-            ev = (double)j / N;
-        } else if (bdry_kind == FK_DATA_EQUIDISTRIBUTED) {
+        double xv = (double)i / N, ev = (double)j / N;
+        if (bdry_kind == FK_DATA_ZERO) xv = ev = 0.0;
+        if (bdry_kind == FK_DATA_EQUIDISTRIBUTED) {
             // xi = 0 / 1 on the left / right edges, eta = 0 / 1 on the bottom /
             // top edges; on the others the 1-D equidistribution of w
-            if (i == 0) xv = 0.0;
-            else if (i == N) xv = 1.0;
-            else xv = edge_fraction(edge_cells, N, j == 0 ? 0 : 1, i);
-            if (j == 0) ev = 0.0;
-            else if (j == N) ev = 1.0;
-            else ev = edge_fraction(edge_cells, N, i == 0 ? 2 : 3, j);
+            const int edge = side == 0 ? 0 : side == 1 ? 3 : side == 2 ? 1 : 2;
+            const int along = (side & 1) ? j : i;
+            const double f = edge_fraction(edge_cells, N, edge, max(along, 0));
+            xv = (side & 1) ? (side == 1 ? 1.0 : 0.0) : (i == 0 ? 0.0 : i == N ? 1.0 : f);
+            ev = (side & 1) ? (j == 0 ? 0.0 : j == N ? 1.0 : f) : (side == 0 ? 0.0 : 1.0);
         }
-        xi_out[g] = xv;
-        eta_out[g] = ev;
+        if (o < N) {
+            const int64_t g = (int64_t)j * N1 + i;
+            xi_out[g] = xv;
+            eta_out[g] = ev;
+        }
         return;
     }
-    const int64_t f = t - n_bd;
+    const int64_t f = (int64_t)(blockIdx.x - 4 * nb) * blockDim.x + threadIdx.x;
     if (f >= n_iface) return;
     // canonical order: vertical lines x = a/px (nodes y = j/N), then
     // horizontal lines y = c/py without the crossings
@@ -1271,6 +1292,10 @@ __global__ void dirichlet_kernel(const SubArgs a, const double *iface_xi, const 
     const int64_t g = (int64_t)j * N1 + i;
     xi_out[g] = iface_xi[f];
     eta_out[g] = iface_eta[f];
+}
+
+static unsigned dirichlet_blocks(int N, int64_t n_iface) {
+    return (unsigned)(4 * ((N + 255) / 256) + (n_iface + 255) / 256);
 }
 
 // min Jacobian and max skewness over all cells (cell-centred differences),
@@ -1647,8 +1672,7 @@ int subdomain_solve_rect(const fk_density *w, double t_w, double dt_mesh, int32_
                            edge_cells);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "edge integral kernel launch");
     }
-    const int64_t nthr = 4 * (int64_t)N + n_iface;
-    hipLaunchKernelGGL(dirichlet_kernel, dim3((unsigned)((nthr + 255) / 256)), dim3(256), 0, stream, a, iface_xi,
+    hipLaunchKernelGGL(dirichlet_kernel, dim3(dirichlet_blocks(N, n_iface)), dim3(256), 0, stream, a, iface_xi,
                        iface_eta, n_iface, (int)bdry_kind, (const double *)edge_cells, xi_out, eta_out);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "dirichlet kernel launch");
     if (dissect) {
@@ -1734,7 +1758,7 @@ int fk_boundary_data(const fk_density *w, double t_w, int32_t n, int32_t bdry_ki
                            edge_cells);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "edge integral kernel launch");
     }
-    hipLaunchKernelGGL(dirichlet_kernel, dim3((unsigned)((4 * n + 255) / 256)), dim3(256), 0, stream, a,
+    hipLaunchKernelGGL(dirichlet_kernel, dim3(dirichlet_blocks(n, 0)), dim3(256), 0, stream, a,
                        (const double *)nullptr, (const double *)nullptr, (int64_t)0, (int)bdry_kind,
                        (const double *)edge_cells, xi_out, eta_out);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "boundary kernel launch");
