@@ -101,8 +101,8 @@ struct NetLds {
     float b1[64], b2[64], b3[64];
     float w4[128];
     float b4[2];
-    uint16_t w2[64 * kWS];
-    uint16_t w3[64 * kWS];
+    alignas(16) uint16_t w2[64 * kWS];
+    alignas(16) uint16_t w3[64 * kWS];
     // for the gradient evaluation: per unit u (K2 w0, K2 w1, K2 w2, K2 b1);
     // per group of four units 4 q .. 4 q + 3 (the four a lane takes from one
     // 16x16 output tile) K2 b2, K2 b3, W4[0] and W4[1]
@@ -119,21 +119,23 @@ __device__ __forceinline__ int wcol(int k) {
     return (k & ~31) | (8 * ((b & 15) >> 2) + 4 * (b >> 4) + (b & 3));
 }
 
-__device__ void load_net(NetLds &N, const uint16_t *bf) {
-    for (int i = threadIdx.x; i < 192; i += blockDim.x) N.w1[i] = bf2f(bf[OW1 + i]);
-    for (int i = threadIdx.x; i < 64; i += blockDim.x) {
+// By threads t of nt.
+__device__ void load_net(NetLds &N, const uint16_t *bf, int t, int nt) {
+    for (int i = t; i < 192; i += nt) N.w1[i] = bf2f(bf[OW1 + i]);
+    for (int i = t; i < 64; i += nt) {
         N.b1[i] = bf2f(bf[OB1 + i]);
         N.b2[i] = bf2f(bf[OB2 + i]);
         N.b3[i] = bf2f(bf[OB3 + i]);
     }
-    for (int i = threadIdx.x; i < 128; i += blockDim.x) N.w4[i] = bf2f(bf[OW4 + i]);
-    if (threadIdx.x < 2) N.b4[threadIdx.x] = bf2f(bf[OB4 + threadIdx.x]);
-    for (int i = threadIdx.x; i < 4096; i += blockDim.x) {
-        const int r = i >> 6, c = i & 63;
-        N.w2[r * kWS + wcol(c)] = bf[OW2 + i];
-        N.w3[r * kWS + wcol(c)] = bf[OW3 + i];
+    for (int i = t; i < 128; i += nt) N.w4[i] = bf2f(bf[OW4 + i]);
+    if (t < 2) N.b4[t] = bf2f(bf[OB4 + t]);
+    // four units at a time: they stay together in an operand's order
+    for (int i = 4 * t; i < 4096; i += 4 * nt) {
+        const int at = (i >> 6) * kWS + wcol(i & 63);
+        *reinterpret_cast<uint2 *>(N.w2 + at) = *reinterpret_cast<const uint2 *>(bf + OW2 + i);
+        *reinterpret_cast<uint2 *>(N.w3 + at) = *reinterpret_cast<const uint2 *>(bf + OW3 + i);
     }
-    for (int u = threadIdx.x; u < 64; u += blockDim.x) {
+    for (int u = t; u < 64; u += nt) {
         const float w0 = bf2f(bf[OW1 + 3 * u]), w1 = bf2f(bf[OW1 + 3 * u + 1]), w2 = bf2f(bf[OW1 + 3 * u + 2]);
         N.g1[u] = make_float4(K2 * w0, K2 * w1, K2 * w2, K2 * bf2f(bf[OB1 + u]));
         reinterpret_cast<float *>(N.q2)[u] = K2 * bf2f(bf[OB2 + u]);
@@ -142,6 +144,7 @@ __device__ void load_net(NetLds &N, const uint16_t *bf) {
         reinterpret_cast<float *>(N.q41)[u] = bf2f(bf[OW4 + 64 + u]);
     }
 }
+__device__ void load_net(NetLds &N, const uint16_t *bf) { load_net(N, bf, threadIdx.x, blockDim.x); }
 
 // tanh and its forward-mode channels: h = tanh(a), s = 1 - h^2 = 4 e / (1+e)^2
 // with e = exp(2a); dh = s da; Laplacian h = s (Laplacian a - 2 h |grad a|^2).
@@ -1114,9 +1117,10 @@ struct TrainLds {
     float z[3][64];
     float y[2][64];
     float dout[2][64];
+    float valid[64];
     float H1[64 * kTS], H2[64 * kTS], H3[64 * kTS];
     float D[64 * kTS], E[64 * kTS];
-    float red[256];
+    float red[2];
 };
 
 // Per-call values of fk_cv_train, read by the kernels from device memory so
@@ -1132,11 +1136,11 @@ struct TrainDesc {
     float loss_scale;      // 1 / (2 batch)
     float *loss_out;       // [steps] or nullptr
     float tscale2, base;
-    int64_t pad;
+    float c1, c2;          // bias corrections of the current step (written by its gradient kernel)
 };
 
 struct TrainArgs {
-    const TrainDesc *desc; // iteration `iter` of fk_cv_train (the fields below from desc), or nullptr
+    TrainDesc *desc;       // iteration `iter` of fk_cv_train (the fields below from desc), or nullptr
     uint32_t iter;
     const uint16_t *bf;
     const float *txy;      // [n][3]
@@ -1151,32 +1155,42 @@ struct TrainArgs {
 };
 
 // C[M = 64][N = 64] = A[64 x K] B[K x 64] with K = 64, A and B given by
-// element accessors, on MFMA (two 32-deep K blocks); each wavefront computes
-// four 16 x 16 tiles and hands each result fragment to `sink(row, col, value)`.
+// element accessors, on MFMA (two 32-deep K blocks); each of the workgroup's
+// 16 wavefronts computes a 16 x 16 tile and hands its result fragment to
+// `sink(row, col, value)`.
 template <typename FA, typename FB, typename FS>
 __device__ __forceinline__ void wave_gemm64(FA A, FB B, FS sink) {
     const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15, w = threadIdx.x >> 6;
-#pragma unroll 1
-    for (int t = 0; t < 4; ++t) {
-        const int tile = 4 * w + t, mt = tile >> 2, nt = tile & 3;
-        fk_f4 acc = {0.f, 0.f, 0.f, 0.f};
+    const int mt = w >> 2, nt = w & 3;
+    fk_f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            fk_b8 a, b;
+    for (int kb = 0; kb < 2; ++kb) {
+        fk_b8 a, b;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int k = ku(kb, g, j);
-                a[j] = (__bf16)A(16 * mt + n, k);
-                b[j] = (__bf16)B(k, 16 * nt + n);
-            }
-            acc = mfma32(a, b, acc);
+        for (int j = 0; j < 8; ++j) {
+            const int k = ku(kb, g, j);
+            a[j] = (__bf16)A(16 * mt + n, k);
+            b[j] = (__bf16)B(k, 16 * nt + n);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sink(16 * mt + 4 * g + i, 16 * nt + n, acc[i]);
+        acc = mfma32(a, b, acc);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sink(16 * mt + 4 * g + i, 16 * nt + n, acc[i]);
 }
 
-__global__ void __launch_bounds__(256) cv_grad_kernel(TrainArgs ta) {
+// Bias corrections of Adam step `step` (>= 1), in FP64 then rounded.
+__device__ __forceinline__ void adam_corrections(int64_t step, float &c1, float &c2) {
+    c1 = (float)(1.0 - pow(0.9, (double)step));
+    c2 = (float)(1.0 - pow(0.999, (double)step));
+}
+
+// One 64-sample tile per workgroup of 16 wavefronts: a step's 128 tiles leave
+// half the chip idle whatever a workgroup's size, so what counts is the chain
+// of its phases -- with a 16 x 16 product tile and four activations a thread
+// in each they take ~9 us; with four wavefronts, 22 us.
+constexpr int kGradThreads = 1024;
+
+__global__ void __launch_bounds__(kGradThreads) cv_grad_kernel(TrainArgs ta) {
     if (ta.desc) {
         const TrainDesc &d = *ta.desc;
         ta.txy = d.txy;
@@ -1191,32 +1205,41 @@ __global__ void __launch_bounds__(256) cv_grad_kernel(TrainArgs ta) {
     extern __shared__ char smem[];
     TrainLds &S = *reinterpret_cast<TrainLds *>(smem);
     const int tid = threadIdx.x;
-    load_net(S.net, ta.bf);
     float *P = ta.partial + (int64_t)blockIdx.x * (kNP + 1);
-    // ---- the tile's samples ----------------------------------------------------
-    if (tid < 64) {
+    // ---- the tile's samples (the last wavefront), the network (the others) -------
+    if (tid >= kGradThreads - 64) {
+        const int s = tid & 63;
         int64_t idx;
         bool valid = true;
         if (ta.full) {
-            idx = (int64_t)blockIdx.x * 64 + tid;
+            idx = (int64_t)blockIdx.x * 64 + s;
             valid = idx < ta.n;
             if (!valid) idx = 0;
         } else {
-            const int64_t j = (int64_t)blockIdx.x * 64 + tid;
+            const int64_t j = (int64_t)blockIdx.x * 64 + s;
             const PhiloxOut r = philox4x32_10((uint32_t)j, ta.step, 0u, 2u, ta.key0, ta.key1);
             idx = (int64_t)(r.r0 % (uint32_t)ta.n);
             valid = j < ta.batch;
         }
-        S.z[0][tid] = ta.txy[3 * idx] * ta.tscale2 - 1.f;
-        S.z[1][tid] = 2.f * ta.txy[3 * idx + 1] - 1.f;
-        S.z[2][tid] = 2.f * ta.txy[3 * idx + 2] - 1.f;
-        S.y[0][tid] = fmaf(-ta.base, ta.txy[3 * idx + 1], ta.target[2 * idx]);
-        S.y[1][tid] = fmaf(-ta.base, ta.txy[3 * idx + 2], ta.target[2 * idx + 1]);
-        S.dout[0][tid] = valid ? 1.f : 0.f;  // validity mask until the residual is known
+        S.z[0][s] = ta.txy[3 * idx] * ta.tscale2 - 1.f;
+        S.z[1][s] = 2.f * ta.txy[3 * idx + 1] - 1.f;
+        S.z[2][s] = 2.f * ta.txy[3 * idx + 2] - 1.f;
+        S.y[0][s] = fmaf(-ta.base, ta.txy[3 * idx + 1], ta.target[2 * idx]);
+        S.y[1][s] = fmaf(-ta.base, ta.txy[3 * idx + 2], ta.target[2 * idx + 1]);
+        S.valid[s] = valid ? 1.f : 0.f;
+        // this step's bias corrections, for the Adam kernel that follows
+        if (ta.desc && blockIdx.x == 0 && s == 0) {
+            float c1, c2;
+            adam_corrections((int64_t)ta.desc->step0 + ta.iter + 1, c1, c2);
+            ta.desc->c1 = c1;
+            ta.desc->c2 = c2;
+        }
+    } else {
+        load_net(S.net, ta.bf, tid, kGradThreads - 64);
     }
     __syncthreads();
     // ---- forward ------------------------------------------------------------------
-    for (int e = tid; e < 4096; e += 256) {
+    for (int e = tid; e < 4096; e += kGradThreads) {
         const int u = e >> 6, s = e & 63;
         const float a = fmaf(S.net.w1[3 * u], S.z[0][s],
                              fmaf(S.net.w1[3 * u + 1], S.z[1][s], fmaf(S.net.w1[3 * u + 2], S.z[2][s], S.net.b1[u])));
@@ -1229,45 +1252,40 @@ __global__ void __launch_bounds__(256) cv_grad_kernel(TrainArgs ta) {
     wave_gemm64([&](int m, int k) { return bf2f(S.net.w3[m * kWS + wcol(k)]); }, [&](int k, int n) { return S.H2[k * kTS + n]; },
                 [&](int m, int n, float v) { S.H3[m * kTS + n] = tanhf(v + S.net.b3[m]); });
     __syncthreads();
-    // outputs, residuals and d loss / d out (mean over batch and both outputs)
-    float lsum = 0.f;
+    // outputs, residuals, d loss / d out (mean over batch and both outputs), and
+    // the tile's loss
     if (tid < 128) {
         const int o = tid >> 6, s = tid & 63;
         float acc = S.net.b4[o];
+#pragma unroll 16
         for (int u = 0; u < 64; ++u) acc = fmaf(S.net.w4[64 * o + u], S.H3[u * kTS + s], acc);
-        const float valid = S.dout[0][s];
-        const float res = (acc - S.y[o][s]) * valid;
-        lsum = res * res;
-        S.red[tid] = 2.f * res / (2.f * (float)ta.batch);
-    }
-    __syncthreads();
-    if (tid < 128) S.dout[tid >> 6][tid & 63] = S.red[tid];
-    // loss of the tile
-    {
-        float v = lsum;
+        const float res = (acc - S.y[o][s]) * S.valid[s];
+        S.dout[o][s] = 2.f * res / (2.f * (float)ta.batch);
+        float v = res * res;
+        asm("" : "+v"(v));   // the square rounded, as it is summed
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        __syncthreads();
-        if ((tid & 63) == 0) S.red[tid >> 6] = v;
-        __syncthreads();
-        if (tid == 0) P[kNP] = S.red[0] + S.red[1] + S.red[2] + S.red[3];
+        if (s == 0) S.red[o] = v;
     }
     __syncthreads();
+    if (tid == 0) P[kNP] = S.red[0] + S.red[1];
     // ---- backward -----------------------------------------------------------------
-    // W4, b4
-    if (tid < 128) {
-        const int o = tid >> 6, u = tid & 63;
+    // W4, b4 (the last wavefronts, beside the others' share of dA3)
+    if (tid >= kGradThreads - 128) {
+        const int o = (tid >> 6) & 1, u = tid & 63;
         float acc = 0.f;
+#pragma unroll 16
         for (int s = 0; s < 64; ++s) acc = fmaf(S.dout[o][s], S.H3[u * kTS + s], acc);
         P[OW4 + 64 * o + u] = acc;
-    } else if (tid < 130) {
-        const int o = tid - 128;
+    } else if (tid >= kGradThreads - 130) {
+        const int o = tid - (kGradThreads - 130);
         float acc = 0.f;
+#pragma unroll 16
         for (int s = 0; s < 64; ++s) acc += S.dout[o][s];
         P[OB4 + o] = acc;
     }
     // dA3 = (W4^T dout) (1 - H3^2)
-    for (int e = tid; e < 4096; e += 256) {
+    for (int e = tid; e < 4096; e += kGradThreads) {
         const int u = e >> 6, s = e & 63;
         const float h = S.H3[u * kTS + s];
         S.D[u * kTS + s] = fmaf(S.net.w4[u], S.dout[0][s], S.net.w4[64 + u] * S.dout[1][s]) * (1.f - h * h);
@@ -1278,6 +1296,7 @@ __global__ void __launch_bounds__(256) cv_grad_kernel(TrainArgs ta) {
                 [&](int m, int n, float v) { P[OW3 + 64 * m + n] = v; });
     if (tid < 64) {
         float acc = 0.f;
+#pragma unroll 16
         for (int s = 0; s < 64; ++s) acc += S.D[tid * kTS + s];
         P[OB3 + tid] = acc;
     }
@@ -1293,6 +1312,7 @@ __global__ void __launch_bounds__(256) cv_grad_kernel(TrainArgs ta) {
                 [&](int m, int n, float v) { P[OW2 + 64 * m + n] = v; });
     if (tid < 64) {
         float acc = 0.f;
+#pragma unroll 16
         for (int s = 0; s < 64; ++s) acc += S.E[tid * kTS + s];
         P[OB2 + tid] = acc;
     }
@@ -1307,23 +1327,61 @@ __global__ void __launch_bounds__(256) cv_grad_kernel(TrainArgs ta) {
     if (tid < 192) {
         const int u = tid / 3, j = tid % 3;
         float acc = 0.f;
+#pragma unroll 16
         for (int s = 0; s < 64; ++s) acc = fmaf(S.D[u * kTS + s], S.z[j][s], acc);
         P[OW1 + tid] = acc;
-    } else {
-        for (int u = tid - 192; u < 64; u += 64) {
-            float acc = 0.f;
-            for (int s = 0; s < 64; ++s) acc += S.D[u * kTS + s];
-            P[OB1 + u] = acc;
-        }
+    } else if (tid < 256) {
+        const int u = tid - 192;
+        float acc = 0.f;
+#pragma unroll 16
+        for (int s = 0; s < 64; ++s) acc += S.D[u * kTS + s];
+        P[OB1 + u] = acc;
     }
 }
 
-// Sum of the tiles' gradients in a fixed order: grad[i] (and the loss).
-__global__ void cv_sum_kernel(const float *partial, int tiles, float *grad, float *loss, float loss_scale) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > kNP) return;
+// The gradients' sum over the tiles, in tile order, by workgroups of four
+// wavefronts for 64 entries: each wavefront loads every fourth run of 32
+// tiles (all loads in flight), the first adds them up from LDS one after the
+// other.  4.5 MB of partial sums for 128 tiles: with the loads of a thread one
+// after the other, on 35 workgroups, the Adam kernel took 32 us, now 4.
+constexpr int kSumBlocks = (kNP + 1 + 63) / 64;
+
+// Sum of entry 64 blockIdx.x + lane, in the first wavefront (every thread of
+// the workgroup calls it).
+__device__ __forceinline__ float sum_tiles(const float *partial, int tiles) {
+    __shared__ float part[128][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = min(blockIdx.x * 64 + lane, (unsigned)kNP);
     float acc = 0.f;
-    for (int t = 0; t < tiles; ++t) acc += partial[(int64_t)t * (kNP + 1) + i];
+    for (int t0 = 0; t0 < tiles; t0 += 128) {
+        float v[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) v[k] = partial[(int64_t)min(t0 + 32 * w + k, tiles - 1) * (kNP + 1) + i];
+        if (t0 > 0) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 32; ++k) part[32 * w + k][lane] = v[k];
+        __syncthreads();
+        if (w == 0) {
+            const int n = min(128, tiles - t0);
+            int t = 0;
+            for (; t + 16 <= n; t += 16) {
+                float q[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) q[k] = part[t + k][lane];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) acc += q[k];
+            }
+            for (; t < n; ++t) acc += part[t][lane];
+        }
+    }
+    return acc;
+}
+
+// grad[i] (and the loss).
+__global__ void __launch_bounds__(256) cv_sum_kernel(const float *partial, int tiles, float *grad, float *loss,
+                                                     float loss_scale) {
+    const float acc = sum_tiles(partial, tiles);
+    const int i = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x >= 64 || i > kNP) return;
     if (i < kNP) {
         if (grad) grad[i] = acc;
     } else if (loss) {
@@ -1344,27 +1402,19 @@ struct AdamArgs {
     float loss_scale;
 };
 
-// Bias corrections of Adam step `step` (>= 1), in FP64 then rounded.
-__device__ __forceinline__ void adam_corrections(int64_t step, float &c1, float &c2) {
-    c1 = (float)(1.0 - pow(0.9, (double)step));
-    c2 = (float)(1.0 - pow(0.999, (double)step));
-}
-
-__global__ void cv_adam_kernel(AdamArgs A) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > kNP) return;
+__global__ void __launch_bounds__(256) cv_adam_kernel(AdamArgs A) {
+    const int i = blockIdx.x * 64 + (threadIdx.x & 63);
+    float g = 0.f;
+    if (A.partial) g = sum_tiles(A.partial, A.tiles);
+    if (threadIdx.x >= 64 || i > kNP) return;
+    if (!A.partial && i < kNP) g = A.grad[i];
     if (A.desc) {
         const TrainDesc &d = *A.desc;
-        adam_corrections(d.step0 + A.iter + 1, A.c1, A.c2);
+        A.c1 = d.c1;
+        A.c2 = d.c2;
         A.lr = d.lr;
         A.loss_out = d.loss_out ? d.loss_out + A.iter : nullptr;
         A.loss_scale = d.loss_scale;
-    }
-    float g = 0.f;
-    if (A.partial) {
-        for (int t = 0; t < A.tiles; ++t) g += A.partial[(int64_t)t * (kNP + 1) + i];
-    } else if (i < kNP) {
-        g = A.grad[i];
     }
     if (i == kNP) {
         if (A.loss_out) *A.loss_out = g * A.loss_scale;
@@ -1419,7 +1469,7 @@ static hipError_t grad_kernel_attribute(int dev) {
 }
 
 static hipError_t launch_grad(const TrainArgs &ta, int tiles, hipStream_t s) {
-    hipLaunchKernelGGL(cv_grad_kernel, dim3(tiles), dim3(256), sizeof(TrainLds), s, ta);
+    hipLaunchKernelGGL(cv_grad_kernel, dim3(tiles), dim3(kGradThreads), sizeof(TrainLds), s, ta);
     return hipGetLastError();
 }
 
@@ -1453,7 +1503,7 @@ static int capture_training(fk_cv *cv, int steps, int64_t batch, TrainGraph &g) 
         A.bf = cv->s.bf;
         A.partial = cv->s.partial;
         A.tiles = tiles;
-        hipLaunchKernelGGL(cv_adam_kernel, dim3((kNP + 256) / 256), dim3(256), 0, cv->capture_stream, A);
+        hipLaunchKernelGGL(cv_adam_kernel, dim3(kSumBlocks), dim3(256), 0, cv->capture_stream, A);
         le = hipGetLastError();
     }
     hipGraph_t graph = nullptr;
@@ -1790,7 +1840,7 @@ int fk_cv_grad(fk_cv_t cv, const float *txy, const float *target, int64_t n, flo
     hipError_t e = launch_grad(ta, tiles, stream);
     if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
     // the tiles' loss entries are sums of squared residuals: report the mean
-    hipLaunchKernelGGL(cv_sum_kernel, dim3((kNP + 256) / 256), dim3(256), 0, stream, cv->s.partial, tiles, grad,
+    hipLaunchKernelGGL(cv_sum_kernel, dim3(kSumBlocks), dim3(256), 0, stream, cv->s.partial, tiles, grad,
                        loss, 1.f / (2.f * (float)n));
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "sum kernel launch");
     return FK_OK;
@@ -1809,7 +1859,7 @@ int fk_cv_adam_apply(fk_cv_t cv, const float *grad, float lr, hipStream_t stream
     A.lr = lr;
     A.c1 = (float)(1.0 - std::pow(0.9, (double)step));
     A.c2 = (float)(1.0 - std::pow(0.999, (double)step));
-    hipLaunchKernelGGL(cv_adam_kernel, dim3((kNP + 256) / 256), dim3(256), 0, stream, A);
+    hipLaunchKernelGGL(cv_adam_kernel, dim3(kSumBlocks), dim3(256), 0, stream, A);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FK_OK : hip_fail(e, "adam kernel launch");
 }
