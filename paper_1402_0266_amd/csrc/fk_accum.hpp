@@ -83,7 +83,7 @@ __device__ __forceinline__ void slots_collect(AccSlot<NV> *slots, NodeAcc *const
     lds_order();
     bool closed = false;
     if (lane < (uint32_t)kAccSlots) closed = slots[lane].tag != kSlotFree && slots[lane].cnt < kCntOne;
-    uint64_t cm = __ballot(closed);
+    uint64_t cm = __builtin_amdgcn_ballot_w64(closed);
     while (cm != 0ull) {
         const int j = __builtin_ctzll(cm);
         cm &= cm - 1ull;
@@ -110,7 +110,7 @@ __device__ __forceinline__ uint32_t slot_open(AccSlot<NV> *slots, NodeAcc *const
                                               uint32_t n, uint32_t lane) {
     // free slots (closed ones wait for slots_collect)
     lds_order();
-    const uint32_t fm = (uint32_t)__ballot(lane < (uint32_t)kAccSlots && slots[lane & (kAccSlots - 1)].tag == kSlotFree);
+    const uint32_t fm = (uint32_t)__builtin_amdgcn_ballot_w64(lane < (uint32_t)kAccSlots && slots[lane & (kAccSlots - 1)].tag == kSlotFree);
     if (fm == 0u) return kNoSlot;
     const uint32_t j = (uint32_t)__builtin_ctz(fm);
     const uint32_t tag = (seq << 3) | j;
@@ -212,10 +212,10 @@ __device__ __forceinline__ bool acc_path(AccSlot<NV> *slots, NodeAcc *const *acc
 template <int NV>
 __device__ __forceinline__ void acc_wave(AccSlot<NV> *slots, NodeAcc *const *acc, bool fin, uint32_t tag,
                                          uint32_t out, const float (&v)[NV], uint32_t steps, uint32_t lane) {
-    if (__ballot(fin) == 0ull) return;
+    if (__builtin_amdgcn_ballot_w64(fin) == 0ull) return;
     bool cl = false;
     if (fin) cl = acc_path<NV>(slots, acc, tag, out, v, steps);
-    if (__ballot(cl) != 0ull) slots_collect<NV>(slots, acc, lane);
+    if (__builtin_amdgcn_ballot_w64(cl) != 0ull) slots_collect<NV>(slots, acc, lane);
 }
 
 // A split sum as FP64: hi 2^24 + lo, both exact in FP64 while |hi| < 2^53,

@@ -226,8 +226,8 @@ int build_tables(const LevelSpec *lv, int n_levels, const double *pts, int64_t n
         const int l = level_of[(size_t)g];
         NodeDev &nd = T.nodes[(size_t)s];
         // Start point as an FP32 (hi, lo) pair holding the FP64 node to ~2^-48.
-        nd.x = (float)pts[2 * g];
-        nd.y = (float)pts[2 * g + 1];
+        nd.x = (float)pts[2 * g] + 0.f;   // + 0: no -0 (the path kernels' exit test)
+        nd.y = (float)pts[2 * g + 1] + 0.f;
         nd.xlo = (float)(pts[2 * g] - (double)nd.x);
         nd.ylo = (float)(pts[2 * g + 1] - (double)nd.y);
         nd.nid = (uint32_t)(g - lv[l].node_offset);

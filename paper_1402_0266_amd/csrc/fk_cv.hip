@@ -579,7 +579,7 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
             until_eval = c.stride_iters;
             // ---- evaluation point: integrand of running paths, end value of
             //      parked ones (every lane of the wavefront joins) ------------
-            if (__ballot(active || parked) != 0ull) {
+            if (ballot(active || parked) != 0ull) {
                 const bool ev = active || parked;
                 const float sk = (parked && L.k >= L.K) ? L.horizon : (float)L.k * L.dt;
                 const float tau = ev ? tend - sk : 0.f;
@@ -616,7 +616,7 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
                 parked = false;
             }
             // ---- refill idle lanes (paths start only at evaluation points) ----
-            uint64_t need = __ballot(!active && !parked);
+            uint64_t need = ballot(!active && !parked);
             while (need != 0ull && !q_done) {
                 if (q_next >= q_end) {
                     if (!grab_chunk<2>(a, total_chunks, next_chunk(a), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane)) {
@@ -641,10 +641,10 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
                     active = true;
                 }
                 q_next += min((uint32_t)__popcll(need), avail);
-                need = __ballot(!active && !parked);
+                need = ballot(!active && !parked);
             }
         }
-        if (__ballot(active || parked) == 0ull && q_done) break;
+        if (ballot(active || parked) == 0ull && q_done) break;
 
         if (active) {
             out = false;
@@ -713,16 +713,20 @@ __global__ void grad_table_kernel(const double *gxi, const double *geta, int n, 
 template <int KIND, bool UNIFORM, bool BRIDGE>
 __device__ __forceinline__ bool cv_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, float &wx, float &wy,
                                         uint32_t key0, uint32_t key1) {
-    float x0h = 0.f, x0l = 0.f, y0h = 0.f, y0l = 0.f;
-    if constexpr (BRIDGE) {
-        x0h = L.xh;
-        x0l = L.xl;
-        y0h = L.yh;
-        y0l = L.yl;
-    }
+    SideDist d0{};
+    if constexpr (BRIDGE) d0 = side_dist(L);
     bool out = em_step_w<KIND, UNIFORM>(L, ra, rb, ox, oy, wx, wy);
     if constexpr (BRIDGE) {
-        if (!out) out = bridge_exit<UNIFORM>(L, x0h, x0l, y0h, y0l, key0, key1);
+        if (!out) {
+            const int32_t k = L.k - 1;
+            int side;
+            const float p = bridge_prob(d0, side_dist(L), 1.f / (!UNIFORM && k == L.K - 1 ? L.dt_last : L.dt), side);
+            if (side >= 0) {
+                const PhiloxOut r = philox4x32_10((uint32_t)k >> 1, L.path, L.nid, L.ctr3 | 4u, key0, key1);
+                out = bridge_uniform((k & 1) ? r.r1 : r.r0) < p;
+                if (out) move_to_side(L, side);
+            }
+        }
     }
     return out;
 }
@@ -785,14 +789,14 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
 
     bool closed = false;                                // the lane's last path closed its chunk's slot
     for (uint32_t until_eval = 0;; --until_eval) {     // iterations to the next block boundary
-        if (__ballot(closed) != 0ull) {
+        if (ballot(closed) != 0ull) {
             slots_collect<2>(slots, accs, lane);
             closed = false;
         }
         if (until_eval == 0) {
             until_eval = c.stride_iters;
             // ---- block boundary of running paths (every lane joins) ---------
-            if (__ballot(active) != 0ull) {
+            if (ballot(active) != 0ull) {
                 const float tau = active ? tend - (float)L.k * L.dt : 0.f;
                 float o[2][2];
                 net_grad_wave<SPLIT>(N, c.tscale2, tau, active ? L.xh : 0.5f, active ? L.yh : 0.5f, o);
@@ -815,7 +819,7 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
                 }
             }
             // ---- refill idle lanes ------------------------------------------
-            uint64_t need = __ballot(!active);
+            uint64_t need = ballot(!active);
             while (need != 0ull && !q_done) {
                 if (q_next >= q_end) {
                     if (!grab_chunk<2>(a, total_chunks, next_chunk(a), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane)) {
@@ -844,10 +848,10 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
                     active = true;
                 }
                 q_next += min((uint32_t)__popcll(need), avail);
-                need = __ballot(!active);
+                need = ballot(!active);
             }
         }
-        if (__ballot(active) == 0ull && q_done) break;
+        if (ballot(active) == 0ull && q_done) break;
 
         if (active) {
             bool out = false;
@@ -949,11 +953,11 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
 
     bool closed = false;         // the lane's last path closed its chunk's slot
     for (;;) {
-        if (__ballot(closed) != 0ull) {
+        if (ballot(closed) != 0ull) {
             slots_collect<2>(slots, accs, lane);
             closed = false;
         }
-        uint64_t need = __ballot(!active);
+        uint64_t need = ballot(!active);
         while (need != 0ull && !q_done) {
             if (q_next >= q_end) {
                 if (!grab_chunk<2>(a, total_chunks, next_chunk(a), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane)) {
@@ -973,9 +977,9 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
                 active = true;
             }
             q_next += min((uint32_t)__popcll(need), avail);
-            need = __ballot(!active);
+            need = ballot(!active);
         }
-        if (__ballot(active) == 0ull) break;
+        if (ballot(active) == 0ull) break;
 
         if (active) {
             bool out = false;

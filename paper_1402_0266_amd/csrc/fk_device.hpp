@@ -48,6 +48,36 @@ __device__ __forceinline__ PhiloxOut philox4x32_10(uint32_t c0, uint32_t c1, uin
     return PhiloxOut{c0, c1, c2, c3};
 }
 
+// A wave-uniform value in a vector register.  On gfx950 a wave64 FP32 add,
+// multiply or FMA, and a 32-bit add, XOR or three-input bit operation, issues
+// every 2 cycles when its operands are vector registers or constants, and
+// every 4 with a scalar register among them (measured: 2.4 and 4.2 at 8 waves
+// per SIMD; 64-bit multiply-add 4.5, min / max / compare / convert 4.3,
+// transcendentals 8.3), so the path loops keep what they read every step in
+// vector registers.
+__device__ __forceinline__ float in_vgpr(float v) {
+    asm("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
+// a ^ b ^ c, all in vector registers.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// The lanes of the wavefront with v, as a scalar (no vector instruction where
+// the condition is a lane mask already).
+__device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+
+constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u;   // Philox multipliers
+constexpr uint32_t kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;   // key increments
+
 // A path's counter words 1 and 2 (path, node) stay fixed over its calls, so
 // round 1's second product (M1 times the node word) and round 2's first
 // product (M0 times round 1's first output, which combines that product with
@@ -59,45 +89,69 @@ struct PhiloxPath {
 };
 
 __device__ __forceinline__ PhiloxPath philox_path(uint32_t c1, uint32_t c2, uint32_t k0) {
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint64_t p1 = (uint64_t)kM1 * c2;
     const uint32_t a = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint64_t q0 = (uint64_t)0xD2511F53u * a;
+    const uint64_t q0 = (uint64_t)kM0 * a;
     return PhiloxPath{(uint32_t)p1, (uint32_t)(q0 >> 32), (uint32_t)q0};
 }
 
-// philox4x32_10(c0, c1, c2, c3, k0, k1) with P = philox_path(c1, c2, k0):
-// bitwise the same four words.
-__device__ __forceinline__ PhiloxOut philox4x32_10_path(uint32_t c0, uint32_t c3, const PhiloxPath &P, uint32_t k0,
-                                                        uint32_t k1) {
-    asm volatile("" : "+s"(k0), "+s"(k1));
-    // round 1: words 0 and 1 of the result are fixed (their product is in P)
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
-    const uint32_t x2 = xor3_uniform((uint32_t)(p0 >> 32), c3, k1);
-    const uint32_t x3 = (uint32_t)p0;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-    // round 2: M0 times the fixed word 0 is P.h0, P.l0
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * x2;
-    c0 = xor3_uniform((uint32_t)(p1 >> 32), P.b, k0);
-    uint32_t c1 = (uint32_t)p1;
-    uint32_t c2 = xor3_uniform(P.h0, x3, k1);
-    c3 = P.l0;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
+// The same products with the round keys (and counter word 3) they meet folded
+// in: what a lane keeps of its path.
+struct PhiloxLane {
+    uint32_t ck;           // counter word 3 ^ key word 1: round 1
+    uint32_t bk, hk, lk;   // b, h0 and l0 with the keys of rounds 2, 2 and 3
+};
+__device__ __forceinline__ PhiloxLane philox_lane(uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
+    const PhiloxPath P = philox_path(c1, c2, k0);
+    return PhiloxLane{c3 ^ k1, P.b ^ (k0 + kW0), P.h0 ^ (k1 + kW1), P.l0 ^ (k1 + 2u * kW1)};
+}
+
+// The round keys that are left, in vector registers.
+struct PhiloxKeys {
+    uint32_t k0r3;          // round 3's first key
+    uint32_t k0[7], k1[7];  // rounds 4 .. 10
+};
+__device__ __forceinline__ PhiloxKeys philox_keys(uint32_t key0, uint32_t key1) {
+    PhiloxKeys K;
+    K.k0r3 = in_vgpr(key0 + 2u * kW0);
 #pragma unroll
-    for (int r = 2; r < 10; ++r) {
-        const uint64_t q0 = (uint64_t)0xD2511F53u * c0;
-        const uint64_t q1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = xor3_uniform((uint32_t)(q1 >> 32), c1, k0);
-        const uint32_t n2 = xor3_uniform((uint32_t)(q0 >> 32), c3, k1);
-        c1 = (uint32_t)q1;
-        c3 = (uint32_t)q0;
-        c0 = n0;
-        c2 = n2;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
+    for (int r = 0; r < 7; ++r) {
+        K.k0[r] = in_vgpr(key0 + (uint32_t)(r + 3) * kW0);
+        K.k1[r] = in_vgpr(key1 + (uint32_t)(r + 3) * kW1);
     }
-    return PhiloxOut{c0, c1, c2, c3};
+    return K;
+}
+
+// philox4x32_10(c0, c1, c2, c3, k0, k1) with P = philox_lane(c1, c2, c3, k0,
+// k1), K = philox_keys(k0, k1): bitwise the same four words.  flip: bits of
+// counter word 3 to invert (another stream of the same path).
+__device__ __forceinline__ PhiloxOut philox4x32_10_lane(uint32_t c0, const PhiloxLane &P, const PhiloxKeys &K,
+                                                        uint32_t flip = 0) {
+    // round 1: words 0 and 1 of the result are fixed (folded into P)
+    const uint64_t p0 = (uint64_t)kM0 * c0;
+    const uint32_t x2 = (uint32_t)(p0 >> 32) ^ P.ck, x3 = (uint32_t)p0;
+    // round 2: its first product is in P
+    const uint64_t p1 = (uint64_t)kM1 * x2;
+    uint32_t v0 = (uint32_t)(p1 >> 32) ^ P.bk, v1 = (uint32_t)p1, v2 = P.hk ^ x3, v3;
+    // round 3
+    {
+        const uint64_t a = (uint64_t)kM0 * v0, b = (uint64_t)kM1 * v2;
+        v0 = xor3((uint32_t)(b >> 32), v1, K.k0r3);
+        v2 = (uint32_t)(a >> 32) ^ P.lk;
+        v1 = (uint32_t)b;
+        v3 = (uint32_t)a;
+    }
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+        const uint64_t a = (uint64_t)kM0 * v0, b = (uint64_t)kM1 * v2;
+        const uint32_t n0 = xor3((uint32_t)(b >> 32), v1, K.k0[r]);
+        const uint32_t n2 = xor3((uint32_t)(a >> 32), v3, K.k1[r]);
+        v1 = (uint32_t)b;
+        v3 = (uint32_t)a;
+        v0 = n0;
+        v2 = n2;
+    }
+    return PhiloxOut{v0, v1, v2, v3};
 }
 
 // Hardware transcendentals.  v_sin/v_cos take their argument in revolutions
@@ -117,13 +171,25 @@ __device__ __forceinline__ float hw_cos_rev(float x) { return __builtin_amdgcn_c
 // bits m under the exponent of 1.0 make the float 1 + m 2^-23 in one
 // instruction: u1 is 2 minus that (exact), and the angle is that float
 // itself, as sin and cos in revolutions have period 1.
-__device__ __forceinline__ void brownian_increment(uint32_t ra, uint32_t rb, float cbm,
-                                                   float &dwx, float &dwy) {
-    const float u1 = 2.f - __uint_as_float((ra & 0x7fffffu) | 0x3f800000u);
-    const float a2 = __uint_as_float((rb & 0x7fffffu) | 0x3f800000u);   // 1 + u2
+constexpr uint32_t kUnitMask = 0x7fffffu;
+
+// (r & m) | 1.0f for m = kUnitMask in a vector register: one bit operation.
+__device__ __forceinline__ float unit_bits(uint32_t r, uint32_t m) {
+    uint32_t v;
+    asm("v_bitop3_b32 %0, %1, %2, 1.0 bitop3:0xea" : "=v"(v) : "v"(r), "v"(m));
+    return __uint_as_float(v);
+}
+
+__device__ __forceinline__ void brownian_increment(uint32_t ra, uint32_t rb, float cbm, uint32_t m, float &dwx,
+                                                   float &dwy) {
+    const float u1 = 2.f - unit_bits(ra, m);
+    const float a2 = unit_bits(rb, m);   // 1 + u2
     const float rad = hw_sqrt(cbm * hw_log2(u1));
     dwx = rad * hw_cos_rev(a2);
     dwy = rad * hw_sin_rev(a2);
+}
+__device__ __forceinline__ void brownian_increment(uint32_t ra, uint32_t rb, float cbm, float &dwx, float &dwy) {
+    brownian_increment(ra, rb, cbm, kUnitMask, dwx, dwy);
 }
 
 // ---------------------------------------------------------------------------

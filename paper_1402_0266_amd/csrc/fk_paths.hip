@@ -10,9 +10,10 @@
 // The node value is the mean of the scores over its paths.
 //
 // MI355X mapping:
-//  * The path loop is ALU-bound (Philox integer multiplies, 6-8 hardware
-//    transcendentals, ~40 FP32 ops per step) and touches no memory, so every
-//    lane keeps its whole path state in registers.
+//  * The path loop is bound by VALU issue (per pair of steps: 18 64-bit
+//    multiplies and 20 bit operations of one Philox call, 10-14 hardware
+//    transcendentals, ~60 FP32 ops) and touches no memory, so every lane keeps
+//    its whole path state in registers.
 //  * Exit times vary by two orders of magnitude between nodes and
 //    geometrically within a node; lanes therefore refill individually: a
 //    wavefront grabs `chunk` consecutive paths of one node from a global
@@ -91,13 +92,13 @@ __device__ __forceinline__ int cost_bucket(const TableArgs &t, double x, double 
 // the same b.  Every lane of the wavefront calls it.
 __device__ __forceinline__ uint32_t wave_bucket_add(uint32_t *hist, bool take, int b) {
     const int lane = (int)(threadIdx.x & 63u);
-    uint64_t left = __ballot(take);
+    uint64_t left = ballot(take);
     uint32_t slot = 0;
     while (left != 0ull) {
         const int leader = __builtin_ctzll(left);
         const int lb = __shfl(b, leader, 64);
         const bool mine = take && b == lb;
-        const uint64_t grp = __ballot(mine);
+        const uint64_t grp = ballot(mine);
         uint32_t base = 0;
         if (lane == leader) base = atomicAdd(&hist[lb], (uint32_t)__popcll(grp));
         base = (uint32_t)__shfl((int)base, leader, 64);
@@ -161,8 +162,8 @@ __global__ void table_scatter_kernel(const TableArgs t) {
     if (!take) return;
     NodeDev nd{};
     // the start point as an FP32 (hi, lo) pair holding the FP64 node to ~2^-48
-    nd.x = (float)x;
-    nd.y = (float)y;
+    nd.x = (float)x + 0.f;   // + 0: no -0 (the path kernels' exit test)
+    nd.y = (float)y + 0.f;
     nd.xlo = (float)(x - (double)nd.x);
     nd.ylo = (float)(y - (double)nd.y);
     nd.nid = (uint32_t)i;
@@ -240,8 +241,25 @@ hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_ste
 // counter past the first grid-full, so a launch of short paths does not open
 // with every wavefront contending for the counter.  Long horizons keep the
 // counter for every grab (the other form costs their hot loop ~3% in code).
+//
+// The inner loop takes step pairs without a branch until some lane's path may
+// have ended: both steps are taken at once, and one unsigned maximum over the
+// four new coordinates and the pair count finds the wavefronts that have to
+// look closer.  Idle lanes hold a point that stays at (0.5, 0.5).  Scores,
+// refill and queue stand outside the inner loop: kept in one loop they cost
+// it ~20 register moves a pair.  Five to six wavefronts per SIMD (78 - 96
+// registers, 15 of them Philox round keys): with the keys in scalar registers
+// eight fit, and run 2% slower; forced to 72 or 64 registers the kernel
+// spills.  Measured (moving bump, 1521 nodes x 4096 paths x <= 10^4 steps):
+// 37.5 ms, 117 VALU instructions and ~410 issue cycles a pair, against
+// 41.1 ms of the form with a branch after each step; with the bridge test
+// (125 nodes x 16384 paths to their exits) 4.8 ms against 6.9, of which the
+// one Philox call for the uniforms of both steps and a position that stays
+// in registers are the larger part.  Handing the last paths of a thinning
+// wavefront to the block's others through LDS brought nothing (the launch
+// then ends on the latency of single chains).
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FIRST_BY_INDEX = false>
-__global__ void __launch_bounds__(256) fk_path_kernel(const PathArgs a) {
+__global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
     constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
     const uint32_t lane = threadIdx.x & 63u;
     __shared__ AccSlot<2> slot_tab[4][kAccSlots];
@@ -260,22 +278,36 @@ __global__ void __launch_bounds__(256) fk_path_kernel(const PathArgs a) {
         }
     }
     const uint32_t key0 = a.key0, key1 = a.key1;
+    const PhiloxKeys keys = philox_keys(key0, key1);
+    const uint32_t mask = in_vgpr(kUnitMask);
 
     Lane L;
-    PhiloxPath pp{};          // the lane's path's fixed Philox products
-    bool active = false;
+    PhiloxLane pp{};          // the lane's path's fixed Philox products
+    uint32_t bridge_ck = 0;   // pp.ck of the bridge test's stream
+    SideDist dist{};          // the bridge test's distances at the lane's position
+    float iD = 0.f, iD_last = 0.f, drev2 = 0.f;
+    int32_t half = 0, half_end = 0;   // step pairs taken; the pair that reaches step K
     uint32_t my_tag = 0;      // accumulation tag of the lane's path's chunk
     uint32_t my_steps = 0;
-
-    bool closed = false;      // the lane's last path closed its chunk's slot
-    for (;;) {
-        // ---- flush closed chunks, refill idle lanes ---------------------
-        if (__ballot(closed) != 0ull) {
-            slots_collect<2>(slots, accs, lane);
-            closed = false;
+    uint64_t act = 0;         // the lanes with a path
+    auto idle = [&]() {       // a lane without a path: a point that stays where it is
+        L.xh = L.yh = 0.5f;
+        L.xl = L.yl = 0.f;
+        L.dt = L.cbm = 0.f;
+        L.K = 0x7fffffff;
+        half_end = 0x3f000000;
+        half = 0;
+        if constexpr (BRIDGE) {
+            dist = side_dist(L);
+            iD = 1e30f;
         }
-        uint64_t need = __ballot(!active);
-        while (need != 0ull && !q_done) {
+    };
+    lane_level<KIND, TMODE>(L, a.levels[0]);
+    idle();
+
+    for (;;) {
+        // ---- refill idle lanes -------------------------------------------
+        while (~act != 0ull && !q_done) {
             if (q_next >= q_end) {
                 if constexpr (FIRST_BY_INDEX) {
                     // a grid no larger than the chunk count hands out no more
@@ -300,72 +332,132 @@ __global__ void __launch_bounds__(256) fk_path_kernel(const PathArgs a) {
                 q_tag = slot_open<2>(slots, accs, grabs++, (uint32_t)a.nodes[q_slot].out, q_end - q_next, lane);
                 continue;
             }
+            const uint64_t need = ~act;
             const uint32_t avail = q_end - q_next;
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
-            if (!active && rank < avail) {
+            const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
+            if (take) {
                 lane_start<KIND, TMODE>(L, a.nodes[q_slot], a.levels, q_next + rank);
-                pp = philox_path(L.path, L.nid, key0);
+                pp = philox_lane(L.path, L.nid, L.ctr3, key0, key1);
+                half = 0;
+                half_end = min((L.K - 1) >> 1, 0x3f000000);   // past it every pair is looked at
+                drev2 = 2.f * L.drev;
+                if (L.K <= 0) {      // scored where it starts: keeps its low parts in values it has no use for
+                    L.horizon = L.xl;
+                    L.dt_last = L.yl;
+                }
+                if constexpr (BRIDGE) {
+                    bridge_ck = (L.ctr3 | 4u) ^ key1;
+                    dist = side_dist(L);
+                    iD = 1.f / L.dt;
+                    iD_last = 1.f / L.dt_last;
+                }
                 my_tag = q_tag;
-                active = true;
             }
-            const uint32_t n_need = (uint32_t)__popcll(need);
-            q_next += min(n_need, avail);
-            need = __ballot(!active);
+            act |= ballot(take);
+            q_next += min((uint32_t)__popcll(need), avail);
         }
-        if (__ballot(active) == 0ull) break;
+        if (act == 0ull) break;
 
-        // ---- two Euler-Maruyama steps from one Philox call ----------------
-        if (active) {
-            bool out = false;
-            if (L.k < L.K) {
-                const PhiloxOut r = philox4x32_10_path((uint32_t)L.k >> 1, L.ctr3, pp, key0, key1);
-                float ox = L.ox, oy = L.oy, cr = 0.f, sr = 0.f;
-                if constexpr (kMovingBackward) {
-                    // Orbit angle at PDE time t_init + t - k dt, in revolutions.
-                    const float rev = fmaf(-(float)L.k, L.drev, L.rev0);
-                    cr = hw_cos_rev(rev);
-                    sr = hw_sin_rev(rev);
-                    ox = L.dens.orbit_r * cr;
-                    oy = L.dens.orbit_r * sr;
-                }
-                float x0h = 0.f, x0l = 0.f, y0h = 0.f, y0l = 0.f;
-                if constexpr (BRIDGE) {
-                    x0h = L.xh; x0l = L.xl; y0h = L.yh; y0l = L.yl;
-                }
-                out = em_step<KIND, UNIFORM>(L, r.r0, r.r1, ox, oy);
-                if constexpr (BRIDGE) {
-                    if (!out) out = bridge_exit<UNIFORM>(L, x0h, x0l, y0h, y0l, key0, key1);
-                }
-                if (!out && L.k < L.K) {
-                    if constexpr (kMovingBackward) {
-                        // One step later the angle is smaller by omega dt:
-                        // rotate (cos, sin) instead of re-evaluating them.
-                        const float c2 = fmaf(cr, L.cos_d, sr * L.sin_d);
-                        const float s2 = fmaf(sr, L.cos_d, -cr * L.sin_d);
-                        ox = L.dens.orbit_r * c2;
-                        oy = L.dens.orbit_r * s2;
-                    }
-                    if constexpr (BRIDGE) {
-                        x0h = L.xh; x0l = L.xl; y0h = L.yh; y0l = L.yl;
-                    }
-                    out = em_step<KIND, UNIFORM>(L, r.r2, r.r3, ox, oy);
-                    if constexpr (BRIDGE) {
-                        if (!out) out = bridge_exit<UNIFORM>(L, x0h, x0l, y0h, y0l, key0, key1);
-                    }
-                }
+        // ---- step pairs, until a path ends ---------------------------------
+        float x1h, x1l, y1h, y1l;            // the position after the pair's first step
+        int32_t side1 = -1, side2 = -1;
+        uint64_t fin;
+        for (;;) {
+            const PhiloxOut r = philox4x32_10_lane((uint32_t)half, pp, keys);
+            float ox = L.ox, oy = L.oy, ox2 = ox, oy2 = oy;
+            if constexpr (kMovingBackward) {
+                // Orbit angle at PDE time t_init + t - k dt (k = 2 half), in
+                // revolutions; one step later it is smaller by omega dt: rotate
+                // (cos, sin) instead of re-evaluating them.
+                const float rev = fmaf(-(float)half, drev2, L.rev0);
+                const float cr = hw_cos_rev(rev), sr = hw_sin_rev(rev);
+                ox = L.dens.orbit_r * cr;
+                oy = L.dens.orbit_r * sr;
+                ox2 = L.dens.orbit_r * fmaf(cr, L.cos_d, sr * L.sin_d);
+                oy2 = L.dens.orbit_r * fmaf(sr, L.cos_d, -cr * L.sin_d);
             }
-            if (out || L.k >= L.K) {
-                // ---- score (eq. (7b)) and its node's sums ------------------
-                float v[2];
-                score_path(a, L, out, v[0], v[1]);
-                closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
-                my_steps += (uint32_t)L.k;      // the path's steps, counted once at its end
-                if (a.scores) a.scores[path_rec(L, a.n_paths)] = make_float2(v[0], v[1]);
-                if (a.exit_step) a.exit_step[path_rec(L, a.n_paths)] = out ? L.k : -1;
-                active = false;
+            float D1 = L.dt, D2 = L.dt, cb1 = L.cbm, cb2 = L.cbm, iD1 = iD, iD2 = iD;
+            if constexpr (!UNIFORM) {
+                // the last step K - 1 is the pair's first (K odd) or second one
+                const bool l1 = 2 * half == L.K - 1, l2 = 2 * half == L.K - 2;
+                D1 = l1 ? L.dt_last : D1;
+                cb1 = l1 ? L.cbm_last : cb1;
+                iD1 = l1 ? iD_last : iD1;
+                D2 = l2 ? L.dt_last : D2;
+                cb2 = l2 ? L.cbm_last : cb2;
+                iD2 = l2 ? iD_last : iD2;
             }
+            float dwx, dwy;
+            x1h = L.xh;
+            x1l = L.xl;
+            y1h = L.yh;
+            y1l = L.yl;
+            em_move<KIND>(x1h, x1l, y1h, y1l, L.dens, r.r0, r.r1, ox, oy, D1, cb1, mask, dwx, dwy);
+            L.xh = x1h;
+            L.xl = x1l;
+            L.yh = y1h;
+            L.yl = y1l;
+            em_move<KIND>(L.xh, L.xl, L.yh, L.yl, L.dens, r.r2, r.r3, ox2, oy2, D2, cb2, mask, dwx, dwy);
+            half += 1;
+            // The path may have ended in this pair: as unsigned numbers, the bit
+            // patterns of the floats in [0, 1) lie below that of 1, all others
+            // (1 itself among them, hence "may") from there on, and half_end -
+            // half once it is negative.
+            uint32_t u1 = max(max(__float_as_uint(x1h), __float_as_uint(y1h)), __float_as_uint(L.xh));
+            u1 = max(max(u1, __float_as_uint(L.yh)), (uint32_t)(half_end - half));
+            bool ends = u1 >= 0x3f800000u;
+            if constexpr (BRIDGE) {
+                // The bridge tests of both steps; their uniforms are words 0 and 1
+                // of Philox(k/2, path, node, ctr3 | 4).
+                const PhiloxOut u =
+                    philox4x32_10_lane((uint32_t)half - 1u, PhiloxLane{bridge_ck, pp.bk, pp.hk, pp.lk}, keys);
+                const SideDist d1 = side_dist(x1h, x1l, y1h, y1l), d2 = side_dist(L);
+                const float p1 = bridge_prob(dist, d1, iD1, side1), p2 = bridge_prob(d1, d2, iD2, side2);
+                side1 = bridge_uniform(u.r0) < p1 ? side1 : -1;
+                side2 = bridge_uniform(u.r1) < p2 ? side2 : -1;
+                ends |= (side1 & side2) >= 0;
+                dist = d2;
+            }
+            fin = ballot(ends) & act;
+            if (fin != 0ull) break;
         }
+
+        // ---- score (eq. (7b)) and the node's sums ------------------------------
+        const int32_t k0 = 2 * half - 2;
+        const int32_t s1 = outside<KIND>(x1h, x1l, y1h, y1l), s2 = outside<KIND>(L.xh, L.xl, L.yh, L.yl);
+        const bool first = s1 < 0 || side1 >= 0 || k0 + 1 >= L.K;   // ends with the pair's first step
+        fin &= ballot(first || s2 < 0 || side2 >= 0 || k0 + 2 >= L.K);
+        bool closed = false;      // the lane's path closed its chunk's slot
+        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+            const bool cross = first ? s1 < 0 : s2 < 0;
+            const int side = first ? side1 : side2;
+            const bool out = L.K > 0 && (cross || side >= 0);
+            if (first) {
+                L.xh = x1h;
+                L.xl = x1l;
+                L.yh = y1h;
+                L.yl = y1l;
+            }
+            if (L.K <= 0) {
+                L.xh = L.px;
+                L.xl = L.horizon;
+                L.yh = L.py;
+                L.yl = L.dt_last;
+            }
+            if constexpr (BRIDGE) move_to_side(L, cross || !out ? -1 : side);
+            L.k = out ? k0 + (first ? 1 : 2) : L.K;
+            float v[2];
+            score_path(a, L, out, v[0], v[1]);
+            closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
+            my_steps += (uint32_t)L.k;      // the path's steps, counted once at its end
+            if (a.scores) a.scores[path_rec(L, a.n_paths)] = make_float2(v[0], v[1]);
+            if (a.exit_step) a.exit_step[path_rec(L, a.n_paths)] = out ? L.k : -1;
+            idle();
+        }
+        act &= ~fin;
+        if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);
     }
 
     // ---- the last closed chunks' sums ----------------------------------------
@@ -403,11 +495,11 @@ __global__ void __launch_bounds__(256) fk_expo_path_kernel(const PathArgs a) {
     uint32_t my_tag = 0, my_steps = 0;
     bool closed = false;
     for (;;) {
-        if (__ballot(closed) != 0ull) {
+        if (ballot(closed) != 0ull) {
             slots_collect<2>(slots, accs, lane);
             closed = false;
         }
-        uint64_t need = __ballot(!active);
+        uint64_t need = ballot(!active);
         while (need != 0ull && !q_done) {
             if (q_next >= q_end) {
                 uint32_t c = 0;
@@ -431,9 +523,9 @@ __global__ void __launch_bounds__(256) fk_expo_path_kernel(const PathArgs a) {
                 active = true;
             }
             q_next += min((uint32_t)__popcll(need), avail);
-            need = __ballot(!active);
+            need = ballot(!active);
         }
-        if (__ballot(active) == 0ull) break;
+        if (ballot(active) == 0ull) break;
 
         if (active) {
             bool out = false;
@@ -456,7 +548,7 @@ __global__ void __launch_bounds__(256) fk_expo_path_kernel(const PathArgs a) {
                 brownian_increment(odd ? r.r2 : r.r0, odd ? r.r3 : r.r1, -2.77258872f * D, dwx, dwy);
                 float bx, by;
                 drift<KIND>(L.dens, ox, oy, L.xh, L.yh, bx, by);
-                const float x0h = L.xh, x0l = L.xl, y0h = L.yh, y0l = L.yl;
+                const SideDist d0 = side_dist(L);
                 comp_add(L.xh, L.xl, fmaf(bx, D, dwx));
                 comp_add(L.yh, L.yl, fmaf(by, D, dwy));
                 if (last) {
@@ -472,14 +564,9 @@ __global__ void __launch_bounds__(256) fk_expo_path_kernel(const PathArgs a) {
                 out = (lo < 0.f) | (hi > 0.f);
                 if (!out) {
                     int side;
-                    const float p = bridge_prob(L, x0h, x0l, y0h, y0l, 1.f / D, side);
-                    if (side >= 0) {
-                        const float ub = fmaf((float)((odd ? q.r1 : q.r0) >> 8), 0x1p-24f, 0x1p-24f);
-                        if (ub < p) {
-                            move_to_side(L, side);
-                            out = true;
-                        }
-                    }
+                    const float p = bridge_prob(d0, side_dist(L), 1.f / D, side);
+                    out = side >= 0 && bridge_uniform(odd ? q.r1 : q.r0) < p;
+                    if (out) move_to_side(L, side);
                 }
                 if (last) L.K = L.k;
             }

@@ -41,55 +41,89 @@ __device__ __forceinline__ void comp_add(float &hi, float &lo, float inc) {
     hi = s;
 }
 
-// One Euler-Maruyama step with centre offset (ox, oy); returns true if the
-// new point is outside the closed unit square, and the step's Brownian part
-// sqrt(2 D) z in (dwx, dwy).  UNIFORM: every step has length dt (t/dt
-// integral), so the last-step selection is compiled out.
+// Negative if the point is outside the closed unit square: x, y, 1 - x or
+// 1 - y negative.  hi is the rounded position; (1 - hi) is exact near 1, so
+// the tests against 1 see the lo part too.  No value is -0 (a sum that cancels
+// is +0, and the start points hold no -0), so the sign bits decide: two bit
+// operations and a compare instead of a minimum, a three-way maximum and a
+// compare.  A grid density's drift may be NaN, which is never outside.
+template <int KIND>
+__device__ __forceinline__ int32_t outside(float xh, float xl, float yh, float yl) {
+    const float x1 = (1.f - xh) - xl, y1 = (1.f - yh) - yl;
+    if constexpr (KIND == KIND_GRID) return fminf(fminf(xh, yh), fminf(x1, y1)) < 0.f ? -1 : 0;
+    uint32_t s;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xfe" : "=v"(s) : "v"(xh), "v"(yh), "v"(x1));
+    return (int32_t)(s | __float_as_uint(y1));
+}
+
+// One Euler-Maruyama step of length D (cb = -4 ln2 D) of the position with
+// centre offset (ox, oy); the step's Brownian part sqrt(2 D) z in (dwx, dwy).
+// m: kUnitMask, in a vector register.
+template <int KIND>
+__device__ __forceinline__ void em_move(float &xh, float &xl, float &yh, float &yl, const DensityRegs &dens,
+                                        uint32_t ra, uint32_t rb, float ox, float oy, float D, float cb, uint32_t m,
+                                        float &dwx, float &dwy) {
+    brownian_increment(ra, rb, cb, m, dwx, dwy);
+    float bx, by;
+    drift<KIND>(dens, ox, oy, xh, yh, bx, by);
+    comp_add(xh, xl, fmaf(bx, D, dwx));
+    comp_add(yh, yl, fmaf(by, D, dwy));
+}
+
+// em_move, and its outcome (outside).
+template <int KIND>
+__device__ __forceinline__ int32_t em_update(float &xh, float &xl, float &yh, float &yl, const DensityRegs &dens,
+                                             uint32_t ra, uint32_t rb, float ox, float oy, float D, float cb,
+                                             uint32_t m, float &dwx, float &dwy) {
+    em_move<KIND>(xh, xl, yh, yl, dens, ra, rb, ox, oy, D, cb, m, dwx, dwy);
+    return outside<KIND>(xh, xl, yh, yl);
+}
+
+// The lane's step L.k (see em_update).  UNIFORM: every step has length dt
+// (t/dt integral), so the last-step selection is compiled out.
 template <int KIND, bool UNIFORM>
 __device__ __forceinline__ bool em_step_w(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, float &dwx,
-                                          float &dwy) {
+                                          float &dwy, uint32_t m = kUnitMask) {
     float D = L.dt, cb = L.cbm;
     if constexpr (!UNIFORM) {
         const bool last = (L.k == L.K - 1);
         D = last ? L.dt_last : D;
         cb = last ? L.cbm_last : cb;
     }
-    brownian_increment(ra, rb, cb, dwx, dwy);
-    float bx, by;
-    drift<KIND>(L.dens, ox, oy, L.xh, L.yh, bx, by);
-    comp_add(L.xh, L.xl, fmaf(bx, D, dwx));
-    comp_add(L.yh, L.yl, fmaf(by, D, dwy));
     L.k += 1;
-    // Outside the closed square: -x > 0, -y > 0, x - 1 > 0 or y - 1 > 0, as
-    // one maximum and one compare.  hi is the rounded position; (hi - 1) is
-    // exact near 1, so the tests against 1 see the lo part too.
-    const float m = fmaxf(fmaxf(-L.xh, -L.yh), fmaxf((L.xh - 1.f) + L.xl, (L.yh - 1.f) + L.yl));
-    return m > 0.f;
+    return em_update<KIND>(L.xh, L.xl, L.yh, L.yl, L.dens, ra, rb, ox, oy, D, cb, m, dwx, dwy) < 0;
 }
 
 template <int KIND, bool UNIFORM>
-__device__ __forceinline__ bool em_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy) {
+__device__ __forceinline__ bool em_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, uint32_t m = kUnitMask) {
     float dwx, dwy;
-    return em_step_w<KIND, UNIFORM>(L, ra, rb, ox, oy, dwx, dwy);
+    return em_step_w<KIND, UNIFORM>(L, ra, rb, ox, oy, dwx, dwy, m);
 }
 
-// Brownian-bridge exit test of the step just taken (from (x0h + x0l,
-// y0h + y0l) to the lane's position, both inside), for a step of length D
-// (iD = 1/D).  The diffusion sqrt(2) W pinned at both ends crosses a side at
-// distances d0, d1 with probability exp(-d0 d1 / D); the four sides combine
-// as independent events.  A side whose exponent d0 d1 / D exceeds 17 counts
-// as 0 (below the uniforms' resolution 2^-24; a zero-length step on a side,
-// 0/0, too).  Returns the crossing probability and the side most likely
-// crossed (-1: none within reach, and the caller needs no uniform).
-__device__ __forceinline__ float bridge_prob(const Lane &L, float x0h, float x0l, float y0h, float y0l, float iD,
-                                             int &side) {
-    const float d0[4] = {x0h + x0l, (1.f - x0h) - x0l, y0h + y0l, (1.f - y0h) - y0l};
-    const float d1[4] = {L.xh + L.xl, (1.f - L.xh) - L.xl, L.yh + L.yl, (1.f - L.yh) - L.yl};
+// Distances of the lane's position to the sides 0 (x = 0), 1 (x = 1),
+// 2 (y = 0) and 3 (y = 1).
+struct SideDist {
+    float d[4];
+};
+__device__ __forceinline__ SideDist side_dist(float xh, float xl, float yh, float yl) {
+    return SideDist{{xh + xl, (1.f - xh) - xl, yh + yl, (1.f - yh) - yl}};
+}
+__device__ __forceinline__ SideDist side_dist(const Lane &L) { return side_dist(L.xh, L.xl, L.yh, L.yl); }
+
+// Brownian-bridge exit test of a step of length D (iD = 1/D) between two
+// points inside, at the distances a and b from the sides.  The diffusion
+// sqrt(2) W pinned at both ends crosses a side at distances d0, d1 with
+// probability exp(-d0 d1 / D); the four sides combine as independent events.
+// A side whose exponent d0 d1 / D exceeds 17 counts as 0 (below the
+// uniforms' resolution 2^-24; a zero-length step on a side, 0/0, too).
+// Returns the crossing probability and the side most likely crossed (-1:
+// none within reach, and the caller needs no uniform).
+__device__ __forceinline__ float bridge_prob(const SideDist &a, const SideDist &b, float iD, int &side) {
     float p = 0.f, pmax = 0.f;
     side = -1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float e = d0[i] * d1[i] * iD;
+        const float e = a.d[i] * b.d[i] * iD;
         if (e <= 17.f) {
             const float ps = hw_exp2(-1.44269504f * e);
             p = (p + ps) - p * ps;  // 1 - (1 - p)(1 - ps)
@@ -102,33 +136,19 @@ __device__ __forceinline__ float bridge_prob(const Lane &L, float x0h, float x0l
     return p;
 }
 
-// The lane's end point projected onto side 0 (x = 0), 1 (x = 1), 2 (y = 0) or 3 (y = 1).
-__device__ __forceinline__ void move_to_side(Lane &L, int side) {
-    if (side == 0) { L.xh = 0.f; L.xl = 0.f; }
-    else if (side == 1) { L.xh = 1.f; L.xl = 0.f; }
-    else if (side == 2) { L.yh = 0.f; L.yl = 0.f; }
-    else { L.yh = 1.f; L.yl = 0.f; }
-}
+// The bridge test's uniform ((r >> 8) + 1) 2^-24: on u < p the path has left
+// within the step and is moved onto the side it most likely crossed.
+__device__ __forceinline__ float bridge_uniform(uint32_t r) { return fmaf((float)(r >> 8), 0x1p-24f, 0x1p-24f); }
 
-// The bridge test of fixed step k (FK_SCORE_BRIDGE).  The uniform of step k
-// is word (k & 1) of Philox(k/2, path, node, ctr3 | 4), u = ((r >> 8) + 1)
-// 2^-24; on u < p the path has left within the step and is moved onto the
-// side it most likely crossed (its end point projected).
-template <bool UNIFORM>
-__device__ __forceinline__ bool bridge_exit(Lane &L, float x0h, float x0l, float y0h, float y0l, uint32_t key0,
-                                            uint32_t key1) {
-    const int32_t k = L.k - 1;
-    float D = L.dt;
-    if constexpr (!UNIFORM) D = (k == L.K - 1) ? L.dt_last : D;
-    int side;
-    const float p = bridge_prob(L, x0h, x0l, y0h, y0l, 1.f / D, side);
-    if (side < 0) return false;
-    const PhiloxOut r = philox4x32_10((uint32_t)k >> 1, L.path, L.nid, L.ctr3 | 4u, key0, key1);
-    const uint32_t word = (k & 1) ? r.r1 : r.r0;
-    const float u = fmaf((float)(word >> 8), 0x1p-24f, 0x1p-24f);
-    if (!(u < p)) return false;
-    move_to_side(L, side);
-    return true;
+// The lane's end point projected onto a side (-1: left as it is), by selects,
+// so that the position stays in registers.
+__device__ __forceinline__ void move_to_side(Lane &L, int side) {
+    const bool mx = side == 0 || side == 1, my = side >= 2;
+    const float to = (side & 1) ? 1.f : 0.f;
+    L.xh = mx ? to : L.xh;
+    L.xl = mx ? 0.f : L.xl;
+    L.yh = my ? to : L.yh;
+    L.yl = my ? 0.f : L.yl;
 }
 
 // Bilinear interpolation in a nodal grid; off the grid, the nearest cell's
@@ -278,7 +298,7 @@ __device__ __forceinline__ void lane_level(Lane &L, const LevelDev &lv) {
 template <int KIND, int TMODE>
 __device__ __forceinline__ void lane_start(Lane &L, const NodeDev &nd, const LevelDev *levels, uint32_t path) {
     L.path = path;
-    L.xh = nd.x;
+    L.xh = nd.x;   // not -0 (em_update's exit test)
     L.yh = nd.y;
     L.xl = nd.xlo;
     L.yl = nd.ylo;
@@ -307,6 +327,10 @@ __device__ __forceinline__ void score_path(const PathArgs &a, const Lane &L, boo
         if (x < 0.f || x > 1.f) { x = fminf(fmaxf(x, 0.f), 1.f); lx = 0.f; }
         if (y < 0.f || y > 1.f) { y = fminf(fmaxf(y, 0.f), 1.f); ly = 0.f; }
     }
+    // zero data (FK_DATA_ZERO); formed here, ahead of the branches: as a last
+    // branch's constants they were lost in some variants' code
+    asm("v_mov_b32 %0, 0" : "=v"(sx));
+    asm("v_mov_b32 %0, 0" : "=v"(sy));
     if (kind == FK_DATA_IDENTITY) {
         const float bx0 = a.shift ? L.px : 0.f, by0 = a.shift ? L.py : 0.f;
         sx = (x - bx0) + lx;
@@ -327,9 +351,6 @@ __device__ __forceinline__ void score_path(const PathArgs &a, const Lane &L, boo
         // loop's (this runs once per path)
         __builtin_amdgcn_sched_barrier(0);
         sy = grid_bilinear(a.grid_eta, a.grid_n, x, y);
-    } else {
-        sx = 0.f;
-        sy = 0.f;
     }
 }
 

@@ -16,12 +16,8 @@
 //  * wavefronts take chunks in a fixed stride (all chunks cost about the
 //    same), so there is no queue and no counter to clear.
 //
-// The kernel is bound by VALU issue.  On gfx950 a wave64 FP32 add, multiply
-// or FMA, and a 32-bit add, XOR or three-input bit operation, issues every 2
-// cycles when all its operands are vector registers or constants, and every
-// 4 with a scalar register among them (measured: 2.4 and 4.2 at 8 waves per
-// SIMD; 64-bit multiply-add 4.5, transcendentals 8.3).  So the loop's
-// constants and the round keys are kept in vector registers (in_vgpr).
+// The kernel is bound by VALU issue, so the loop's constants and the round
+// keys are kept in vector registers (in_vgpr, fk_device.hpp).
 //
 // Measured (two bumps frozen, 10689 nodes x 16384 paths x 20 steps): 6.1 ms
 // against the refilling kernel's 9.7 ms, 70 VALU instructions per step of a
@@ -40,16 +36,6 @@
 
 namespace fk {
 
-// A wave-uniform value in a vector register.
-__device__ __forceinline__ float in_vgpr(float v) {
-    asm("" : "+v"(v));
-    return v;
-}
-__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
-    asm("" : "+v"(v));
-    return v;
-}
-
 // The same value, formed where it stands: keeps the branch around it (two
 // selects per step otherwise).
 __device__ __forceinline__ float last_step(float v) {
@@ -63,16 +49,6 @@ __device__ __forceinline__ int32_t step_number(int32_t k) {
     asm volatile("v_mov_b32 %0, %1" : "=v"(v) : "s"(k));
     return v;
 }
-
-// a ^ b ^ c, all in vector registers.
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
-    uint32_t r;
-    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u;   // Philox multipliers
-constexpr uint32_t kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;   // key increments
 
 // Philox4x32-10 with every counter word but the path (word 1) wave-uniform.
 // After three rounds the uniform words have met the path's word everywhere;
@@ -133,42 +109,6 @@ __device__ __forceinline__ PhiloxOut philox4x32_10_wave(uint32_t c0, uint32_t c3
     return PhiloxOut{v0, v1, v2, v3};
 }
 
-// (r & m) | 1.0f: the float 1 + (r mod 2^23) 2^-23 for m = 2^23 - 1 in a
-// vector register.
-__device__ __forceinline__ float unit_bits(uint32_t r, uint32_t m) {
-    uint32_t v;
-    asm("v_bitop3_b32 %0, %1, %2, 1.0 bitop3:0xea" : "=v"(v) : "v"(r), "v"(m));
-    return __uint_as_float(v);
-}
-
-// One Euler-Maruyama step of length D (cb = -4 ln2 D) with centre offset
-// (ox, oy): em_step_w's arithmetic (fk_pathstep.hpp), bitwise, with the
-// bit operations and the exit test in the cheap forms; returns true if the
-// new point is outside the closed unit square.
-template <int KIND>
-__device__ __forceinline__ bool em_update(float &xh, float &xl, float &yh, float &yl, const DensityRegs &dens,
-                                          uint32_t ra, uint32_t rb, float ox, float oy, float D, float cb,
-                                          uint32_t fmask, float &dwx, float &dwy) {
-    // brownian_increment
-    const float u1 = 2.f - unit_bits(ra, fmask);
-    const float a2 = unit_bits(rb, fmask);
-    const float rad = hw_sqrt(cb * hw_log2(u1));
-    dwx = rad * hw_cos_rev(a2);
-    dwy = rad * hw_sin_rev(a2);
-    float bx, by;
-    drift<KIND>(dens, ox, oy, xh, yh, bx, by);
-    comp_add(xh, xl, fmaf(bx, D, dwx));
-    comp_add(yh, yl, fmaf(by, D, dwy));
-    const float x1 = (1.f - xh) - xl, y1 = (1.f - yh) - yl;
-    // Outside: x, y, 1 - x or 1 - y negative.  No value is -0 (a sum that
-    // cancels is +0, and the start points hold no -0), so the sign bits
-    // decide; a grid density's drift may be NaN, which is never outside.
-    if constexpr (KIND == KIND_GRID) return fminf(fminf(xh, yh), fminf(x1, y1)) < 0.f;
-    uint32_t m;
-    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xfe" : "=v"(m) : "v"(xh), "v"(yh), "v"(x1));
-    return (int32_t)(m | __float_as_uint(y1)) < 0;
-}
-
 template <int CTRL>
 __device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, CTRL, 0xf, 0xf, false);
@@ -212,7 +152,7 @@ __global__ void __launch_bounds__(256, MESH ? 5 : 6) fk_short_path_kernel(const 
     const uint32_t ctr3 = lv.ctr3;
     const float dt = in_vgpr(L.dt), cbm = in_vgpr(L.cbm);
     const float dt_last = in_vgpr(L.dt_last), cbm_last = in_vgpr(L.cbm_last);
-    const uint32_t fmask = in_vgpr(0x7fffffu);
+    const uint32_t fmask = in_vgpr(kUnitMask);
     const float rev0 = in_vgpr(L.rev0), drev = in_vgpr(L.drev), cos_d = in_vgpr(L.cos_d), sin_d = in_vgpr(L.sin_d);
     L.dens.amp = in_vgpr(L.dens.amp);
     L.dens.nscale = in_vgpr(L.dens.nscale);
@@ -252,7 +192,7 @@ __global__ void __launch_bounds__(256, MESH ? 5 : 6) fk_short_path_kernel(const 
             int32_t k_end = K;       // steps the lane's path takes
             // The loop is the wavefront's (k is a scalar): it ends at K, or
             // with the last path that is still inside.
-            for (int32_t k = 0; k < K && __builtin_amdgcn_ballot_w64(alive) != 0ull; k += 2) {
+            for (int32_t k = 0; k < K && ballot(alive) != 0ull; k += 2) {
                 const PhiloxOut r = philox4x32_10_wave((uint32_t)k >> 1, ctr3, nlo, pp, W, key0, key1);
                 if constexpr (MESH) {
                     if (blk_left == 0) {
@@ -292,7 +232,7 @@ __global__ void __launch_bounds__(256, MESH ? 5 : 6) fk_short_path_kernel(const 
                 }
                 float wx, wy;
                 if (alive) {
-                    const bool out = em_update<KIND>(xh, xl, yh, yl, L.dens, r.r0, r.r1, ox, oy, D, cb, fmask, wx, wy);
+                    const bool out = em_update<KIND>(xh, xl, yh, yl, L.dens, r.r0, r.r1, ox, oy, D, cb, fmask, wx, wy) < 0;
                     if constexpr (MESH) {
                         dbx += wx;
                         dby += wy;
@@ -314,7 +254,7 @@ __global__ void __launch_bounds__(256, MESH ? 5 : 6) fk_short_path_kernel(const 
                     cb = last_step(cbm_last);
                 }
                 if (alive) {
-                    const bool out = em_update<KIND>(xh, xl, yh, yl, L.dens, r.r2, r.r3, ox, oy, D, cb, fmask, wx, wy);
+                    const bool out = em_update<KIND>(xh, xl, yh, yl, L.dens, r.r2, r.r3, ox, oy, D, cb, fmask, wx, wy) < 0;
                     if constexpr (MESH) {
                         dbx += wx;
                         dby += wy;

@@ -60,6 +60,23 @@ def test_equals_the_refilling_kernel(name, K, t, last):
         b.close()
 
 
+@pytest.mark.parametrize("K,last,t", [(0, 1.0, 0.0), (1, 1.0, 0.3), (3, 0.4, 0.2), (33, 1.0, 0.04), (33, 0.6, 0.04)])
+def test_pairs_cut_by_the_horizon(K, last, t):
+    """Odd step counts, no steps at all, and steps long enough to jump far past the square, in the refilling kernel
+    (which takes steps in pairs) against the lockstep one."""
+    import paper_1402_0266_amd as fk
+    pts = np.concatenate([_nodes(), [(1.0, 0.3), (0.3, 1.0), (0.7, -0.0)]])
+    dt = t / (K - 1 + last) if K else 0.01
+    for name in ("const", "moving", "two"):
+        for data in (W.Data(t_init=0.1), W.Data(init_kind=W.DATA_SIN, bdry_kind=W.DATA_ZERO)):
+            b = fk.FkBatch([(DENSITIES[name], t, data.t_init, pts, 5)], data, dt, 129, seed=7)
+            ref = b.run(exit_step=True, scores=True)
+            out = fk.fk_interface_solve(DENSITIES[name], data, pts, t, dt, 129, seed=7, level_id=5, exit_step=True,
+                                        scores=True)
+            _same(out, ref, ("xi", "eta", "se_xi", "se_eta", "exit_step", "scores", "total_steps"))
+            b.close()
+
+
 def test_mask_and_nodes_outside():
     """Masked nodes get the full solve's results, others keep their values; a node outside the square gets NaN."""
     import torch
