@@ -200,25 +200,47 @@ __device__ __forceinline__ void put_bf16(float v, fk_b8 &hi, fk_b8 &lo, int j) {
     if constexpr (SPLIT) lo[j] = (__bf16)(v - (float)h);
 }
 
+// The lanes whose points an evaluation takes, in rounds of 16: the lanes in
+// `mask` first, in order, so that as many rounds are run as those fill.  A
+// point's results do not depend on its place.  (At the Dynkin kernel's
+// evaluation points a third of the lanes hold a path on average at the path
+// counts a control variate leaves, and the four rounds took near half its
+// instructions.)
+struct EvalLanes {
+    int dest;      // the lane's place: round dest / 16, column dest % 16
+    int src;       // the lane whose place this lane's number is
+    int rounds;
+};
+__device__ __forceinline__ EvalLanes eval_lanes(uint64_t mask) {
+    const int lane = threadIdx.x & 63, cnt = __popcll(mask);
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    const int dest = __builtin_amdgcn_inverse_ballot_w64(mask) ? rank : cnt + lane - rank;
+    return EvalLanes{dest, __builtin_amdgcn_ds_permute(4 * dest, lane), (cnt + 15) >> 4};
+}
+
 // Wavefront-wide forward-mode evaluation.  Every lane of the wavefront must
-// call it.  Lane l's point is (tau, x, y); on return out[o][c] holds, for
-// output o, channel c = value, d/dx, d/dy, d/dtau, Laplacian (x, y).
+// call it.  The point of a lane in `mask` is (tau, x, y); on return its
+// out[o][c] holds, for output o, channel c = value, d/dx, d/dy, d/dtau,
+// Laplacian (x, y) (other lanes: not set).
 // Activations enter the products as BF16 hi + lo pairs.
 //
 // Register budget: per round (16 points) at most the layer-2 accumulators
 // (4 output tiles x 5 channels x 4) plus one operand block are live; layer 1
 // is computed per K block as it is consumed, and layer 3 per output tile from
 // the hi/lo operands of both K blocks.
-__device__ void net_eval_wave(const NetLds &N, float tscale2, float tau, float x, float y, float out[2][5]) {
+__device__ void net_eval_wave(const NetLds &N, uint64_t mask, float tscale2, float tau, float x, float y,
+                              float out[2][5]) {
     const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15;
+    const EvalLanes E = eval_lanes(mask);
 #pragma unroll 1
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < E.rounds; ++r) {
         // an index offset the compiler cannot see through: keeps the weight
         // reads inside the loop instead of hoisting them into registers
         int lz = 0;
         asm volatile("" : "+s"(lz));
         const NetLds &M = *reinterpret_cast<const NetLds *>(reinterpret_cast<const char *>(&N) + lz);
-        const int src = 16 * r + n;
+        const int src = __shfl(E.src, 16 * r + n, 64);
         const float z0 = __shfl(tau, src, 64) * tscale2 - 1.f;
         const float z1 = 2.f * __shfl(x, src, 64) - 1.f;
         const float z2 = 2.f * __shfl(y, src, 64) - 1.f;
@@ -307,7 +329,8 @@ __device__ void net_eval_wave(const NetLds &N, float tscale2, float tau, float x
                 v += __shfl_xor(v, 16, 64);
                 v += __shfl_xor(v, 32, 64);
                 if (c == 0) v += M.b4[o];
-                if (g == r) out[o][c] = v;
+                v = __shfl(v, E.dest & 15, 64);
+                if ((E.dest >> 4) == r) out[o][c] = v;
             }
     }
 }
@@ -353,13 +376,15 @@ __device__ __forceinline__ fk_b8 load_a_at(const uint16_t *W, int mt, int kb, in
 // reads stay inside the round (the weights are not hoisted into registers)
 // and fold into the reads' immediate offsets.
 template <bool SPLIT>
-__device__ void net_grad_wave(const NetLds &N, float tscale2, float tau, float x, float y, float out[2][2]) {
+__device__ void net_grad_wave(const NetLds &N, uint64_t mask, float tscale2, float tau, float x, float y,
+                              float out[2][2]) {
     const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15;
+    const EvalLanes E = eval_lanes(mask);
 #pragma unroll 1
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < E.rounds; ++r) {
         int off_g = 64 * g, off_q = 16 * g, off_w = 2 * (n * kWS + 8 * g);
         asm volatile("" : "+v"(off_g), "+v"(off_q), "+v"(off_w));
-        const int src = 16 * r + n;
+        const int src = __shfl(E.src, 16 * r + n, 64);
         const float z0 = __shfl(tau, src, 64) * tscale2 - 1.f;
         const float z1 = 2.f * __shfl(x, src, 64) - 1.f;
         const float z2 = 2.f * __shfl(y, src, 64) - 1.f;
@@ -469,7 +494,8 @@ __device__ void net_grad_wave(const NetLds &N, float tscale2, float tau, float x
                 float v = po[o][c];
                 v += __shfl_xor(v, 16, 64);
                 v += __shfl_xor(v, 32, 64);
-                if (g == r) out[o][c] = v * (2.f / K2);
+                v = __shfl(v, E.dest & 15, 64);
+                if ((E.dest >> 4) == r) out[o][c] = v * (2.f / K2);
             }
     }
 }
@@ -486,7 +512,7 @@ __global__ void __launch_bounds__(256) cv_eval_kernel(const uint16_t *bf, float 
     const bool ok = i < n;
     const float t = ok ? txy[3 * i] : 0.f, x = ok ? txy[3 * i + 1] : 0.5f, y = ok ? txy[3 * i + 2] : 0.5f;
     float o[2][5];
-    net_eval_wave(N, tscale2, t, x, y, o);
+    net_eval_wave(N, ~0ull, tscale2, t, x, y, o);
     add_base(base, x, y, o);
     if (ok)
         for (int c = 0; c < 2; ++c)
@@ -505,7 +531,7 @@ __global__ void __launch_bounds__(256) cv_eval_grad_kernel(const uint16_t *bf, f
     const bool ok = i < n;
     const float t = ok ? txy[3 * i] : 0.f, x = ok ? txy[3 * i + 1] : 0.5f, y = ok ? txy[3 * i + 2] : 0.5f;
     float o[2][2];
-    net_grad_wave<SPLIT>(N, tscale2, t, x, y, o);
+    net_grad_wave<SPLIT>(N, ~0ull, tscale2, t, x, y, o);
     add_base_grad(base, o);
     if (ok)
         for (int c = 0; c < 2; ++c)
@@ -518,7 +544,7 @@ __global__ void __launch_bounds__(256) cv_eval_grad_kernel(const uint16_t *bf, f
 struct CvArgs {
     const uint16_t *bf;
     float tscale2;               // 2 / T
-    uint32_t stride_iters;       // network evaluations every stride_iters iterations (2 steps each)
+    uint32_t stride_iters;       // network evaluations every stride_iters pairs of steps
     float base;                  // identity base (0 or 1)
     const float2 *r0;            // [n_out] integrand at the start point of each node
     NodeAcc *acc_cv;             // [n_out] sums of the CV scores
@@ -548,9 +574,15 @@ __device__ __forceinline__ void drift_at_tau(const Lane &L, float tau, float &bx
     drift<KIND>(L.dens, ox, oy, L.xh, L.yh, bx, by);
 }
 
+// Dynkin form.  Between evaluation points the lanes take step pairs without a
+// branch (pair_step); an ended path waits for the next evaluation, which takes
+// the lanes that need it only.  Two waves per SIMD (256 VGPRs; at three the
+// evaluation spills and the kernel runs 25% slower).  Measured (moving bump,
+// 1521 nodes x 173 paths, stride 100): 6.7 ms against 9.9 with a branch after
+// each step and four rounds per evaluation; what is left is two paths to a
+// lane, so that half of it is the wait for the last ones.
 template <int KIND, int TMODE, bool UNIFORM>
 __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, const CvArgs c) {
-    constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
     __shared__ NetLds N;
     load_net(N, c.bf);
     __syncthreads();
@@ -563,28 +595,43 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
     const uint32_t total_chunks = launch_chunks(a);
     bool q_done = !grab_chunk<2>(a, total_chunks, first_chunk(), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane);
     const uint32_t key0 = a.key0, key1 = a.key1;
+    const PhiloxKeys keys = philox_keys(key0, key1);
+    const uint32_t mask = in_vgpr(kUnitMask);
     Lane L;
-    bool active = false, parked = false, out = false;
-    float plx = 0.f, ply = 0.f;              // plain score of a parked path
+    PairLane P{};
+    uint64_t act = 0, park = 0;              // lanes with a running path, and with one that has ended
+    bool out = false;
+    float plx = 0.f, ply = 0.f;              // a parked path: its plain score,
+    float ex = 0.f, ey = 0.f, s_end = 0.f;   // end point and elapsed time
     float Ix = 0.f, Iy = 0.f;                // sum of r ds
     float rx = 0.f, ry = 0.f;                // integrand at the last evaluation
-    int32_t k_last = 0;
+    int32_t k_last = 0;                      // steps there
     const float tend = a.levels[0].tend;     // PDE time at path start
+    const float dt = a.levels[0].dt;
     uint32_t my_tag = 0;                     // accumulation tag of the path's chunk
     uint32_t my_steps = 0;
-    uint32_t until_eval = 0;                 // iterations to the next evaluation point
+    uint32_t until_eval = 0;                 // pairs of steps to the next evaluation point
+    lane_level<KIND, TMODE>(L, a.levels[0]);
+    pair_idle<false>(L, P);
 
-    for (;; --until_eval) {
+    for (;;) {
         if (until_eval == 0) {
             until_eval = c.stride_iters;
             // ---- evaluation point: integrand of running paths, end value of
             //      parked ones (every lane of the wavefront joins) ------------
-            if (ballot(active || parked) != 0ull) {
-                const bool ev = active || parked;
-                const float sk = (parked && L.k >= L.K) ? L.horizon : (float)L.k * L.dt;
-                const float tau = ev ? tend - sk : 0.f;
-                float o[2][5];
-                net_eval_wave(N, c.tscale2, tau, ev ? L.xh : 0.5f, ev ? L.yh : 0.5f, o);
+            const uint64_t ev = act | park;
+            if (ev != 0ull) {
+                const bool active = __builtin_amdgcn_inverse_ballot_w64(act);
+                const bool parked = __builtin_amdgcn_inverse_ballot_w64(park);
+                if (active) L.k = 2 * P.half;
+                if (parked) {
+                    L.xh = ex;
+                    L.yh = ey;
+                }
+                const float sk = parked ? s_end : (float)L.k * dt;
+                const float tau = active || parked ? tend - sk : 0.f;
+                float o[2][5] = {};
+                net_eval_wave(N, ev, c.tscale2, tau, L.xh, L.yh, o);
                 add_base(c.base, L.xh, L.yh, o);
                 // integrand at this state; for a parked path its end state,
                 // with the drift at the end time
@@ -593,15 +640,13 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
                 if (parked) drift_at_tau<KIND, TMODE>(L, tau, bx, by);
                 const float rnx = o[0][4] + fmaf(bx, o[0][1], by * o[0][2]) - o[0][3];
                 const float rny = o[1][4] + fmaf(bx, o[1][1], by * o[1][2]) - o[1][3];
-                if (ev) {
-                    // trapezoidal rule over the interval since the last evaluation
-                    const float ds = sk - (float)k_last * L.dt;
-                    Ix = fmaf(0.5f * (rx + rnx), ds, Ix);
-                    Iy = fmaf(0.5f * (ry + rny), ds, Iy);
-                    rx = rnx;
-                    ry = rny;
-                    k_last = L.k;
-                }
+                // trapezoidal rule over the interval since the last evaluation
+                const float ds = fmaf(-(float)k_last, dt, sk);
+                Ix = fmaf(0.5f * (rx + rnx), ds, Ix);
+                Iy = fmaf(0.5f * (ry + rny), ds, Iy);
+                rx = rnx;
+                ry = rny;
+                k_last = L.k;
                 // plain scores may be relative to the start point; the CV
                 // score is g - u_hat(end) + sum r ds, absolute
                 const float sx0 = a.shift ? L.px : 0.f, sy0 = a.shift ? L.py : 0.f;
@@ -613,11 +658,11 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
                     if (a.exit_step) a.exit_step[rec] = out ? L.k : -1;
                 }
                 acc_wave<2>(slots, accs, parked, my_tag, L.out, v, (uint32_t)L.k, lane);
-                parked = false;
+                if (parked) pair_idle<false>(L, P);
+                park = 0ull;
             }
             // ---- refill idle lanes (paths start only at evaluation points) ----
-            uint64_t need = ballot(!active && !parked);
-            while (need != 0ull && !q_done) {
+            while (~act != 0ull && !q_done) {
                 if (q_next >= q_end) {
                     if (!grab_chunk<2>(a, total_chunks, next_chunk(a), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane)) {
                         q_done = true;
@@ -625,12 +670,15 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
                     }
                     continue;
                 }
+                const uint64_t need = ~act;
                 const uint32_t avail = q_end - q_next;
                 const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
-                if (!active && !parked && rank < avail) {
+                const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
+                if (take) {
                     const NodeDev nd = a.nodes[q_slot];
                     lane_start<KIND, TMODE>(L, nd, a.levels, q_next + rank);
+                    pair_start<false>(L, P, key0, key1);
                     my_tag = q_tag;
                     const float2 r0 = c.r0[nd.out];
                     rx = r0.x;
@@ -638,47 +686,40 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
                     Ix = 0.f;
                     Iy = 0.f;
                     k_last = 0;
-                    active = true;
                 }
+                act |= ballot(take);
                 q_next += min((uint32_t)__popcll(need), avail);
-                need = ballot(!active && !parked);
             }
         }
-        if (ballot(active || parked) == 0ull && q_done) break;
+        if (act == 0ull) {
+            if (park == 0ull && q_done) break;
+            until_eval = 0;      // nothing runs: on to the evaluation and refill
+            continue;
+        }
 
-        if (active) {
-            out = false;
-            if (L.k < L.K) {
-                const PhiloxOut r = philox4x32_10((uint32_t)L.k >> 1, L.path, L.nid, L.ctr3, key0, key1);
-                float ox = L.ox, oy = L.oy, cr = 0.f, sr = 0.f;
-                if constexpr (kMovingBackward) {
-                    const float rev = fmaf(-(float)L.k, L.drev, L.rev0);
-                    cr = hw_cos_rev(rev);
-                    sr = hw_sin_rev(rev);
-                    ox = L.dens.orbit_r * cr;
-                    oy = L.dens.orbit_r * sr;
-                }
-                out = em_step<KIND, UNIFORM>(L, r.r0, r.r1, ox, oy);
-                my_steps += 1;
-                if (!out && L.k < L.K) {
-                    if constexpr (kMovingBackward) {
-                        const float c2 = fmaf(cr, L.cos_d, sr * L.sin_d);
-                        const float s2 = fmaf(sr, L.cos_d, -cr * L.sin_d);
-                        ox = L.dens.orbit_r * c2;
-                        oy = L.dens.orbit_r * s2;
-                    }
-                    out = em_step<KIND, UNIFORM>(L, r.r2, r.r3, ox, oy);
-                    my_steps += 1;
-                }
-            }
-            if (out || L.k >= L.K) {
-                // the last interval is closed at the next evaluation point,
-                // where u_hat and the integrand at the end state are known
-                score_path(a, L, out, plx, ply);
-                active = false;
-                parked = true;
-            }
+        // ---- step pairs, until the evaluation point or until a path ends -----
+        Pair p;
+        uint64_t fin;
+        do {
+            fin = ballot(pair_step<KIND, TMODE, UNIFORM, false>(L, P, keys, mask, p)) & act;
+            --until_eval;
+        } while (fin == 0ull && until_eval != 0);
+        if (fin == 0ull) continue;
+        const int with = pair_ends<KIND>(L, P, p);
+        fin &= ballot(with != 0);
+        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+            // the last interval is closed at the next evaluation point, where
+            // u_hat and the integrand at the end state are known
+            out = pair_end<KIND, false>(L, P, p, with);
+            score_path(a, L, out, plx, ply);
+            my_steps += (uint32_t)L.k;
+            ex = L.xh;
+            ey = L.yh;
+            s_end = L.k >= L.K ? a.levels[0].horizon : (float)L.k * dt;
+            pair_idle<false>(L, P);
         }
+        act &= ~fin;
+        park |= fin;
     }
     slots_collect<2>(slots, accs, lane);
     unsigned long long st = my_steps;
@@ -754,17 +795,19 @@ struct MgArgs {
                                  // BF16-rounded activations (0); selects the instantiation
 };
 
-// Four waves per SIMD (128 VGPRs) with the BF16 gradient, three (168) with
-// the hi + lo split: the few values the compiler moves to scratch are
-// touched at block boundaries, and the path loop between them gains the
-// latency hiding of the extra waves (four waves were about 14% faster per
-// path than two on the moving bump; at four the split form spills ~57
-// registers around each evaluation and runs 5% slower at stride 20 than at
-// three).  The Dynkin kernel, whose evaluation points are ten times as
-// frequent, stays at two.
+// Steps run in pairs without a branch (pair_step) up to the next evaluation
+// point or the end of some path, and the evaluation takes the lanes that hold
+// a path only.  Bound by VALU issue; a third of the lanes' time goes to the
+// wait for the next evaluation point and to the last paths of a wavefront.
+// Three waves per SIMD (163 VGPRs) with the BF16 gradient, two (201) with the
+// hi + lo split, as many as fit without spilling: with one more the pairs
+// reload what the evaluation displaced (10.0 -> 11.0 ms and 9.9 -> 10.8).
+// Measured (moving bump, 1521 nodes x 696 paths, stride 500, BF16): 10.0 ms
+// against 13.9 with a branch after each step at four waves; at stride 20
+// (173 paths) 10.7 against 19.5, of which the evaluation's rounds are most,
+// and with the split 13 against 23.
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool SPLIT>
-__global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const PathArgs a, const MgArgs c) {
-    constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
+__global__ void __launch_bounds__(256, SPLIT ? 2 : 3) fk_mg_path_kernel(const PathArgs a, const MgArgs c) {
     __shared__ NetLds N;
     load_net(N, c.bf);
     __syncthreads();
@@ -777,8 +820,13 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
     const uint32_t total_chunks = launch_chunks(a);
     bool q_done = !grab_chunk<2>(a, total_chunks, first_chunk(), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane);
     const uint32_t key0 = a.key0, key1 = a.key1;
+    const PhiloxKeys keys = philox_keys(key0, key1);
+    const uint32_t mask = in_vgpr(kUnitMask);
     Lane L;
-    bool active = false;
+    PairLane P{};
+    uint64_t act = 0;                                   // lanes with a path
+    lane_level<KIND, TMODE>(L, a.levels[0]);
+    pair_idle<BRIDGE>(L, P);
     float gxx = 0.f, gxy = 0.f, gyx = 0.f, gyy = 0.f;   // gradient of (xi_hat, eta_hat) held over the block
     float dbx = 0.f, dby = 0.f;                         // Brownian part of the block so far
     float mx = 0.f, my = 0.f;                           // the martingale sum of the closed blocks
@@ -787,19 +835,15 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
     uint32_t my_tag = 0;                                // accumulation tag of the path's chunk
     uint32_t my_steps = 0;
 
-    bool closed = false;                                // the lane's last path closed its chunk's slot
-    for (uint32_t until_eval = 0;; --until_eval) {     // iterations to the next block boundary
-        if (ballot(closed) != 0ull) {
-            slots_collect<2>(slots, accs, lane);
-            closed = false;
-        }
+    for (uint32_t until_eval = 0;;) {                  // pairs of steps to the next block boundary
         if (until_eval == 0) {
             until_eval = c.stride_iters;
             // ---- block boundary of running paths (every lane joins) ---------
-            if (ballot(active) != 0ull) {
-                const float tau = active ? tend - (float)L.k * L.dt : 0.f;
-                float o[2][2];
-                net_grad_wave<SPLIT>(N, c.tscale2, tau, active ? L.xh : 0.5f, active ? L.yh : 0.5f, o);
+            if (act != 0ull) {
+                const bool active = __builtin_amdgcn_inverse_ballot_w64(act);
+                const float tau = active ? tend - (float)(2 * P.half) * L.dt : 0.f;
+                float o[2][2] = {};
+                net_grad_wave<SPLIT>(N, act, c.tscale2, tau, L.xh, L.yh, o);
                 add_base_grad(c.base, o);
                 if (c.grid_base) {
                     // grid base: the network's part, held until the next
@@ -819,8 +863,7 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
                 }
             }
             // ---- refill idle lanes ------------------------------------------
-            uint64_t need = ballot(!active);
-            while (need != 0ull && !q_done) {
+            while (~act != 0ull && !q_done) {
                 if (q_next >= q_end) {
                     if (!grab_chunk<2>(a, total_chunks, next_chunk(a), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane)) {
                         q_done = true;
@@ -828,12 +871,15 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
                     }
                     continue;
                 }
+                const uint64_t need = ~act;
                 const uint32_t avail = q_end - q_next;
                 const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
-                if (!active && rank < avail) {
+                const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
+                if (take) {
                     const NodeDev nd = a.nodes[q_slot];
                     lane_start<KIND, TMODE>(L, nd, a.levels, q_next + rank);
+                    pair_start<BRIDGE>(L, P, key0, key1);
                     my_tag = q_tag;
                     const float4 g0 = c.g0[nd.out];
                     gxx = g0.x;
@@ -845,77 +891,75 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) fk_mg_path_kernel(const Pa
                     nyx = g0.z;
                     nyy = g0.w;
                     dbx = dby = mx = my = 0.f;
-                    active = true;
                 }
+                act |= ballot(take);
                 q_next += min((uint32_t)__popcll(need), avail);
-                need = ballot(!active);
             }
         }
-        if (ballot(active) == 0ull && q_done) break;
+        if (act == 0ull) {
+            if (q_done) break;
+            until_eval = 0;      // nothing runs: on to the refill
+            continue;
+        }
 
-        if (active) {
-            bool out = false;
-            if (L.k < L.K) {
-                if (c.grid_base) {
-                    // close the block (every 2 steps): G = the mesh's gradient
-                    // here + the network's part
-                    mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
-                    my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
-                    dbx = dby = 0.f;
-                    if (c.gtab) {
-                        table_gradient(c.gtab, a.grid_n, 0, L.xh, L.yh, gxx, gxy);
-                        table_gradient(c.gtab, a.grid_n, 1, L.xh, L.yh, gyx, gyy);
-                    } else {
-                        grid_gradient(a.grid_xi, a.grid_n, L.xh, L.yh, gxx, gxy);
-                        grid_gradient(a.grid_eta, a.grid_n, L.xh, L.yh, gyx, gyy);
-                    }
-                    gxx += nxx;
-                    gxy += nxy;
-                    gyx += nyx;
-                    gyy += nyy;
-                }
-                const PhiloxOut r = philox4x32_10((uint32_t)L.k >> 1, L.path, L.nid, L.ctr3, key0, key1);
-                float ox = L.ox, oy = L.oy, cr = 0.f, sr = 0.f;
-                if constexpr (kMovingBackward) {
-                    const float rev = fmaf(-(float)L.k, L.drev, L.rev0);
-                    cr = hw_cos_rev(rev);
-                    sr = hw_sin_rev(rev);
-                    ox = L.dens.orbit_r * cr;
-                    oy = L.dens.orbit_r * sr;
-                }
-                float wx, wy;
-                out = cv_step<KIND, UNIFORM, BRIDGE>(L, r.r0, r.r1, ox, oy, wx, wy, key0, key1);
-                dbx += wx;
-                dby += wy;
-                my_steps += 1;
-                if (!out && L.k < L.K) {
-                    if constexpr (kMovingBackward) {
-                        const float c2 = fmaf(cr, L.cos_d, sr * L.sin_d);
-                        const float s2 = fmaf(sr, L.cos_d, -cr * L.sin_d);
-                        ox = L.dens.orbit_r * c2;
-                        oy = L.dens.orbit_r * s2;
-                    }
-                    out = cv_step<KIND, UNIFORM, BRIDGE>(L, r.r2, r.r3, ox, oy, wx, wy, key0, key1);
-                    dbx += wx;
-                    dby += wy;
-                    my_steps += 1;
-                }
-            }
-            if (out || L.k >= L.K) {
-                float plx, ply;
-                score_path(a, L, out, plx, ply);
+        // ---- step pairs, until the block boundary or until a path ends -------
+        Pair p;
+        float d1x, d1y;          // the block's Brownian part after the pair's first step
+        uint64_t fin;
+        do {
+            if (c.grid_base) {
+                // close the block (every 2 steps): G = the mesh's gradient
+                // here + the network's part
                 mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
                 my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
-                const float sx0 = a.shift ? L.px : 0.f, sy0 = a.shift ? L.py : 0.f;
-                const float v[2] = {(plx + sx0) - mx, (ply + sy0) - my};
-                closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
-                const uint64_t rec = path_rec(L, a.n_paths);
-                if (a.scores) a.scores[rec] = make_float2(plx, ply);
-                if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
-                if (a.exit_step) a.exit_step[rec] = out ? L.k : -1;
-                active = false;
+                dbx = dby = 0.f;
+                if (c.gtab) {
+                    table_gradient(c.gtab, a.grid_n, 0, L.xh, L.yh, gxx, gxy);
+                    table_gradient(c.gtab, a.grid_n, 1, L.xh, L.yh, gyx, gyy);
+                } else {
+                    grid_gradient(a.grid_xi, a.grid_n, L.xh, L.yh, gxx, gxy);
+                    grid_gradient(a.grid_eta, a.grid_n, L.xh, L.yh, gyx, gyy);
+                }
+                gxx += nxx;
+                gxy += nxy;
+                gyx += nyx;
+                gyy += nyy;
             }
+            const bool may = pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p);
+            d1x = dbx + p.w1x;
+            d1y = dby + p.w1y;
+            dbx = d1x + p.w2x;
+            dby = d1y + p.w2y;
+            fin = ballot(may) & act;
+            --until_eval;
+        } while (fin == 0ull && until_eval != 0);
+        if (fin == 0ull) continue;
+        const int with = pair_ends<KIND>(L, P, p);
+        fin &= ballot(with != 0);
+        bool closed = false;     // the lane's path closed its chunk's slot
+        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+            if (with == 1) {
+                dbx = d1x;
+                dby = d1y;
+            }
+            if (L.K <= 0) dbx = dby = 0.f;
+            const bool out = pair_end<KIND, BRIDGE>(L, P, p, with);
+            float plx, ply;
+            score_path(a, L, out, plx, ply);
+            mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
+            my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
+            const float sx0 = a.shift ? L.px : 0.f, sy0 = a.shift ? L.py : 0.f;
+            const float v[2] = {(plx + sx0) - mx, (ply + sy0) - my};
+            closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
+            my_steps += (uint32_t)L.k;
+            const uint64_t rec = path_rec(L, a.n_paths);
+            if (a.scores) a.scores[rec] = make_float2(plx, ply);
+            if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
+            if (a.exit_step) a.exit_step[rec] = out ? L.k : -1;
+            pair_idle<BRIDGE>(L, P);
         }
+        act &= ~fin;
+        if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);
     }
     slots_collect<2>(slots, accs, lane);
     unsigned long long st = my_steps;
@@ -1091,7 +1135,7 @@ __global__ void __launch_bounds__(256) cv_node_kernel(const CvNodeArgs na, const
         L.yl = 0.f;
     }
     float o[2][5];
-    net_eval_wave(N, tscale2, tend, L.xh, L.yh, o);
+    net_eval_wave(N, ~0ull, tscale2, tend, L.xh, L.yh, o);
     // the value's base in FP64 from the node's hi + lo coordinates
     const double vx = (double)o[0][0] + na.base * ((double)L.xh + (double)L.xl);
     const double vy = (double)o[1][0] + na.base * ((double)L.yh + (double)L.yl);

@@ -260,7 +260,6 @@ hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_ste
 // then ends on the latency of single chains).
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FIRST_BY_INDEX = false>
 __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
-    constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
     const uint32_t lane = threadIdx.x & 63u;
     __shared__ AccSlot<2> slot_tab[4][kAccSlots];
     AccSlot<2> *slots = slot_tab[threadIdx.x >> 6];
@@ -282,28 +281,12 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
     const uint32_t mask = in_vgpr(kUnitMask);
 
     Lane L;
-    PhiloxLane pp{};          // the lane's path's fixed Philox products
-    uint32_t bridge_ck = 0;   // pp.ck of the bridge test's stream
-    SideDist dist{};          // the bridge test's distances at the lane's position
-    float iD = 0.f, iD_last = 0.f, drev2 = 0.f;
-    int32_t half = 0, half_end = 0;   // step pairs taken; the pair that reaches step K
+    PairLane P{};
     uint32_t my_tag = 0;      // accumulation tag of the lane's path's chunk
     uint32_t my_steps = 0;
     uint64_t act = 0;         // the lanes with a path
-    auto idle = [&]() {       // a lane without a path: a point that stays where it is
-        L.xh = L.yh = 0.5f;
-        L.xl = L.yl = 0.f;
-        L.dt = L.cbm = 0.f;
-        L.K = 0x7fffffff;
-        half_end = 0x3f000000;
-        half = 0;
-        if constexpr (BRIDGE) {
-            dist = side_dist(L);
-            iD = 1e30f;
-        }
-    };
     lane_level<KIND, TMODE>(L, a.levels[0]);
-    idle();
+    pair_idle<BRIDGE>(L, P);
 
     for (;;) {
         // ---- refill idle lanes -------------------------------------------
@@ -339,20 +322,7 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
             const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
             if (take) {
                 lane_start<KIND, TMODE>(L, a.nodes[q_slot], a.levels, q_next + rank);
-                pp = philox_lane(L.path, L.nid, L.ctr3, key0, key1);
-                half = 0;
-                half_end = min((L.K - 1) >> 1, 0x3f000000);   // past it every pair is looked at
-                drev2 = 2.f * L.drev;
-                if (L.K <= 0) {      // scored where it starts: keeps its low parts in values it has no use for
-                    L.horizon = L.xl;
-                    L.dt_last = L.yl;
-                }
-                if constexpr (BRIDGE) {
-                    bridge_ck = (L.ctr3 | 4u) ^ key1;
-                    dist = side_dist(L);
-                    iD = 1.f / L.dt;
-                    iD_last = 1.f / L.dt_last;
-                }
+                pair_start<BRIDGE>(L, P, key0, key1);
                 my_tag = q_tag;
             }
             act |= ballot(take);
@@ -361,100 +331,25 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
         if (act == 0ull) break;
 
         // ---- step pairs, until a path ends ---------------------------------
-        float x1h, x1l, y1h, y1l;            // the position after the pair's first step
-        int32_t side1 = -1, side2 = -1;
+        Pair p;
         uint64_t fin;
-        for (;;) {
-            const PhiloxOut r = philox4x32_10_lane((uint32_t)half, pp, keys);
-            float ox = L.ox, oy = L.oy, ox2 = ox, oy2 = oy;
-            if constexpr (kMovingBackward) {
-                // Orbit angle at PDE time t_init + t - k dt (k = 2 half), in
-                // revolutions; one step later it is smaller by omega dt: rotate
-                // (cos, sin) instead of re-evaluating them.
-                const float rev = fmaf(-(float)half, drev2, L.rev0);
-                const float cr = hw_cos_rev(rev), sr = hw_sin_rev(rev);
-                ox = L.dens.orbit_r * cr;
-                oy = L.dens.orbit_r * sr;
-                ox2 = L.dens.orbit_r * fmaf(cr, L.cos_d, sr * L.sin_d);
-                oy2 = L.dens.orbit_r * fmaf(sr, L.cos_d, -cr * L.sin_d);
-            }
-            float D1 = L.dt, D2 = L.dt, cb1 = L.cbm, cb2 = L.cbm, iD1 = iD, iD2 = iD;
-            if constexpr (!UNIFORM) {
-                // the last step K - 1 is the pair's first (K odd) or second one
-                const bool l1 = 2 * half == L.K - 1, l2 = 2 * half == L.K - 2;
-                D1 = l1 ? L.dt_last : D1;
-                cb1 = l1 ? L.cbm_last : cb1;
-                iD1 = l1 ? iD_last : iD1;
-                D2 = l2 ? L.dt_last : D2;
-                cb2 = l2 ? L.cbm_last : cb2;
-                iD2 = l2 ? iD_last : iD2;
-            }
-            float dwx, dwy;
-            x1h = L.xh;
-            x1l = L.xl;
-            y1h = L.yh;
-            y1l = L.yl;
-            em_move<KIND>(x1h, x1l, y1h, y1l, L.dens, r.r0, r.r1, ox, oy, D1, cb1, mask, dwx, dwy);
-            L.xh = x1h;
-            L.xl = x1l;
-            L.yh = y1h;
-            L.yl = y1l;
-            em_move<KIND>(L.xh, L.xl, L.yh, L.yl, L.dens, r.r2, r.r3, ox2, oy2, D2, cb2, mask, dwx, dwy);
-            half += 1;
-            // The path may have ended in this pair: as unsigned numbers, the bit
-            // patterns of the floats in [0, 1) lie below that of 1, all others
-            // (1 itself among them, hence "may") from there on, and half_end -
-            // half once it is negative.
-            uint32_t u1 = max(max(__float_as_uint(x1h), __float_as_uint(y1h)), __float_as_uint(L.xh));
-            u1 = max(max(u1, __float_as_uint(L.yh)), (uint32_t)(half_end - half));
-            bool ends = u1 >= 0x3f800000u;
-            if constexpr (BRIDGE) {
-                // The bridge tests of both steps; their uniforms are words 0 and 1
-                // of Philox(k/2, path, node, ctr3 | 4).
-                const PhiloxOut u =
-                    philox4x32_10_lane((uint32_t)half - 1u, PhiloxLane{bridge_ck, pp.bk, pp.hk, pp.lk}, keys);
-                const SideDist d1 = side_dist(x1h, x1l, y1h, y1l), d2 = side_dist(L);
-                const float p1 = bridge_prob(dist, d1, iD1, side1), p2 = bridge_prob(d1, d2, iD2, side2);
-                side1 = bridge_uniform(u.r0) < p1 ? side1 : -1;
-                side2 = bridge_uniform(u.r1) < p2 ? side2 : -1;
-                ends |= (side1 & side2) >= 0;
-                dist = d2;
-            }
-            fin = ballot(ends) & act;
-            if (fin != 0ull) break;
-        }
+        do {
+            fin = ballot(pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p)) & act;
+        } while (fin == 0ull);
 
         // ---- score (eq. (7b)) and the node's sums ------------------------------
-        const int32_t k0 = 2 * half - 2;
-        const int32_t s1 = outside<KIND>(x1h, x1l, y1h, y1l), s2 = outside<KIND>(L.xh, L.xl, L.yh, L.yl);
-        const bool first = s1 < 0 || side1 >= 0 || k0 + 1 >= L.K;   // ends with the pair's first step
-        fin &= ballot(first || s2 < 0 || side2 >= 0 || k0 + 2 >= L.K);
+        const int with = pair_ends<KIND>(L, P, p);
+        fin &= ballot(with != 0);
         bool closed = false;      // the lane's path closed its chunk's slot
         if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
-            const bool cross = first ? s1 < 0 : s2 < 0;
-            const int side = first ? side1 : side2;
-            const bool out = L.K > 0 && (cross || side >= 0);
-            if (first) {
-                L.xh = x1h;
-                L.xl = x1l;
-                L.yh = y1h;
-                L.yl = y1l;
-            }
-            if (L.K <= 0) {
-                L.xh = L.px;
-                L.xl = L.horizon;
-                L.yh = L.py;
-                L.yl = L.dt_last;
-            }
-            if constexpr (BRIDGE) move_to_side(L, cross || !out ? -1 : side);
-            L.k = out ? k0 + (first ? 1 : 2) : L.K;
+            const bool out = pair_end<KIND, BRIDGE>(L, P, p, with);
             float v[2];
             score_path(a, L, out, v[0], v[1]);
             closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
             my_steps += (uint32_t)L.k;      // the path's steps, counted once at its end
             if (a.scores) a.scores[path_rec(L, a.n_paths)] = make_float2(v[0], v[1]);
             if (a.exit_step) a.exit_step[path_rec(L, a.n_paths)] = out ? L.k : -1;
-            idle();
+            pair_idle<BRIDGE>(L, P);
         }
         act &= ~fin;
         if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);

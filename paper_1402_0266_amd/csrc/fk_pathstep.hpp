@@ -310,6 +310,159 @@ __device__ __forceinline__ void lane_start(Lane &L, const NodeDev &nd, const Lev
     lane_level<KIND, TMODE>(L, levels[nd.level]);
 }
 
+// ---------------------------------------------------------------------------
+// Steps in pairs (the two steps of one Philox call) without a branch between
+// them: both are taken, and the rare path that ends in the pair is sorted out
+// afterwards (pair_end).
+// ---------------------------------------------------------------------------
+struct PairLane {
+    PhiloxLane pp;            // the path's fixed Philox products
+    uint32_t bridge_ck;       // pp.ck of the bridge test's stream
+    SideDist dist;            // the bridge test's distances at the lane's position
+    float iD, iD_last;        // the bridge test's 1 / D
+    float drev2;              // 2 drev
+    int32_t half, half_end;   // pairs taken; the number of them by which the path has ended
+};
+
+// The pair's first point, its Brownian parts, and the bridge test's outcomes.
+struct Pair {
+    float xh, xl, yh, yl;
+    float w1x, w1y, w2x, w2y;
+    int side1, side2;
+};
+
+// half_end past this (as a float's bits, 0.5) would read as a float >= 1:
+// there every pair is looked at.
+constexpr int32_t kHalfMax = 0x3f000000;
+
+// A lane without a path: a point that stays at (0.5, 0.5).  L.k is kept.
+template <bool BRIDGE>
+__device__ __forceinline__ void pair_idle(Lane &L, PairLane &P) {
+    L.xh = L.yh = 0.5f;
+    L.xl = L.yl = 0.f;
+    L.dt = L.cbm = 0.f;
+    L.K = 0x7fffffff;
+    P.half = 0;
+    P.half_end = kHalfMax;
+    if constexpr (BRIDGE) {
+        P.dist = side_dist(L);
+        P.iD = 1e30f;
+    }
+}
+
+// After lane_start.
+template <bool BRIDGE>
+__device__ __forceinline__ void pair_start(Lane &L, PairLane &P, uint32_t key0, uint32_t key1) {
+    P.pp = philox_lane(L.path, L.nid, L.ctr3, key0, key1);
+    P.half = 0;
+    P.half_end = min((L.K - 1) >> 1, kHalfMax);
+    P.drev2 = 2.f * L.drev;
+    if (L.K <= 0) {      // scored where it starts: keeps its low parts in values it has no use for
+        L.horizon = L.xl;
+        L.dt_last = L.yl;
+    }
+    if constexpr (BRIDGE) {
+        P.bridge_ck = (L.ctr3 | 4u) ^ key1;
+        P.dist = side_dist(L);
+        P.iD = 1.f / L.dt;
+        P.iD_last = 1.f / L.dt_last;
+    }
+}
+
+// Takes a pair of steps; true where the path may have ended in it.
+template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE>
+__device__ __forceinline__ bool pair_step(Lane &L, PairLane &P, const PhiloxKeys &keys, uint32_t mask, Pair &p) {
+    const PhiloxOut r = philox4x32_10_lane((uint32_t)P.half, P.pp, keys);
+    float ox = L.ox, oy = L.oy, ox2 = ox, oy2 = oy;
+    if constexpr (moving_kind(KIND) && TMODE == TIME_BACKWARD) {
+        // Orbit angle at PDE time t_init + t - k dt (k = 2 half), in
+        // revolutions; one step later it is smaller by omega dt: rotate
+        // (cos, sin) instead of re-evaluating them.
+        const float rev = fmaf(-(float)P.half, P.drev2, L.rev0);
+        const float cr = hw_cos_rev(rev), sr = hw_sin_rev(rev);
+        ox = L.dens.orbit_r * cr;
+        oy = L.dens.orbit_r * sr;
+        ox2 = L.dens.orbit_r * fmaf(cr, L.cos_d, sr * L.sin_d);
+        oy2 = L.dens.orbit_r * fmaf(sr, L.cos_d, -cr * L.sin_d);
+    }
+    float D1 = L.dt, D2 = L.dt, cb1 = L.cbm, cb2 = L.cbm, iD1 = P.iD, iD2 = P.iD;
+    if constexpr (!UNIFORM) {
+        // the last step K - 1 is the pair's first (K odd) or second one
+        const bool l1 = 2 * P.half == L.K - 1, l2 = 2 * P.half == L.K - 2;
+        D1 = l1 ? L.dt_last : D1;
+        cb1 = l1 ? L.cbm_last : cb1;
+        iD1 = l1 ? P.iD_last : iD1;
+        D2 = l2 ? L.dt_last : D2;
+        cb2 = l2 ? L.cbm_last : cb2;
+        iD2 = l2 ? P.iD_last : iD2;
+    }
+    p.xh = L.xh;
+    p.xl = L.xl;
+    p.yh = L.yh;
+    p.yl = L.yl;
+    em_move<KIND>(p.xh, p.xl, p.yh, p.yl, L.dens, r.r0, r.r1, ox, oy, D1, cb1, mask, p.w1x, p.w1y);
+    L.xh = p.xh;
+    L.xl = p.xl;
+    L.yh = p.yh;
+    L.yl = p.yl;
+    em_move<KIND>(L.xh, L.xl, L.yh, L.yl, L.dens, r.r2, r.r3, ox2, oy2, D2, cb2, mask, p.w2x, p.w2y);
+    P.half += 1;
+    // As unsigned numbers, the bit patterns of the floats in [0, 1) lie below
+    // that of 1, all others (1 itself among them, hence "may") from there on,
+    // and half_end - half once it is negative.
+    uint32_t m = max(max(__float_as_uint(p.xh), __float_as_uint(p.yh)), __float_as_uint(L.xh));
+    m = max(max(m, __float_as_uint(L.yh)), (uint32_t)(P.half_end - P.half));
+    bool ends = m >= 0x3f800000u;
+    p.side1 = p.side2 = -1;
+    if constexpr (BRIDGE) {
+        // The bridge tests of both steps; their uniforms are words 0 and 1 of
+        // Philox(k/2, path, node, ctr3 | 4).
+        const PhiloxOut u =
+            philox4x32_10_lane((uint32_t)P.half - 1u, PhiloxLane{P.bridge_ck, P.pp.bk, P.pp.hk, P.pp.lk}, keys);
+        const SideDist d1 = side_dist(p.xh, p.xl, p.yh, p.yl), d2 = side_dist(L);
+        const float p1 = bridge_prob(P.dist, d1, iD1, p.side1), p2 = bridge_prob(d1, d2, iD2, p.side2);
+        p.side1 = bridge_uniform(u.r0) < p1 ? p.side1 : -1;
+        p.side2 = bridge_uniform(u.r1) < p2 ? p.side2 : -1;
+        ends |= (p.side1 & p.side2) >= 0;
+        P.dist = d2;
+    }
+    return ends;
+}
+
+// How a path ends in the pair just taken: not (0), with its first step (1) or
+// with its second one (2).
+template <int KIND>
+__device__ __forceinline__ int pair_ends(const Lane &L, const PairLane &P, const Pair &p) {
+    const int32_t k0 = 2 * P.half - 2;
+    if (outside<KIND>(p.xh, p.xl, p.yh, p.yl) < 0 || p.side1 >= 0 || k0 + 1 >= L.K) return 1;
+    return outside<KIND>(L.xh, L.xl, L.yh, L.yl) < 0 || p.side2 >= 0 || k0 + 2 >= L.K ? 2 : 0;
+}
+
+// The end state of a path that ended with step `with` of the pair: its
+// position, its steps in L.k; true if it left the square.
+template <int KIND, bool BRIDGE>
+__device__ __forceinline__ bool pair_end(Lane &L, const PairLane &P, const Pair &p, int with) {
+    const bool first = with == 1;
+    if (first) {
+        L.xh = p.xh;
+        L.xl = p.xl;
+        L.yh = p.yh;
+        L.yl = p.yl;
+    }
+    const bool cross = outside<KIND>(L.xh, L.xl, L.yh, L.yl) < 0;
+    const int side = first ? p.side1 : p.side2;
+    const bool out = L.K > 0 && (cross || side >= 0);
+    if (L.K <= 0) {
+        L.xh = L.px;
+        L.xl = L.horizon;
+        L.yh = L.py;
+        L.yl = L.dt_last;
+    }
+    if constexpr (BRIDGE) move_to_side(L, cross || !out ? -1 : side);
+    L.k = out ? 2 * P.half - (first ? 1 : 0) : L.K;
+    return out;
+}
+
 // Score of a finished path (eq. (7b)): boundary data at the exit point if
 // it left the square (out), else the initial data at its end point.  With
 // a.shift the identity scores are stored relative to the start point.
