@@ -380,7 +380,7 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
     const int grid = cap_grid(n_cu * bpc, a.total_chunks, S.plan.block);
     if ((e = timing_mark(timed, 0, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    e = S.lockstep ? launch_short_paths(S.kind, S.time_mode, a, nullptr, grid, S.plan.block, stream)
+    e = S.lockstep ? launch_short_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
         : expo     ? launch_expo_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
                    : launch_paths(S.kind, S.time_mode, S.uniform, S.first_by_index, a, grid, S.plan.block, stream);
     if (e != hipSuccess) return hip_fail(e, "path kernel launch");

@@ -2124,7 +2124,7 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
         const int grid = cap_grid(n_cu * bpc, a.total_chunks, 256);
         a.masked = mask ? 1u : 0u;
-        e = lockstep ? launch_short_paths(w->kind, w->time_mode, a, &c, grid, 256, stream)
+        e = lockstep ? launch_short_mesh_paths(w->kind, w->time_mode, a, c, t, level.K, n_nodes, n_cu, grid, 256, stream)
                      : cv_dispatch<MggLaunchF>(w->kind, w->time_mode, uniform, a, c, grid, stream);
         if (e != hipSuccess) return hip_fail(e, "control-variate path kernel launch");
     } else {

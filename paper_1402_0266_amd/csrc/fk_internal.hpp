@@ -244,9 +244,11 @@ hipError_t launch_tables(const TableArgs &t, hipStream_t s);
 // caller's node order (one kernel; with a mask, two): sets
 // counters[kCtrActive], and *total_steps (or nullptr) to 0.
 hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_steps, hipStream_t s);
-// The short-horizon path kernel; mesh: the mesh-gradient control, or nullptr (plain).
-hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, const MggArgs *mesh, int grid, int block,
-                              hipStream_t s);
+// The short-horizon path kernel; with the mesh-gradient control (horizon t in
+// K steps; a's chunks and `grid` hold where the mesh is read from memory).
+hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, int grid, int block, hipStream_t s);
+hipError_t launch_short_mesh_paths(int kind, int time_mode, const PathArgs &a, const MggArgs &c, double t, int64_t K,
+                                   int64_t n_nodes, int n_cu, int grid, int block, hipStream_t s);
 int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, int block);
 // Zeroes a launch's 64 counter words and sets counters[kCtrTotal] (host tables).
 hipError_t launch_counters_init(uint32_t *counters, uint32_t total_chunks, hipStream_t s);

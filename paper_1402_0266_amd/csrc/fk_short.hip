@@ -19,14 +19,19 @@
 // The kernel is bound by VALU issue, so the loop's constants and the round
 // keys are kept in vector registers (in_vgpr, fk_device.hpp).
 //
-// Measured (two bumps frozen, 10689 nodes x 16384 paths x 20 steps): 6.1 ms
-// against the refilling kernel's 9.7 ms, 70 VALU instructions per step of a
-// wavefront at one per 3.8 cycles and SIMD (the rates above give 3.6 for this
-// mix); the ring's 77 nodes x 10^4 paths: 37 us for the whole solve against
-// 106 us.
+// While every path of a wavefront is inside, steps run in pairs without a
+// branch (as pair_step, fk_pathstep.hpp); after the first exit, and for the
+// pair with the last step, lane by lane under a mask.
+//
+// Measured (two bumps frozen, 10689 nodes x 16384 paths x 20 steps): 5.8 ms
+// (6.1 with the masked loop alone) against the refilling kernel's 9.7 ms when
+// it tested after each step; the ring's 77 nodes x 10^4 paths: 36 us for the
+// whole solve against 106 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "fk_accum.hpp"
@@ -133,36 +138,302 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
     return s;
 }
 
-// MESH: the martingale form with the mesh's gradient as control (as
-// fk_mgg_path_kernel, fk_cv.hip), else the plain estimate.
-template <int KIND, int TMODE, bool MESH>
-__global__ void __launch_bounds__(256, MESH ? 5 : 6) fk_short_path_kernel(const PathArgs a, const MggArgs c) {
+// What a path's control needs: nothing (the plain estimate), the mesh's
+// gradient (as fk_mgg_path_kernel, fk_cv.hip) from memory, or the same from
+// the node's tile of the mesh in LDS.
+enum { CTL_NONE = 0, CTL_MESH = 1, CTL_TILE = 2 };
+
+// The launch's constants of a wavefront.
+struct ShortWave {
+    Lane L;
+    int32_t K;
+    uint32_t ctr3, key0, key1;
+    float dt, cbm, dt_last, cbm_last, rev0, drev, cos_d, sin_d;
+    uint32_t mask;
+    PhiloxWave W;
+};
+
+template <int KIND, int TMODE>
+__device__ __forceinline__ ShortWave short_wave(const PathArgs &a) {
+    ShortWave S;
+    const LevelDev &lv = a.levels[0];
+    lane_level<KIND, TMODE>(S.L, lv);
+    S.K = lv.K;
+    S.ctr3 = lv.ctr3;
+    S.key0 = a.key0;
+    S.key1 = a.key1;
+    S.dt = in_vgpr(S.L.dt);
+    S.cbm = in_vgpr(S.L.cbm);
+    S.dt_last = in_vgpr(S.L.dt_last);
+    S.cbm_last = in_vgpr(S.L.cbm_last);
+    S.rev0 = in_vgpr(S.L.rev0);
+    S.drev = in_vgpr(S.L.drev);
+    S.cos_d = in_vgpr(S.L.cos_d);
+    S.sin_d = in_vgpr(S.L.sin_d);
+    S.mask = in_vgpr(kUnitMask);
+    S.L.dens.amp = in_vgpr(S.L.dens.amp);
+    S.L.dens.nscale = in_vgpr(S.L.dens.nscale);
+    S.L.dens.a2s = in_vgpr(S.L.dens.a2s);
+    S.L.dens.cx = in_vgpr(S.L.dens.cx);
+    S.L.dens.cy = in_vgpr(S.L.dens.cy);
+    S.L.dens.orbit_r = in_vgpr(S.L.dens.orbit_r);
+    if constexpr (KIND == KIND_GRID) S.L.dens.fn = in_vgpr(S.L.dens.fn);
+    S.W = philox_wave(S.key0, S.key1);
+    return S;
+}
+
+// A tile of the mesh around a node: per grid node the FP32 differences the
+// gradient is formed from, to the next node in x (xi, eta) and in y (xi, eta).
+constexpr int kTile = 100;
+struct MeshTile {
+    float4 d[kTile * kTile];
+};
+
+__device__ __forceinline__ void load_tile(MeshTile &T, const double *gxi, const double *geta, int n, int i0, int j0) {
+    for (int e = threadIdx.x; e < kTile * kTile; e += blockDim.x) {
+        const int tj = e / kTile, i = min(i0 + e - kTile * tj, n), j = min(j0 + tj, n);
+        const int64_t at = (int64_t)j * (n + 1) + i;
+        const int64_t ax = i < n ? at + 1 : at, ay = j < n ? at + (n + 1) : at;
+        T.d[e] = make_float4((float)(gxi[ax] - gxi[at]), (float)(geta[ax] - geta[at]), (float)(gxi[ay] - gxi[at]),
+                             (float)(geta[ay] - geta[at]));
+    }
+}
+
+// The gradient of both components at (x, y), bitwise table_gradient's.
+template <int CTL>
+__device__ __forceinline__ void mesh_gradient(const PathArgs &a, const MggArgs &c, const MeshTile *tile, int i0, int j0,
+                                              float x, float y, float (&g)[4]) {
+    const int n = a.grid_n;
+    if constexpr (CTL == CTL_TILE) {
+        const float fx = x * (float)n, fy = y * (float)n;
+        int i = (int)floorf(fx), j = (int)floorf(fy);
+        i = min(max(i, 0), n - 1);
+        j = min(max(j, 0), n - 1);
+        const uint32_t ti = (uint32_t)(i - i0), tj = (uint32_t)(j - j0);
+        if (max(ti, tj) < (uint32_t)(kTile - 1)) {
+            const float ax = fx - (float)i, ay = fy - (float)j;
+            const float4 *at = tile->d + (tj * kTile + ti);
+            const float4 d = at[0];
+            const float2 h = *reinterpret_cast<const float2 *>(at + kTile);
+            const float2 v = reinterpret_cast<const float2 *>(at + 1)[1];
+            g[0] = (float)n * fmaf(ay, h.x - d.x, d.x);
+            g[1] = (float)n * fmaf(ax, v.x - d.z, d.z);
+            g[2] = (float)n * fmaf(ay, h.y - d.y, d.y);
+            g[3] = (float)n * fmaf(ax, v.y - d.w, d.w);
+            return;
+        }
+    }
+    if (c.gtab) {
+        table_gradient(c.gtab, n, 0, x, y, g[0], g[1]);
+        table_gradient(c.gtab, n, 1, x, y, g[2], g[3]);
+    } else {
+        grid_gradient(a.grid_xi, n, x, y, g[0], g[1]);
+        grid_gradient(a.grid_eta, n, x, y, g[2], g[3]);
+    }
+}
+
+// One path per lane of the wavefront (has: the lane holds one), of node nd;
+// its moments are added to q, its steps to `steps`.
+template <int KIND, int TMODE, int CTL>
+__device__ __forceinline__ void short_paths(const PathArgs &a, const MggArgs &c, const ShortWave &S, const NodeDev &nd,
+                                            uint32_t out_row, uint32_t nid, float4 ofs, const MeshTile *tile, int i0,
+                                            int j0, uint32_t path, bool has, unsigned long long (&q)[4],
+                                            uint32_t &steps) {
     constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
+    constexpr bool MESH = CTL != CTL_NONE;
+    const int32_t K = S.K;
+    const uint32_t nlo = kM1 * nid;
+    const uint64_t rec = (uint64_t)out_row * a.n_paths + path;
+    NodeAcc *const accs[1] = {MESH ? c.acc_cv : a.acc};
+    const PhiloxPath pp = philox_path(path, nid, S.key0);
+    float xh = nd.x, xl = nd.xlo, yh = nd.y, yl = nd.ylo;
+    float g[4] = {0.f, 0.f, 0.f, 0.f}, dbx = 0.f, dby = 0.f, mx = 0.f, my = 0.f;
+    uint32_t blk_left = 0;   // pairs of steps to the next block boundary
+    bool alive = has;
+    int32_t k_end = K;       // steps the lane's path takes
+
+    auto new_block = [&]() {
+        mx = fmaf(g[0], dbx, fmaf(g[1], dby, mx));
+        my = fmaf(g[2], dbx, fmaf(g[3], dby, my));
+        dbx = dby = 0.f;
+        mesh_gradient<CTL>(a, c, tile, i0, j0, xh, yh, g);
+        if (c.gofs) {
+            g[0] += ofs.x;
+            g[1] += ofs.y;
+            g[2] += ofs.z;
+            g[3] += ofs.w;
+        }
+    };
+    // the density's centre offset at step k and at k + 1
+    auto centre = [&](int32_t k, float &ox, float &oy, float &ox2, float &oy2) {
+        ox = ox2 = S.L.ox;
+        oy = oy2 = S.L.oy;
+        if constexpr (kMovingBackward) {
+            const float rev = fmaf(-(float)k, S.drev, S.rev0);
+            const float cr = hw_cos_rev(rev), sr = hw_sin_rev(rev);
+            ox = S.L.dens.orbit_r * cr;
+            oy = S.L.dens.orbit_r * sr;
+            ox2 = S.L.dens.orbit_r * fmaf(cr, S.cos_d, sr * S.sin_d);
+            oy2 = S.L.dens.orbit_r * fmaf(sr, S.cos_d, -cr * S.sin_d);
+        }
+    };
+
+    // ---- while every path is inside: pairs of steps without a branch -------
+    // (the loop is the wavefront's: k is a scalar)
+    const uint64_t held = ballot(has);
+    int32_t k = 0;
+    for (; k + 2 < K; k += 2) {
+        const PhiloxOut r = philox4x32_10_wave((uint32_t)k >> 1, S.ctr3, nlo, pp, S.W, S.key0, S.key1);
+        if constexpr (MESH) {
+            if (blk_left == 0) {
+                blk_left = c.stride_iters;
+                new_block();
+            }
+            --blk_left;
+        }
+        float ox, oy, ox2, oy2, w1x, w1y, w2x, w2y;
+        centre(k, ox, oy, ox2, oy2);
+        float x1h = xh, x1l = xl, y1h = yh, y1l = yl;
+        em_move<KIND>(x1h, x1l, y1h, y1l, S.L.dens, r.r0, r.r1, ox, oy, S.dt, S.cbm, S.mask, w1x, w1y);
+        xh = x1h;
+        xl = x1l;
+        yh = y1h;
+        yl = y1l;
+        em_move<KIND>(xh, xl, yh, yl, S.L.dens, r.r2, r.r3, ox2, oy2, S.dt, S.cbm, S.mask, w2x, w2y);
+        const float d1x = dbx + w1x, d1y = dby + w1y;
+        if constexpr (MESH) {
+            dbx = d1x + w2x;
+            dby = d1y + w2y;
+        }
+        // as in pair_step: not all four coordinates in [0, 1)
+        uint32_t m = max(max(__float_as_uint(x1h), __float_as_uint(y1h)), __float_as_uint(xh));
+        m = max(m, __float_as_uint(yh));
+        if ((ballot(m >= 0x3f800000u) & held) != 0ull) {
+            const bool o1 = outside<KIND>(x1h, x1l, y1h, y1l) < 0, o2 = outside<KIND>(xh, xl, yh, yl) < 0;
+            if ((ballot(o1 || o2) & held) != 0ull) {
+                if (has && o1) {
+                    xh = x1h;
+                    xl = x1l;
+                    yh = y1h;
+                    yl = y1l;
+                    if constexpr (MESH) {
+                        dbx = d1x;
+                        dby = d1y;
+                    }
+                }
+                if (has && (o1 || o2)) {
+                    alive = false;
+                    k_end = step_number(k + 1) + (o1 ? 0 : 1);
+                }
+                k += 2;
+                break;
+            }
+        }
+    }
+    // ---- the last pair, and paths that wait for the others -----------------
+    float D = S.dt, cb = S.cbm;
+    for (; k < K && ballot(alive) != 0ull; k += 2) {
+        const PhiloxOut r = philox4x32_10_wave((uint32_t)k >> 1, S.ctr3, nlo, pp, S.W, S.key0, S.key1);
+        if constexpr (MESH) {
+            if (blk_left == 0) {
+                blk_left = c.stride_iters;
+                if (alive) new_block();
+            }
+            --blk_left;
+        }
+        float ox, oy, ox2, oy2;
+        centre(k, ox, oy, ox2, oy2);
+        if (k == K - 1) {
+            D = last_step(S.dt_last);
+            cb = last_step(S.cbm_last);
+        }
+        float wx, wy;
+        if (alive) {
+            const bool out = em_update<KIND>(xh, xl, yh, yl, S.L.dens, r.r0, r.r1, ox, oy, D, cb, S.mask, wx, wy) < 0;
+            if constexpr (MESH) {
+                dbx += wx;
+                dby += wy;
+            }
+            if (out) {
+                alive = false;
+                k_end = step_number(k + 1);
+            }
+        }
+        if (k + 1 >= K) break;
+        if (k + 1 == K - 1) {
+            D = last_step(S.dt_last);
+            cb = last_step(S.cbm_last);
+        }
+        if (alive) {
+            const bool out = em_update<KIND>(xh, xl, yh, yl, S.L.dens, r.r2, r.r3, ox2, oy2, D, cb, S.mask, wx, wy) < 0;
+            if constexpr (MESH) {
+                dbx += wx;
+                dby += wy;
+            }
+            if (out) {
+                alive = false;
+                k_end = step_number(k + 2);
+            }
+        }
+    }
+    if (!has) return;
+    const bool out = !alive;
+    // ---- score (eq. (7b)) ---------------------------------------------------
+    Lane E = S.L;
+    E.xh = xh;
+    E.xl = xl;
+    E.yh = yh;
+    E.yl = yl;
+    E.px = nd.x;
+    E.py = nd.y;
+    E.k = k_end;
+    E.K = K;
+    float v[2];
+    score_path(a, E, out, v[0], v[1]);
+    if constexpr (MESH) {
+        mx = fmaf(g[0], dbx, fmaf(g[1], dby, mx));
+        my = fmaf(g[2], dbx, fmaf(g[3], dby, my));
+        const float sx0 = a.shift ? nd.x : 0.f, sy0 = a.shift ? nd.y : 0.f;
+        v[0] = (v[0] + sx0) - mx;
+        v[1] = (v[1] + sy0) - my;
+        if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
+    } else {
+        if (a.scores) a.scores[rec] = make_float2(v[0], v[1]);
+    }
+    if (a.exit_step) a.exit_step[rec] = out ? k_end : -1;
+    steps += (uint32_t)k_end;
+    // (a comparison per value: false for NaN, which a maximum would drop)
+    if (fabsf(v[0]) < kLdsBound && fabsf(v[1]) < kLdsBound) {
+        q[0] += (unsigned long long)q1_small(v[0]);
+        q[1] += (unsigned long long)q2_small(v[0]);
+        q[2] += (unsigned long long)q1_small(v[1]);
+        q[3] += (unsigned long long)q2_small(v[1]);
+    } else {
+        acc_direct<2>(accs, out_row, v, fabsf(v[0]) < kGlobalBound && fabsf(v[1]) < kGlobalBound);
+    }
+}
+
+// A wavefront's sums into its node's: lane 2 v + h adds half h of sum v.
+__device__ __forceinline__ void short_sums(NodeAcc &A, const unsigned long long (&q)[4], uint32_t steps, uint32_t lane) {
+    unsigned long long add = 0ull;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const long long s = (long long)wave_sum(q[v]);
+        add = lane == 2u * v ? (unsigned long long)(s >> 24) : add;
+        add = lane == 2u * v + 1u ? (unsigned long long)(s & 0xffffffll) : add;
+    }
+    const unsigned long long st = wave_sum(steps);
+    add = lane == 8u ? st : add;
+    if (lane < 9u && add != 0ull) atomicAdd(lane == 8u ? &A.steps : &A.sum[lane >> 1][lane & 1u], add);
+}
+
+template <int KIND, int TMODE, int CTL>
+__global__ void __launch_bounds__(256, CTL == CTL_MESH ? 5 : 6) fk_short_path_kernel(const PathArgs a, const MggArgs c) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t total = a.masked ? __builtin_amdgcn_readfirstlane(a.queue[kCtrActive]) * a.cpn : a.total_chunks;
-    const uint32_t key0 = a.key0, key1 = a.key1;
-    NodeAcc *const acc = MESH ? c.acc_cv : a.acc;
-    NodeAcc *const accs[1] = {acc};
-
-    const LevelDev &lv = a.levels[0];
-    Lane L;
-    lane_level<KIND, TMODE>(L, lv);
-    const int32_t K = lv.K;
-    const uint32_t ctr3 = lv.ctr3;
-    const float dt = in_vgpr(L.dt), cbm = in_vgpr(L.cbm);
-    const float dt_last = in_vgpr(L.dt_last), cbm_last = in_vgpr(L.cbm_last);
-    const uint32_t fmask = in_vgpr(kUnitMask);
-    const float rev0 = in_vgpr(L.rev0), drev = in_vgpr(L.drev), cos_d = in_vgpr(L.cos_d), sin_d = in_vgpr(L.sin_d);
-    L.dens.amp = in_vgpr(L.dens.amp);
-    L.dens.nscale = in_vgpr(L.dens.nscale);
-    L.dens.a2s = in_vgpr(L.dens.a2s);
-    L.dens.cx = in_vgpr(L.dens.cx);
-    L.dens.cy = in_vgpr(L.dens.cy);
-    L.dens.orbit_r = in_vgpr(L.dens.orbit_r);
-    if constexpr (KIND == KIND_GRID) L.dens.fn = in_vgpr(L.dens.fn);
-    const PhiloxWave W = philox_wave(key0, key1);
-
+    NodeAcc *const acc = CTL != CTL_NONE ? c.acc_cv : a.acc;
+    const ShortWave S = short_wave<KIND, TMODE>(a);
     for (uint32_t ch = __builtin_amdgcn_readfirstlane(first_chunk()); ch < total; ch += waves) {
         uint32_t slot, next, end;
         chunk_cursor(a, total, ch, slot, next, end);
@@ -172,177 +443,91 @@ __global__ void __launch_bounds__(256, MESH ? 5 : 6) fk_short_path_kernel(const 
         const NodeDev nd = a.nodes[slot];
         if (!(nd.xlo == nd.xlo)) continue;         // not a node of the square (its results are NaN)
         const uint32_t out_row = __builtin_amdgcn_readfirstlane((uint32_t)nd.out);
-        const uint32_t nid = __builtin_amdgcn_readfirstlane(nd.nid), nlo = kM1 * nid;
-        const uint64_t rec0 = (uint64_t)out_row * a.n_paths;
+        const uint32_t nid = __builtin_amdgcn_readfirstlane(nd.nid);
         float4 ofs = make_float4(0.f, 0.f, 0.f, 0.f);
-        if constexpr (MESH) {
+        if constexpr (CTL != CTL_NONE) {
             if (c.gofs) ofs = c.gofs[out_row];
         }
         unsigned long long q[4] = {0ull, 0ull, 0ull, 0ull};
         uint32_t steps = 0;
-        for (uint32_t p0 = next; p0 < end; p0 += 64) {
-            const uint32_t path = p0 + lane;
-            const bool has = path < end;
-            const PhiloxPath pp = philox_path(path, nid, key0);
-            float xh = nd.x, xl = nd.xlo, yh = nd.y, yl = nd.ylo;
-            float D = dt, cb = cbm;
-            float gxx = 0.f, gxy = 0.f, gyx = 0.f, gyy = 0.f, dbx = 0.f, dby = 0.f, mx = 0.f, my = 0.f;
-            uint32_t blk_left = 0;   // iterations (2 steps each) to the next block boundary
-            bool alive = has;
-            int32_t k_end = K;       // steps the lane's path takes
-            // The loop is the wavefront's (k is a scalar): it ends at K, or
-            // with the last path that is still inside.
-            for (int32_t k = 0; k < K && ballot(alive) != 0ull; k += 2) {
-                const PhiloxOut r = philox4x32_10_wave((uint32_t)k >> 1, ctr3, nlo, pp, W, key0, key1);
-                if constexpr (MESH) {
-                    if (blk_left == 0) {
-                        blk_left = c.stride_iters;
-                        if (alive) {
-                            mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
-                            my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
-                            dbx = dby = 0.f;
-                            if (c.gtab) {
-                                table_gradient(c.gtab, a.grid_n, 0, xh, yh, gxx, gxy);
-                                table_gradient(c.gtab, a.grid_n, 1, xh, yh, gyx, gyy);
-                            } else {
-                                grid_gradient(a.grid_xi, a.grid_n, xh, yh, gxx, gxy);
-                                grid_gradient(a.grid_eta, a.grid_n, xh, yh, gyx, gyy);
-                            }
-                            if (c.gofs) {
-                                gxx += ofs.x;
-                                gxy += ofs.y;
-                                gyx += ofs.z;
-                                gyy += ofs.w;
-                            }
-                        }
-                    }
-                    --blk_left;
-                }
-                float ox = L.ox, oy = L.oy, cr = 0.f, sr = 0.f;
-                if constexpr (kMovingBackward) {
-                    const float rev = fmaf(-(float)k, drev, rev0);
-                    cr = hw_cos_rev(rev);
-                    sr = hw_sin_rev(rev);
-                    ox = L.dens.orbit_r * cr;
-                    oy = L.dens.orbit_r * sr;
-                }
-                if (k == K - 1) {
-                    D = last_step(dt_last);
-                    cb = last_step(cbm_last);
-                }
-                float wx, wy;
-                if (alive) {
-                    const bool out = em_update<KIND>(xh, xl, yh, yl, L.dens, r.r0, r.r1, ox, oy, D, cb, fmask, wx, wy) < 0;
-                    if constexpr (MESH) {
-                        dbx += wx;
-                        dby += wy;
-                    }
-                    if (out) {
-                        alive = false;
-                        k_end = step_number(k + 1);
-                    }
-                }
-                if (k + 1 >= K) break;
-                if constexpr (kMovingBackward) {
-                    const float c2 = fmaf(cr, cos_d, sr * sin_d);
-                    const float s2 = fmaf(sr, cos_d, -cr * sin_d);
-                    ox = L.dens.orbit_r * c2;
-                    oy = L.dens.orbit_r * s2;
-                }
-                if (k + 1 == K - 1) {
-                    D = last_step(dt_last);
-                    cb = last_step(cbm_last);
-                }
-                if (alive) {
-                    const bool out = em_update<KIND>(xh, xl, yh, yl, L.dens, r.r2, r.r3, ox, oy, D, cb, fmask, wx, wy) < 0;
-                    if constexpr (MESH) {
-                        dbx += wx;
-                        dby += wy;
-                    }
-                    if (out) {
-                        alive = false;
-                        k_end = step_number(k + 2);
-                    }
-                }
-            }
-            if (has) {
-                const bool out = !alive;
-                // ---- score (eq. (7b)) ---------------------------------------
-                Lane E = L;
-                E.xh = xh;
-                E.xl = xl;
-                E.yh = yh;
-                E.yl = yl;
-                E.px = nd.x;
-                E.py = nd.y;
-                E.k = k_end;
-                E.K = K;
-                float v[2];
-                score_path(a, E, out, v[0], v[1]);
-                if constexpr (MESH) {
-                    mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
-                    my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
-                    const float sx0 = a.shift ? nd.x : 0.f, sy0 = a.shift ? nd.y : 0.f;
-                    v[0] = (v[0] + sx0) - mx;
-                    v[1] = (v[1] + sy0) - my;
-                    if (c.cv_scores) c.cv_scores[rec0 + path] = make_float2(v[0], v[1]);
-                } else {
-                    if (a.scores) a.scores[rec0 + path] = make_float2(v[0], v[1]);
-                }
-                if (a.exit_step) a.exit_step[rec0 + path] = out ? k_end : -1;
-                steps += (uint32_t)k_end;
-                // (a comparison per value: false for NaN, which a maximum would drop)
-                if (fabsf(v[0]) < kLdsBound && fabsf(v[1]) < kLdsBound) {
-                    q[0] += (unsigned long long)q1_small(v[0]);
-                    q[1] += (unsigned long long)q2_small(v[0]);
-                    q[2] += (unsigned long long)q1_small(v[1]);
-                    q[3] += (unsigned long long)q2_small(v[1]);
-                } else {
-                    acc_direct<2>(accs, out_row, v, fabsf(v[0]) < kGlobalBound && fabsf(v[1]) < kGlobalBound);
-                }
-            }
-        }
-        // ---- the chunk's sums into its node's: lane 2 v + h adds half h of sum v ----
-        unsigned long long add = 0ull;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const long long s = (long long)wave_sum(q[v]);
-            add = lane == 2u * v ? (unsigned long long)(s >> 24) : add;
-            add = lane == 2u * v + 1u ? (unsigned long long)(s & 0xffffffll) : add;
-        }
-        const unsigned long long st = wave_sum(steps);
-        add = lane == 8u ? st : add;
-        if (lane < 9u && add != 0ull) {
-            NodeAcc &A = acc[out_row];
-            unsigned long long *at = lane == 8u ? &A.steps : &A.sum[lane >> 1][lane & 1u];
-            atomicAdd(at, add);
-        }
+        for (uint32_t p0 = next; p0 < end; p0 += 64)
+            short_paths<KIND, TMODE, CTL>(a, c, S, nd, out_row, nid, ofs, nullptr, 0, 0, p0 + lane, p0 + lane < end, q,
+                                          steps);
+        short_sums(acc[out_row], q, steps, lane);
+    }
+}
+
+// The mesh's gradient from LDS: a workgroup of 16 wavefronts (four per SIMD)
+// takes a chunk of one node's paths, with the kTile x kTile grid nodes around
+// the node in LDS (160 KB, the CU's whole); the rare path beyond them reads
+// memory.  From memory two 16-byte gathers per pair of steps take 123 cycles of the CU's
+// address unit each for 64 lanes on lines of their own, more than the four
+// SIMDs need for the steps.  Measured (two bumps frozen, N = 768, 10689 nodes
+// x 16384 paths x 20 steps, stride 2): 8.5 ms against 14.1 from memory; bound
+// by VALU issue as the plain kernel (5.8 ms), the gradient's arithmetic on
+// top.
+template <int KIND, int TMODE>
+__global__ void __launch_bounds__(1024) fk_short_tile_kernel(const PathArgs a, const MggArgs c) {
+    __shared__ MeshTile tile;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t total = a.masked ? __builtin_amdgcn_readfirstlane(a.queue[kCtrActive]) * a.cpn : a.total_chunks;
+    const ShortWave S = short_wave<KIND, TMODE>(a);
+    for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
+        uint32_t slot, next, end;
+        chunk_cursor(a, total, ch, slot, next, end);
+        slot = __builtin_amdgcn_readfirstlane(slot);
+        next = __builtin_amdgcn_readfirstlane(next);
+        end = __builtin_amdgcn_readfirstlane(end);
+        const NodeDev nd = a.nodes[slot];
+        if (!(nd.xlo == nd.xlo)) continue;         // (the whole workgroup)
+        const uint32_t out_row = __builtin_amdgcn_readfirstlane((uint32_t)nd.out);
+        const uint32_t nid = __builtin_amdgcn_readfirstlane(nd.nid);
+        float4 ofs = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c.gofs) ofs = c.gofs[out_row];
+        const int n = a.grid_n, far = max(n + 1 - kTile, 0);
+        const int i0 = __builtin_amdgcn_readfirstlane(min(max((int)(nd.x * (float)n) - kTile / 2, 0), far));
+        const int j0 = __builtin_amdgcn_readfirstlane(min(max((int)(nd.y * (float)n) - kTile / 2, 0), far));
+        __syncthreads();                           // the last chunk's readers
+        load_tile(tile, a.grid_xi, a.grid_eta, n, i0, j0);
+        __syncthreads();
+        unsigned long long q[4] = {0ull, 0ull, 0ull, 0ull};
+        uint32_t steps = 0;
+        for (uint32_t p0 = next + 64u * wave; p0 < end; p0 += 1024u)
+            short_paths<KIND, TMODE, CTL_TILE>(a, c, S, nd, out_row, nid, ofs, &tile, i0, j0, p0 + lane,
+                                               p0 + lane < end, q, steps);
+        short_sums(c.acc_cv[out_row], q, steps, lane);
     }
 }
 
 namespace {
-template <int K, int T, bool M>
+template <int K, int T, int C>
 struct ShortLaunchF {
     static hipError_t run(const PathArgs &a, const MggArgs &c, int grid, int block, hipStream_t s) {
-        hipLaunchKernelGGL((fk_short_path_kernel<K, T, M>), dim3(grid), dim3(block), 0, s, a, c);
+        if constexpr (C == CTL_TILE)
+            hipLaunchKernelGGL((fk_short_tile_kernel<K, T>), dim3(grid), dim3(1024), 0, s, a, c);
+        else
+            hipLaunchKernelGGL((fk_short_path_kernel<K, T, C>), dim3(grid), dim3(block), 0, s, a, c);
         return hipGetLastError();
     }
 };
-template <int K, int T, bool M>
+template <int K, int T, int C>
 struct ShortOccF {
     static int run(int block) {
         int nb = 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_short_path_kernel<K, T, M>, block, 0) == hipSuccess
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_short_path_kernel<K, T, C == CTL_NONE ? C : CTL_MESH>,
+                                                            block, 0) == hipSuccess
                    ? nb
                    : 0;
     }
 };
 
-template <template <int, int, bool> class F, typename... Args>
-auto short_dispatch(int kind, int time_mode, bool mesh, Args &&...args) {
+template <template <int, int, int> class F, typename... Args>
+auto short_dispatch(int kind, int time_mode, int ctl, Args &&...args) {
     const bool frozen = (time_mode == TIME_FROZEN);
-#define FK_SHORT(K, T) \
-    return mesh ? F<K, T, true>::run(std::forward<Args>(args)...) : F<K, T, false>::run(std::forward<Args>(args)...)
+#define FK_SHORT(K, T)                                                                  \
+    return ctl == CTL_TILE   ? F<K, T, CTL_TILE>::run(std::forward<Args>(args)...)      \
+           : ctl == CTL_MESH ? F<K, T, CTL_MESH>::run(std::forward<Args>(args)...)      \
+                             : F<K, T, CTL_NONE>::run(std::forward<Args>(args)...)
     switch (kind) {
     case KIND_CONST: FK_SHORT(KIND_CONST, TIME_BACKWARD);
     case KIND_BUMP: FK_SHORT(KIND_BUMP, TIME_BACKWARD);
@@ -360,15 +545,53 @@ auto short_dispatch(int kind, int time_mode, bool mesh, Args &&...args) {
     }
 #undef FK_SHORT
 }
+
+// A wavefront's sums of a chunk (1/16 of its paths) stay below 2^62.
+constexpr int64_t kMaxTileChunk = 32768;
+
+// Paths per chunk of the tile kernel, or 0 where it is not used: the paths
+// have to stay near the node, a chunk's gathers have to pay for loading its
+// tile, and the chunks have to fill the chip.  Measured from memory / from the
+// tile, in ms (two bumps, N = 768, 20 steps, stride 2 unless stated):
+//   2048 nodes x 8192 paths, Brownian standard deviation 12 cells 1.60 / 0.97,
+//   24: 2.66 / 1.02, 38: 2.99 / 1.06, 46: 3.06 / 1.24, 60: 3.06 / 1.52;
+//   stride 4: 1.66 / 0.86, 10: 0.92 / 0.81, 20 (one block): 0.70 / 0.79;
+//   1024 paths at 2048 nodes 0.39 / 0.26, at 512 0.116 / 0.105, at 128 (fewer
+//   chunks than CUs) 0.066 / 0.075, 2048 paths there 0.082 / 0.076.
+uint32_t tile_chunk(const PathArgs &a, const MggArgs &c, double t, int64_t K, int64_t n_nodes, int n_cu) {
+    const double n = a.grid_n;
+    if (n + 1 > kTile && std::sqrt(2.0 * t) * n > 0.6 * kTile) return 0;
+    const int64_t gathers = (K + 2 * (int64_t)c.stride_iters - 1) / (2 * (int64_t)c.stride_iters);   // of a path
+    if (gathers < 2) return 0;
+    const int64_t least = (kTile * kTile / gathers + 1023) / 1024 * 1024;      // paths that pay for a tile
+    const int64_t split = std::max<int64_t>(1, (8 * (int64_t)n_cu + n_nodes - 1) / n_nodes);
+    const int64_t chunk = std::min<int64_t>(
+        kMaxTileChunk, std::max(least, (((int64_t)a.n_paths + split - 1) / split + 1023) / 1024 * 1024));
+    const int64_t per_node = ((int64_t)a.n_paths + chunk - 1) / chunk;
+    if ((int64_t)a.n_paths < least || per_node * n_nodes < n_cu) return 0;
+    return (uint32_t)chunk;
+}
 }  // namespace
 
-hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, const MggArgs *mesh, int grid, int block,
-                              hipStream_t s) {
-    return short_dispatch<ShortLaunchF>(kind, time_mode, mesh != nullptr, a, mesh ? *mesh : MggArgs{}, grid, block, s);
+hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, int grid, int block, hipStream_t s) {
+    return short_dispatch<ShortLaunchF>(kind, time_mode, CTL_NONE, a, MggArgs{}, grid, block, s);
+}
+
+hipError_t launch_short_mesh_paths(int kind, int time_mode, const PathArgs &a, const MggArgs &c, double t, int64_t K,
+                                   int64_t n_nodes, int n_cu, int grid, int block, hipStream_t s) {
+    const uint32_t chunk = tile_chunk(a, c, t, K, n_nodes, n_cu);
+    if (chunk == 0) return short_dispatch<ShortLaunchF>(kind, time_mode, CTL_MESH, a, c, grid, block, s);
+    PathArgs b = a;
+    b.chunk = chunk;
+    b.cpn = (a.n_paths + chunk - 1) / chunk;
+    b.total_chunks = (uint32_t)(n_nodes * b.cpn);
+    b.tile_shift = 0;
+    return short_dispatch<ShortLaunchF>(kind, time_mode, CTL_TILE, b, c, (int)std::min<int64_t>(b.total_chunks, n_cu),
+                                        1024, s);
 }
 
 int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, int block) {
-    return short_dispatch<ShortOccF>(kind, time_mode, mesh, block);
+    return short_dispatch<ShortOccF>(kind, time_mode, mesh ? CTL_MESH : CTL_NONE, block);
 }
 
 }  // namespace fk

@@ -134,3 +134,42 @@ def test_mesh_gradient_form(oracle_mod, K, stride, n):
     ds = np.abs(got[0]["cv_scores"].astype(np.float64) - o["cv_scores"]).max(-1)
     assert np.mean(ds < 1e-6) >= 0.99 and ds.max() < 1e-3
     assert int(got[0]["total_steps"][0]) == np.where(o["exit_step"] < 0, K, o["exit_step"]).sum()
+
+
+@pytest.mark.parametrize("G,t,K,last,stride", [(24, 2e-3, 20, 1.0, 2), (99, 1e-3, 9, 0.4, 2), (100, 1e-3, 12, 1.0, 4),
+                                               (200, 0.012, 20, 1.0, 2), (768, 5e-4, 19, 0.7, 2)])
+def test_mesh_gradient_from_a_tile(G, t, K, last, stride):
+    """Many paths at many nodes read the mesh's gradient from LDS (the whole mesh, one that just fits, ones cut by the
+    tile, with paths that leave it), few paths from memory: the same paths have bitwise the same scores, and the
+    larger solve's sums are those of its scores."""
+    import torch
+
+    import paper_1402_0266_amd as fk
+    x = np.arange(G + 1) / G
+    X, Y = np.meshgrid(x, x)
+    gx = X + 0.02 * np.sin(np.pi * X) * np.sin(2 * np.pi * Y)
+    gy = Y + 0.015 * np.sin(2 * np.pi * X) * np.sin(np.pi * Y)
+    data = W.Data(init_kind=W.DATA_GRID, score_mode=W.SCORE_EXTEND, grid_xi=gx.ravel(), grid_eta=gy.ravel())
+    grids = (torch.tensor(gx.ravel(), device="cuda"), torch.tensor(gy.ravel(), device="cuda"))
+    pts = np.concatenate([W.uniform_points(592, seed=8, lo=0.0, hi=1.0),
+                          [(0.0, 0.0), (1.0, 1.0), (0.5, 1e-9), (1.0 - 1e-9, 0.5), (1.5, 0.5)]])
+    dt, n, few = t / (K - 1 + last), 17000, 96
+    mask = (np.arange(len(pts)) % 64 != 3).astype(np.uint8)
+    for dens in (W.two_bumps(W.TIME_FROZEN, 0.2), W.moving_bump()):
+        for m in (None, mask):
+            kw = dict(stride=stride, seed=9, plain=False, form=fk.FK_CV_MARTINGALE_GRID, grids=grids, cv_scores=True,
+                      exit_step=True, mask=m)
+            big = fk.fk_interface_solve_cv(dens, data, pts, t, dt, n, None, **kw)
+            small = fk.fk_interface_solve_cv(dens, data, pts, t, dt, few, None, **kw)
+            torch.cuda.synchronize()
+            on = np.ones(len(pts), bool) if m is None else m != 0
+            on[-1] = False
+            sel = torch.tensor(on, device="cuda")
+            assert torch.equal(big["cv_scores"][sel, :few], small["cv_scores"][sel])
+            assert torch.equal(big["exit_step"][sel, :few], small["exit_step"][sel])
+            es = big["exit_step"][sel]
+            assert int(big["total_steps"][0]) == int(torch.where(es < 0, K, es).sum())
+            # fixed-point sums: 2^-49 per score
+            mean = big["cv_scores"][sel].double().mean(1)
+            assert (big["xi"][sel] - mean[:, 0]).abs().max() < 1e-12
+            assert (big["eta"][sel] - mean[:, 1]).abs().max() < 1e-12
