@@ -1158,15 +1158,22 @@ __global__ void __launch_bounds__(256) cv_node_kernel(const CvNodeArgs na, const
 // ---------------------------------------------------------------------------
 // Training: per-tile forward + backward on MFMA, then Adam.
 // ---------------------------------------------------------------------------
-constexpr int kTS = 65;  // LDS row stride (floats) of the 64 x 64 activation tiles
+constexpr int kTS = 65;  // LDS row stride (floats) of the 64 x 64 tiles that are summed in FP32
 
+// Operands of the tile's products: BF16, rows of 64 in an operand's order
+// (wcol), so that a lane's eight elements are one 16-byte read.  By sample and
+// by unit, as the product sums over units or samples.
+typedef uint16_t TrainTile[64 * kWS];
 struct TrainLds {
     NetLds net;
+    alignas(16) TrainTile w2t, w3t;      // transposed weights
+    TrainTile H1s, H1u, H2s, H2u;        // [sample][unit], [unit][sample]
+    TrainTile D2u, D2s;                  // d loss / d (layer 2 pre-activations); layer 3's: in H1s, H2s
     float z[3][64];
     float y[2][64];
     float dout[2][64];
     float valid[64];
-    float H1[64 * kTS], H2[64 * kTS], H3[64 * kTS];
+    float H3[64 * kTS];
     float D[64 * kTS], E[64 * kTS];
     float red[2];
 };
@@ -1202,28 +1209,30 @@ struct TrainArgs {
     float *partial;        // [tiles][kNP + 1]
 };
 
-// C[M = 64][N = 64] = A[64 x K] B[K x 64] with K = 64, A and B given by
-// element accessors, on MFMA (two 32-deep K blocks); each of the workgroup's
-// 16 wavefronts computes a 16 x 16 tile and hands its result fragment to
-// `sink(row, col, value)`.
-template <typename FA, typename FB, typename FS>
-__device__ __forceinline__ void wave_gemm64(FA A, FB B, FS sink) {
-    const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15, w = threadIdx.x >> 6;
-    const int mt = w >> 2, nt = w & 3;
+// The wavefront's 16 x 16 tile (mt, nt) of C = A B^T for operand tiles A, B
+// (rows of C, columns of C): element i is C[16 mt + 4 g + i][16 nt + n].
+__device__ __forceinline__ fk_f4 wave_gemm64(const uint16_t *A, const uint16_t *B, int mt, int nt, int n, int g) {
     fk_f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        fk_b8 a, b;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = ku(kb, g, j);
-            a[j] = (__bf16)A(16 * mt + n, k);
-            b[j] = (__bf16)B(k, 16 * nt + n);
-        }
-        acc = mfma32(a, b, acc);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sink(16 * mt + 4 * g + i, 16 * nt + n, acc[i]);
+    for (int kb = 0; kb < 2; ++kb) acc = mfma32(load_a(A, mt, kb, n, g), load_a(B, nt, kb, n, g), acc);
+    return acc;
+}
+
+// A 16 x 16 tile's elements (units 16 mt + 4 g + 0..3 of sample 16 nt + n) as
+// operands by sample and by unit.
+__device__ __forceinline__ void put_tile(uint16_t *by_sample, uint16_t *by_unit, const float (&v)[4], int mt, int nt,
+                                         int n, int g) {
+    ushort4 b;
+    b.x = __builtin_bit_cast(uint16_t, (__bf16)v[0]);
+    b.y = __builtin_bit_cast(uint16_t, (__bf16)v[1]);
+    b.z = __builtin_bit_cast(uint16_t, (__bf16)v[2]);
+    b.w = __builtin_bit_cast(uint16_t, (__bf16)v[3]);
+    *reinterpret_cast<ushort4 *>(by_sample + (16 * nt + n) * kWS + wcol(16 * mt + 4 * g)) = b;
+    uint16_t *u = by_unit + (16 * mt + 4 * g) * kWS + wcol(16 * nt + n);
+    u[0] = b.x;
+    u[kWS] = b.y;
+    u[2 * kWS] = b.z;
+    u[3 * kWS] = b.w;
 }
 
 // Bias corrections of Adam step `step` (>= 1), in FP64 then rounded.
@@ -1234,8 +1243,13 @@ __device__ __forceinline__ void adam_corrections(int64_t step, float &c1, float 
 
 // One 64-sample tile per workgroup of 16 wavefronts: a step's 128 tiles leave
 // half the chip idle whatever a workgroup's size, so what counts is the chain
-// of its phases -- with a 16 x 16 product tile and four activations a thread
-// in each they take ~9 us; with four wavefronts, 22 us.
+// of its phases, each a 16 x 16 product tile and four activations a thread.
+// A thread keeps its elements of H1 .. H3 in registers, and what the products
+// read is in LDS in their operands' order, so a product is four 16-byte reads
+// and two matrix instructions.  12.7 us a launch (the start of a graph node
+// included); with FP32 tiles read and converted element by element 15.2, on
+// four wavefronts 22.  What is left is the samples' load (two dependent
+// gathers), twelve tanhf a thread and the sums in sample order.
 constexpr int kGradThreads = 1024;
 
 __global__ void __launch_bounds__(kGradThreads) cv_grad_kernel(TrainArgs ta) {
@@ -1284,21 +1298,46 @@ __global__ void __launch_bounds__(kGradThreads) cv_grad_kernel(TrainArgs ta) {
         }
     } else {
         load_net(S.net, ta.bf, tid, kGradThreads - 64);
+        for (int i = 4 * tid; i < 4096; i += 4 * (kGradThreads - 64)) {
+            const int at = (i & 63) * kWS + wcol(i >> 6);
+            const ushort4 a = *reinterpret_cast<const ushort4 *>(ta.bf + OW2 + i);
+            const ushort4 b = *reinterpret_cast<const ushort4 *>(ta.bf + OW3 + i);
+            S.w2t[at] = a.x;
+            S.w2t[at + kWS] = a.y;
+            S.w2t[at + 2 * kWS] = a.z;
+            S.w2t[at + 3 * kWS] = a.w;
+            S.w3t[at] = b.x;
+            S.w3t[at + kWS] = b.y;
+            S.w3t[at + 2 * kWS] = b.z;
+            S.w3t[at + 3 * kWS] = b.w;
+        }
     }
     __syncthreads();
     // ---- forward ------------------------------------------------------------------
-    for (int e = tid; e < 4096; e += kGradThreads) {
-        const int u = e >> 6, s = e & 63;
-        const float a = fmaf(S.net.w1[3 * u], S.z[0][s],
-                             fmaf(S.net.w1[3 * u + 1], S.z[1][s], fmaf(S.net.w1[3 * u + 2], S.z[2][s], S.net.b1[u])));
-        S.H1[u * kTS + s] = tanhf(a);
+    // (a thread's elements of every 64 x 64 tile: units u0 .. u0 + 3 of sample sm)
+    const int lane = tid & 63, g = lane >> 4, n = lane & 15, mt = tid >> 8, nt = (tid >> 6) & 3;
+    const int u0 = 16 * mt + 4 * g, sm = 16 * nt + n;
+    float h1[4], h2[4], h3[4], dv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int u = u0 + i;
+        const float a = fmaf(S.net.w1[3 * u], S.z[0][sm],
+                             fmaf(S.net.w1[3 * u + 1], S.z[1][sm], fmaf(S.net.w1[3 * u + 2], S.z[2][sm], S.net.b1[u])));
+        h1[i] = tanhf(a);
     }
+    put_tile(S.H1s, S.H1u, h1, mt, nt, n, g);
     __syncthreads();
-    wave_gemm64([&](int m, int k) { return bf2f(S.net.w2[m * kWS + wcol(k)]); }, [&](int k, int n) { return S.H1[k * kTS + n]; },
-                [&](int m, int n, float v) { S.H2[m * kTS + n] = tanhf(v + S.net.b2[m]); });
+    fk_f4 c = wave_gemm64(S.net.w2, S.H1s, mt, nt, n, g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h2[i] = tanhf(c[i] + S.net.b2[u0 + i]);
+    put_tile(S.H2s, S.H2u, h2, mt, nt, n, g);
     __syncthreads();
-    wave_gemm64([&](int m, int k) { return bf2f(S.net.w3[m * kWS + wcol(k)]); }, [&](int k, int n) { return S.H2[k * kTS + n]; },
-                [&](int m, int n, float v) { S.H3[m * kTS + n] = tanhf(v + S.net.b3[m]); });
+    c = wave_gemm64(S.net.w3, S.H2s, mt, nt, n, g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h3[i] = tanhf(c[i] + S.net.b3[u0 + i]);
+        S.H3[(u0 + i) * kTS + sm] = h3[i];
+    }
     __syncthreads();
     // outputs, residuals, d loss / d out (mean over batch and both outputs), and
     // the tile's loss
@@ -1333,15 +1372,18 @@ __global__ void __launch_bounds__(kGradThreads) cv_grad_kernel(TrainArgs ta) {
         P[OB4 + o] = acc;
     }
     // dA3 = (W4^T dout) (1 - H3^2)
-    for (int e = tid; e < 4096; e += kGradThreads) {
-        const int u = e >> 6, s = e & 63;
-        const float h = S.H3[u * kTS + s];
-        S.D[u * kTS + s] = fmaf(S.net.w4[u], S.dout[0][s], S.net.w4[64 + u] * S.dout[1][s]) * (1.f - h * h);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int u = u0 + i;
+        dv[i] = fmaf(S.net.w4[u], S.dout[0][sm], S.net.w4[64 + u] * S.dout[1][sm]) * (1.f - h3[i] * h3[i]);
+        S.D[u * kTS + sm] = dv[i];
     }
+    put_tile(S.H2s, S.H1s, dv, mt, nt, n, g);
     __syncthreads();
     // dW3 = dA3 H2^T, db3
-    wave_gemm64([&](int m, int k) { return S.D[m * kTS + k]; }, [&](int k, int n) { return S.H2[n * kTS + k]; },
-                [&](int m, int n, float v) { P[OW3 + 64 * m + n] = v; });
+    c = wave_gemm64(S.H1s, S.H2u, mt, nt, n, g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) P[OW3 + 64 * (u0 + i) + sm] = c[i];
     if (tid < 64) {
         float acc = 0.f;
 #pragma unroll 16
@@ -1349,15 +1391,18 @@ __global__ void __launch_bounds__(kGradThreads) cv_grad_kernel(TrainArgs ta) {
         P[OB3 + tid] = acc;
     }
     // dA2 = (W3^T dA3) (1 - H2^2)
-    wave_gemm64([&](int m, int k) { return bf2f(S.net.w3[k * kWS + wcol(m)]); }, [&](int k, int n) { return S.D[k * kTS + n]; },
-                [&](int m, int n, float v) {
-                    const float h = S.H2[m * kTS + n];
-                    S.E[m * kTS + n] = v * (1.f - h * h);
-                });
+    c = wave_gemm64(S.w3t, S.H2s, mt, nt, n, g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        dv[i] = c[i] * (1.f - h2[i] * h2[i]);
+        S.E[(u0 + i) * kTS + sm] = dv[i];
+    }
+    put_tile(S.D2s, S.D2u, dv, mt, nt, n, g);
     __syncthreads();
     // dW2 = dA2 H1^T, db2
-    wave_gemm64([&](int m, int k) { return S.E[m * kTS + k]; }, [&](int k, int n) { return S.H1[n * kTS + k]; },
-                [&](int m, int n, float v) { P[OW2 + 64 * m + n] = v; });
+    c = wave_gemm64(S.D2u, S.H1u, mt, nt, n, g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) P[OW2 + 64 * (u0 + i) + sm] = c[i];
     if (tid < 64) {
         float acc = 0.f;
 #pragma unroll 16
@@ -1365,11 +1410,9 @@ __global__ void __launch_bounds__(kGradThreads) cv_grad_kernel(TrainArgs ta) {
         P[OB2 + tid] = acc;
     }
     // dA1 = (W2^T dA2) (1 - H1^2)
-    wave_gemm64([&](int m, int k) { return bf2f(S.net.w2[k * kWS + wcol(m)]); }, [&](int k, int n) { return S.E[k * kTS + n]; },
-                [&](int m, int n, float v) {
-                    const float h = S.H1[m * kTS + n];
-                    S.D[m * kTS + n] = v * (1.f - h * h);
-                });
+    c = wave_gemm64(S.w2t, S.D2s, mt, nt, n, g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S.D[(u0 + i) * kTS + sm] = c[i] * (1.f - h1[i] * h1[i]);
     __syncthreads();
     // dW1 = dA1 Z^T, db1
     if (tid < 192) {
