@@ -747,31 +747,6 @@ __global__ void grad_table_kernel(const double *gxi, const double *geta, int n, 
     }
 }
 
-// One Euler-Maruyama step with its Brownian part (wx, wy); with BRIDGE the
-// Brownian-bridge exit test of the step follows (FK_SCORE_BRIDGE), on the
-// same counters as in the plain kernel.  The step's Brownian part counts in
-// full toward the block it ends: the test sees only this step.
-template <int KIND, bool UNIFORM, bool BRIDGE>
-__device__ __forceinline__ bool cv_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, float &wx, float &wy,
-                                        uint32_t key0, uint32_t key1) {
-    SideDist d0{};
-    if constexpr (BRIDGE) d0 = side_dist(L);
-    bool out = em_step_w<KIND, UNIFORM>(L, ra, rb, ox, oy, wx, wy);
-    if constexpr (BRIDGE) {
-        if (!out) {
-            const int32_t k = L.k - 1;
-            int side;
-            const float p = bridge_prob(d0, side_dist(L), 1.f / (!UNIFORM && k == L.K - 1 ? L.dt_last : L.dt), side);
-            if (side >= 0) {
-                const PhiloxOut r = philox4x32_10((uint32_t)k >> 1, L.path, L.nid, L.ctr3 | 4u, key0, key1);
-                out = bridge_uniform((k & 1) ? r.r1 : r.r0) < p;
-                if (out) move_to_side(L, side);
-            }
-        }
-    }
-    return out;
-}
-
 // Martingale-form path kernel.  The score is g - sum_j G_j . dB_j: dB_j is the
 // Brownian part of the path's steps in block j, G_j the gradient of u_hat at
 // the block's first state.  Blocks start at the path's start (G_0 from the
@@ -973,11 +948,15 @@ __global__ void __launch_bounds__(256, SPLIT ? 2 : 3) fk_mg_path_kernel(const Pa
 // bilinear interpolant of (grid_xi, grid_eta) at its position, and the score
 // is g - sum_j G_j . dB_j.  No network: lanes need no common evaluation
 // points, so they start new paths at once, and each path's blocks sit at
-// fixed offsets from its start (schedule-independent results).
+// fixed offsets from its start (schedule-independent results).  Step pairs
+// without a branch, as in the other path kernels; four waves per SIMD (106
+// registers; at five it spills and runs 2-10% slower).  Measured (moving bump,
+// 1521 nodes x 512 paths, the identity's gradient, stride 2 / 100 / once per
+// path): 9.5 / 8.2 / 7.4 ms against 13.0 / 10.8 / 10.4 with a branch after
+// each step, with the bridge test 13.4 / 12.0 / 11.5 against 18.0 / 16.0 / 15.2.
 
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE>
 __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, const MggArgs c) {
-    constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
     const uint32_t lane = threadIdx.x & 63u;
     __shared__ AccSlot<2> slot_tab[4][kAccSlots];
     AccSlot<2> *slots = slot_tab[threadIdx.x >> 6];
@@ -987,22 +966,21 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
     const uint32_t total_chunks = launch_chunks(a);
     bool q_done = !grab_chunk<2>(a, total_chunks, first_chunk(), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane);
     const uint32_t key0 = a.key0, key1 = a.key1;
+    const PhiloxKeys keys = philox_keys(key0, key1);
+    const uint32_t mask = in_vgpr(kUnitMask);
     Lane L;
-    bool active = false;
+    PairLane P{};
     float gxx = 0.f, gxy = 0.f, gyx = 0.f, gyy = 0.f;
     float dbx = 0.f, dby = 0.f, mx = 0.f, my = 0.f;
-    uint32_t blk_left = 0;       // iterations (2 steps each) to the path's next block boundary
+    int32_t next_block = -1;     // the pair before which the path's next block opens
     uint32_t my_tag = 0;         // accumulation tag of the path's chunk
     uint32_t my_steps = 0;
+    uint64_t act = 0;            // lanes with a path
+    lane_level<KIND, TMODE>(L, a.levels[0]);
+    pair_idle<BRIDGE>(L, P);
 
-    bool closed = false;         // the lane's last path closed its chunk's slot
     for (;;) {
-        if (ballot(closed) != 0ull) {
-            slots_collect<2>(slots, accs, lane);
-            closed = false;
-        }
-        uint64_t need = ballot(!active);
-        while (need != 0ull && !q_done) {
+        while (~act != 0ull && !q_done) {
             if (q_next >= q_end) {
                 if (!grab_chunk<2>(a, total_chunks, next_chunk(a), q_slot, q_next, q_end, slots, accs, q_tag, grabs, lane)) {
                     q_done = true;
@@ -1010,28 +988,33 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
                 }
                 continue;
             }
+            const uint64_t need = ~act;
             const uint32_t avail = q_end - q_next;
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
-            if (!active && rank < avail) {
+            const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
+            if (take) {
                 lane_start<KIND, TMODE>(L, a.nodes[q_slot], a.levels, q_next + rank);
+                pair_start<BRIDGE>(L, P, key0, key1);
                 my_tag = q_tag;
                 dbx = dby = mx = my = 0.f;
-                blk_left = 0;
-                active = true;
+                next_block = 0;
             }
+            act |= ballot(take);
             q_next += min((uint32_t)__popcll(need), avail);
-            need = ballot(!active);
         }
-        if (ballot(active) == 0ull) break;
+        if (act == 0ull) break;
 
-        if (active) {
-            bool out = false;
-            if (L.k < L.K) {
-                if (blk_left == 0) {
-                    // block boundary (L.k a multiple of the stride): close the
+        // ---- step pairs, until a path ends ---------------------------------
+        Pair p;
+        float d1x, d1y;              // the block's Brownian part after the pair's first step
+        uint64_t fin;
+        do {
+            if (ballot(P.half == next_block) != 0ull) {
+                if (P.half == next_block) {
+                    // block boundary (a multiple of the stride): close the
                     // block, take the gradient here
-                    blk_left = c.stride_iters;
+                    next_block += (int32_t)c.stride_iters;
                     mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
                     my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
                     dbx = dby = 0.f;
@@ -1050,49 +1033,41 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
                         gyy += o.w;
                     }
                 }
-                --blk_left;
-                const PhiloxOut r = philox4x32_10((uint32_t)L.k >> 1, L.path, L.nid, L.ctr3, key0, key1);
-                float ox = L.ox, oy = L.oy, cr = 0.f, sr = 0.f;
-                if constexpr (kMovingBackward) {
-                    const float rev = fmaf(-(float)L.k, L.drev, L.rev0);
-                    cr = hw_cos_rev(rev);
-                    sr = hw_sin_rev(rev);
-                    ox = L.dens.orbit_r * cr;
-                    oy = L.dens.orbit_r * sr;
-                }
-                float wx, wy;
-                out = cv_step<KIND, UNIFORM, BRIDGE>(L, r.r0, r.r1, ox, oy, wx, wy, key0, key1);
-                dbx += wx;
-                dby += wy;
-                my_steps += 1;
-                if (!out && L.k < L.K) {
-                    if constexpr (kMovingBackward) {
-                        const float c2 = fmaf(cr, L.cos_d, sr * L.sin_d);
-                        const float s2 = fmaf(sr, L.cos_d, -cr * L.sin_d);
-                        ox = L.dens.orbit_r * c2;
-                        oy = L.dens.orbit_r * s2;
-                    }
-                    out = cv_step<KIND, UNIFORM, BRIDGE>(L, r.r2, r.r3, ox, oy, wx, wy, key0, key1);
-                    dbx += wx;
-                    dby += wy;
-                    my_steps += 1;
-                }
             }
-            if (out || L.k >= L.K) {
-                float plx, ply;
-                score_path(a, L, out, plx, ply);
-                mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
-                my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
-                const float sx0 = a.shift ? L.px : 0.f, sy0 = a.shift ? L.py : 0.f;
-                const float v[2] = {(plx + sx0) - mx, (ply + sy0) - my};
-                closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
-                const uint64_t rec = path_rec(L, a.n_paths);
-                if (a.scores) a.scores[rec] = make_float2(plx, ply);
-                if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
-                if (a.exit_step) a.exit_step[rec] = out ? L.k : -1;
-                active = false;
+            const bool may = pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p);
+            d1x = dbx + p.w1x;
+            d1y = dby + p.w1y;
+            dbx = d1x + p.w2x;
+            dby = d1y + p.w2y;
+            fin = ballot(may) & act;
+        } while (fin == 0ull);
+        const int with = pair_ends<KIND>(L, P, p);
+        fin &= ballot(with != 0);
+        bool closed = false;         // the lane's path closed its chunk's slot
+        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+            if (with == 1) {
+                dbx = d1x;
+                dby = d1y;
             }
+            if (L.K <= 0) dbx = dby = 0.f;
+            const bool out = pair_end<KIND, BRIDGE>(L, P, p, with);
+            float plx, ply;
+            score_path(a, L, out, plx, ply);
+            mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
+            my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
+            const float sx0 = a.shift ? L.px : 0.f, sy0 = a.shift ? L.py : 0.f;
+            const float v[2] = {(plx + sx0) - mx, (ply + sy0) - my};
+            closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
+            my_steps += (uint32_t)L.k;
+            const uint64_t rec = path_rec(L, a.n_paths);
+            if (a.scores) a.scores[rec] = make_float2(plx, ply);
+            if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
+            if (a.exit_step) a.exit_step[rec] = out ? L.k : -1;
+            pair_idle<BRIDGE>(L, P);
+            next_block = -1;
         }
+        act &= ~fin;
+        if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);
     }
     slots_collect<2>(slots, accs, lane);
     unsigned long long st = my_steps;

@@ -79,27 +79,6 @@ __device__ __forceinline__ int32_t em_update(float &xh, float &xl, float &yh, fl
     return outside<KIND>(xh, xl, yh, yl);
 }
 
-// The lane's step L.k (see em_update).  UNIFORM: every step has length dt
-// (t/dt integral), so the last-step selection is compiled out.
-template <int KIND, bool UNIFORM>
-__device__ __forceinline__ bool em_step_w(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, float &dwx,
-                                          float &dwy, uint32_t m = kUnitMask) {
-    float D = L.dt, cb = L.cbm;
-    if constexpr (!UNIFORM) {
-        const bool last = (L.k == L.K - 1);
-        D = last ? L.dt_last : D;
-        cb = last ? L.cbm_last : cb;
-    }
-    L.k += 1;
-    return em_update<KIND>(L.xh, L.xl, L.yh, L.yl, L.dens, ra, rb, ox, oy, D, cb, m, dwx, dwy) < 0;
-}
-
-template <int KIND, bool UNIFORM>
-__device__ __forceinline__ bool em_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, uint32_t m = kUnitMask) {
-    float dwx, dwy;
-    return em_step_w<KIND, UNIFORM>(L, ra, rb, ox, oy, dwx, dwy, m);
-}
-
 // Distances of the lane's position to the sides 0 (x = 0), 1 (x = 1),
 // 2 (y = 0) and 3 (y = 1).
 struct SideDist {

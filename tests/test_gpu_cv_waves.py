@@ -45,3 +45,37 @@ def test_scores_do_not_depend_on_the_launch(fk, form, precision, score, K, last,
             assert np.array_equal(g["cv_scores"], full["cv_scores"][:, :n]), (n, plan)
             assert np.array_equal(g["exit_step"], full["exit_step"][:, :n]), (n, plan)
     cv.close()
+
+
+@pytest.mark.parametrize("score", [W.SCORE_EXTEND, W.SCORE_BRIDGE])
+@pytest.mark.parametrize("K,last,stride", [(65, 1.0, 2), (100, 0.3, 10), (101, 1.0, 1 << 20)])
+def test_mesh_control_scores_do_not_depend_on_the_launch(fk, score, K, last, stride):
+    """The same for the mesh's gradient over longer horizons, whose lanes start their paths at once."""
+    import torch
+    G = 20
+    x = np.arange(G + 1) / G
+    X, Y = np.meshgrid(x, x)
+    gx = (X + 0.02 * np.sin(np.pi * X) * np.sin(2 * np.pi * Y)).ravel()
+    gy = (Y + 0.015 * np.sin(2 * np.pi * X) * np.sin(np.pi * Y)).ravel()
+    grids = (torch.tensor(gx, device="cuda"), torch.tensor(gy, device="cuda"))
+    bdry = W.DATA_GRID if score == W.SCORE_BRIDGE else W.DATA_IDENTITY
+    data = W.Data(init_kind=W.DATA_GRID, bdry_kind=bdry, score_mode=score, grid_xi=gx, grid_eta=gy)
+    pts = np.concatenate([W.uniform_points(5, seed=2, lo=0.05, hi=0.95), [(0.01, 0.5), (1.0, 1.0), (0.0, 0.2)]])
+    t = 0.1
+    dt = t / (K - 1 + last)
+
+    def run(n, plan=None):
+        g = fk.fk_interface_solve_cv(W.moving_bump(), data, pts, t, dt, n, None, stride=stride, seed=4, plain=False,
+                                     form=fk.FK_CV_MARTINGALE_GRID, grids=grids, cv_scores=True, exit_step=True,
+                                     plan=plan)
+        torch.cuda.synchronize()
+        return {k: v.cpu().numpy() for k, v in g.items() if not k.startswith("_")}
+
+    full = run(130)
+    assert np.isfinite(full["cv_scores"]).all()
+    assert int(full["total_steps"][0]) == np.where(full["exit_step"] < 0, K, full["exit_step"]).sum()
+    for n in (2, 17, 64, 65):
+        for plan in (None, {"chunk": 1}, {"chunk": 7, "block": 64}):
+            g = run(n, plan)
+            assert np.array_equal(g["cv_scores"], full["cv_scores"][:, :n]), (n, plan)
+            assert np.array_equal(g["exit_step"], full["exit_step"][:, :n]), (n, plan)
