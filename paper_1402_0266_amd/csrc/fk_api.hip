@@ -279,6 +279,21 @@ int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
     return 256;
 }
 
+// Resident workgroups per CU of the refilling path kernel by default (0: all
+// that fit, 5 or 6 of 256 threads).  Three or four wavefronts per SIMD come
+// close to its issue rate, and the fewer paths are under way, the less is left
+// to run after the queue is empty, which weighs more the longer and the fewer
+// the paths.  Moving bump, 1521 nodes, 6 / 4 / 3 per CU in ms: at most 10^4 steps,
+// 4096 paths (16 to a lane at six) 37.4 / 36.1 / 35.4, 1024 paths 13.1 / 11.7 /
+// 10.9, with the bridge test 19.1 / 18.6 / 17.5, 73920 paths (286 to a lane) 599 /
+// - / 618; 2000 steps 8.30 / 8.02 / 8.05; 500 steps 2.58 / 2.60 / 2.80; 200 steps
+// 1.33 / 1.40 / 1.53.  16 levels of up to 1600 steps 3.94 / 3.85 / 3.98, up to
+// 500 steps 1.63 / 1.66 / 1.83.
+static int long_blocks(int64_t steps, double paths_per_lane, int block) {
+    if (steps < 1000 || paths_per_lane > 32.0) return 0;
+    return std::max(1, (steps < 4000 ? 4 : 3) * 256 / block);
+}
+
 // Fixed steps with the discrete exit test, at most 64 of them, and not so
 // long a horizon that lanes whose paths have left wait for most of it.  Both
 // kernels on 1521 nodes x 4096 paths of two bumps (refilling / lockstep, us):
@@ -377,6 +392,9 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
                                : path_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.uniform,
                                                                a.score_mode == FK_SCORE_BRIDGE, S.first_by_index,
                                                                S.plan.block);
+    if (bpc == 0 && !S.lockstep && !expo)
+        bpc = long_blocks(S.steps, (double)S.n_nodes * (double)S.n_paths / ((double)n_cu * occ * S.plan.block + 1.0),
+                          S.plan.block);
     if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
     const int grid = cap_grid(n_cu * bpc, a.total_chunks, S.plan.block);
     if ((e = timing_mark(timed, 0, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -546,6 +564,7 @@ int fk_interface_solve(const fk_density *w, const fk_data *d, const double *pts,
     // which cuts the wavefronts' fixed costs per path.  Otherwise 128, for
     // the balance of the tail.
     S.lockstep = lockstep_paths(level.K, t, d->score_mode);
+    S.steps = level.K;
     S.first_by_index = !S.lockstep && level.K <= 64 && d->score_mode != FK_SCORE_EXPONENTIAL;
     if ((!plan || plan->chunk == 0) && (S.lockstep || S.first_by_index)) {
         int n_cu = 0;

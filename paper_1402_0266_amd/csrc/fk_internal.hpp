@@ -166,6 +166,7 @@ struct SolveLaunch {
     bool uniform;
     bool first_by_index;  // few steps: each wavefront's first chunk by its grid index
     bool lockstep;        // short horizons: the kernel of fk_short.hip (lockstep_paths)
+    int64_t steps;        // most steps a path takes
     const TableArgs *tables;  // device-built tables (filled in by enqueue_solve), or nullptr: host tables
     fk_plan plan;
     int64_t n_nodes, n_paths;

@@ -251,13 +251,14 @@ hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_ste
 // registers, 15 of them Philox round keys): with the keys in scalar registers
 // eight fit, and run 2% slower; forced to 72 or 64 registers the kernel
 // spills.  Measured (moving bump, 1521 nodes x 4096 paths x <= 10^4 steps):
-// 37.5 ms, 117 VALU instructions and ~410 issue cycles a pair, against
+// 35.5 ms, 117 VALU instructions and ~410 issue cycles a pair, against
 // 41.1 ms of the form with a branch after each step; with the bridge test
-// (125 nodes x 16384 paths to their exits) 4.8 ms against 6.9, of which the
+// (125 nodes x 16384 paths to their exits) 4.6 ms against 6.9, of which the
 // one Philox call for the uniforms of both steps and a position that stays
 // in registers are the larger part.  A wavefront alone on its SIMD takes 1050
 // cycles a pair, 2.2 ms for 10^4 steps; while the wavefronts thin out after
-// the queue has run empty ~5 ms pass.
+// the queue has run empty ~5 ms pass at six per SIMD and half that at three
+// (the default there: long_blocks, fk_api.hip).
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FIRST_BY_INDEX = false>
 __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
     const uint32_t lane = threadIdx.x & 63u;
