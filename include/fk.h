@@ -134,7 +134,8 @@ typedef struct fk_data {
 } fk_data;
 
 /* Launch plan of the path kernel (see fk_plan_autotune).  Zero fields take defaults:
- * block 256; blocks_per_cu the kernel's occupancy (the grid is cut to no more
+ * block 256; blocks_per_cu the kernel's occupancy, or less where
+ * paths of many steps are few to a lane (the grid is cut to no more
  * wavefronts than there are chunks); chunk 128, or for horizons of at most 32
  * steps (64 if t <= 0.05) in fk_interface_solve and the mesh-gradient form of
  * fk_interface_solve_cv 64 r paths for the r that finishes first on a grid of

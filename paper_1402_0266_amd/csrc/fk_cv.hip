@@ -777,8 +777,8 @@ struct MgArgs {
 // Three waves per SIMD (163 VGPRs) with the BF16 gradient, two (201) with the
 // hi + lo split, as many as fit without spilling: with one more the pairs
 // reload what the evaluation displaced (10.0 -> 11.0 ms and 9.9 -> 10.8).
-// Measured (moving bump, 1521 nodes x 696 paths, stride 500, BF16): 10.0 ms
-// against 13.9 with a branch after each step at four waves; at stride 20
+// Measured (moving bump, 1521 nodes x 696 paths, stride 500, BF16): 9.6 ms (by
+// default two workgroups per CU there) against 13.9 with a branch after each step at four waves; at stride 20
 // (173 paths) 10.7 against 19.5, of which the evaluation's rounds are most,
 // and with the split 13 against 23.
 template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool SPLIT>
@@ -2116,6 +2116,8 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     float2 *cv_rec = (float2 *)cv_scores;
     NodeAcc *acc_cv = (NodeAcc *)(ws + lay.acc_cv);
     int bpc = pl.blocks_per_cu;
+    // paths to a resident lane at `occ` workgroups per CU
+    const auto per_lane = [&](int occ) { return (double)n_nodes * (double)n_paths / (256.0 * n_cu * std::max(occ, 1)); };
     if (!mg) {
         CvArgs c{};
         c.bf = cv->s.bf;
@@ -2139,6 +2141,11 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         if (e != hipSuccess) return hip_fail(e, "gradient table kernel launch");
         const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, true, 256)
                                  : cv_dispatch<MggOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE);
+        // Fewer workgroups than fit over long horizons, as for the plain kernel
+        // (long_blocks).  The identity's gradient, 10^4 steps, 1521 nodes, 2 / 3 / 4
+        // per CU in ms: 256 paths (1.5 to a lane at four) 4.16 / 4.71 / 5.08, 512
+        // paths 6.51 / 6.92 / 7.28, 2952 paths (17) 29.0 / 27.5 / 28.3.
+        if (bpc == 0 && !lockstep && level.K >= 4000) bpc = per_lane(occ) <= 8.0 ? 2 : 3;
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
         const int grid = cap_grid(n_cu * bpc, a.total_chunks, 256);
         a.masked = mask ? 1u : 0u;
@@ -2160,6 +2167,11 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         c.split = cv->grad_bf16 ? 0 : 1;
         const int occ = cv_dispatch<MgOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE,
                                             c.split != 0);
+        // The same for the BF16 gradient (the split form has two), where steps,
+        // not evaluations, are most of the work: 2 / 3 per CU in ms, stride 100, 173
+        // paths (1.3 to a lane at three) 4.76 / 5.38; stride 500, 696 paths 9.55 /
+        // 10.12, 2952 paths (23) 33.9 / 32.6; stride 20, 696 paths 28.2 / 26.4.
+        if (bpc == 0 && level.K >= 4000 && stride >= 100 && per_lane(occ) <= 10.0) bpc = 2;
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
         if ((e = cv_dispatch<MgLaunchF>(w->kind, w->time_mode, uniform, a, c, cap_grid(n_cu * bpc, a.total_chunks, 256), stream)) != hipSuccess)
             return hip_fail(e, "control-variate path kernel launch");
