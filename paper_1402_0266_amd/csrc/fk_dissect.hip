@@ -440,7 +440,7 @@ bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t) {
         int most = 0;
         for (int i = 0; i < n; ++i) most = std::max(most, cur[i].w * cur[i].h);
         const bool leaf = most <= nd_leaf(blocks);
-        int s = 0, b = 0;
+        int s = 0, b = 0, f = 0;
         for (int i = 0; i < n; ++i) {
             const Kind &k = cur[i];
             const int p = leaf ? k.w * k.h : std::min(k.w, k.h), p2 = (p + 1) & ~1;
@@ -448,10 +448,12 @@ bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t) {
             if (p2 + r > kNdMaxFront) return false;
             s = std::max(s, p2);
             b = std::max(b, r);
+            f = std::max(f, p2 + r);
         }
         NdLevel &lv = t->lv[l];
         lv.s = s;
         lv.b = b;
+        lv.f = f;
         lv.ldw = b + 2;
         lv.lds = b + 2;
         const int64_t boxes = blocks << l;
@@ -511,14 +513,9 @@ static hipError_t nd_launch(int ln, int T, const NdTree &t, const NdArgs &a, uns
 hipError_t nd_solve(const NdTree &t, const NdArgs &a, int blocks, hipStream_t s) {
     hipError_t e;
     for (int l = t.depth; l >= 0; --l) {
-        const int f = t.lv[l].s + t.lv[l].b;
+        const int f = t.lv[l].f;
         const int64_t fronts = (int64_t)blocks << l;
-        // many small fronts: a wavefront each (the work per lane outweighs the
-        // pivots' fixed cost); else 256 lanes, which take a pair of pivots
-        // sooner than 1024 do (every wavefront repeats the pivots'
-        // reciprocals; 95 pivots: 40 us against 43, 47 in a front of 142: 47
-        // against 49) as long as the tile fits their registers
-        const int ln = fronts > 256 && f <= 64 ? 8 : f <= 144 ? 16 : 32;
+        const int ln = nd_lanes(fronts, f);
         if ((e = nd_launch(ln, (f + ln - 1) / ln, t, a, (unsigned)fronts, l, s)) != hipSuccess) return e;
     }
     // down: the upper levels by one workgroup per sub-domain, the boxes

@@ -8,11 +8,12 @@
 namespace fk {
 
 constexpr int kNdMaxLevels = 20;
-constexpr int kNdMaxFront = 192;   // 16 x 16 lanes of 12 x 12 register tiles
+constexpr int kNdMaxFront = 192;   // 32 x 32 lanes of 6 x 6 register tiles
 
 // One level of the tree: the boxes of depth l.
 struct NdLevel {
-    int s, b;            // most pivots (even) and boundary unknowns of a box
+    int s, b;            // most pivots (even) and boundary unknowns of a box (not always the same box)
+    int f;               // most of both together: the largest front
     int ldw, lds;        // row strides of the kept rows and of the Schur complements
     int64_t w_off;       // kept rows (W, y) of the level, in doubles
 };
@@ -34,6 +35,13 @@ struct NdArgs {
     double c, diag;
     int N, px, mx, my;   // grid cells a side; sub-domains in a row; cells of a sub-domain
 };
+
+// Lanes a side of a front's workgroup.  Many small fronts: a wavefront each
+// (the work per lane outweighs the pivots' fixed cost); else 256 lanes, which
+// take a pair of pivots sooner than 1024 do (every wavefront repeats the
+// pivots' reciprocals; 95 pivots: 40 us against 43, 47 in a front of 142: 47
+// against 49) as long as the tile fits their registers.
+inline int nd_lanes(int64_t fronts, int f) { return fronts > 256 && f <= 64 ? 8 : f <= 144 ? 16 : 32; }
 
 // The tree of a qx x qy grid of unknowns in each of `blocks` sub-domains;
 // false where a front would be larger than kNdMaxFront.

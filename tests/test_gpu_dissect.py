@@ -90,3 +90,16 @@ def test_steady_against_long_step(fk, px, py, N):
     torch.cuda.synchronize()
     # |u - u_D| <= |u^n - u| / (D lambda_min), lambda_min > 2, plus rounding (condition number ~ N^2)
     assert max((s[0] - b[0]).abs().max(), (s[1] - b[1]).abs().max()) < 1e-9
+
+
+@pytest.mark.parametrize("px,py,N", [(3, 1, 213), (1, 3, 213), (2, 1, 154)])
+def test_largest_pivots_and_rim_in_different_boxes(fk, px, py, N):
+    """Trees with a level whose most pivots and most lines around a box add up to more than any front of it holds
+    (70 x 212: 54 + 140; 76 x 153 does not)."""
+    import torch
+    dens = W.Density(W.KIND_BUMP, amp=2.0, width2=0.04, cx=0.4, cy=0.6)
+    xi0, eta0, ix, iy = _problem(px, py, N)
+    g = fk.subdomain_solve_rect(dens, 0.0, 1e-3, px, py, N, _cuda(xi0), _cuda(eta0), _cuda(ix), _cuda(iy))
+    torch.cuda.synchronize()
+    ox, oy = S.subdomain_be_step_rect(dens, 0.0, 1e-3, px, py, N, xi0, eta0, ix, iy)
+    assert max(np.abs(g[0].cpu().numpy() - ox).max(), np.abs(g[1].cpu().numpy() - oy).max()) < 1e-12
