@@ -423,7 +423,17 @@ __global__ void __launch_bounds__(512) nd_down_kernel(const NdArgs a, const NdTr
     }
 }
 
+// Work-items of a launch: 2^32 and more are refused.
+constexpr int64_t kMaxItems = ((int64_t)1 << 32) - 1;
+// The way down: the levels from 1 to 3 (all of them, of at most five) by one
+// workgroup of 512 for each box of level 1, those from kDownCut on by one for
+// each box of that level.
+constexpr int kDownCut = 4, kDownOne = 5;
+
 bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t) {
+    // unknowns are packed as x | y << 16 in an int; nd_assemble_kernel
+    // (fk_subdomain.hip) takes a work-item for each
+    if (qx > 32767 || qy > 32767 || blocks > kMaxItems || (int64_t)qx * qy * blocks > kMaxItems - 255) return false;
     // the distinct boxes of a level: sizes and which sides have lines around them
     struct Kind {
         int w, h;
@@ -457,6 +467,8 @@ bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t) {
         lv.ldw = b + 2;
         lv.lds = b + 2;
         const int64_t boxes = blocks << l;
+        const int lanes = nd_lanes(boxes, f);
+        if (boxes * lanes * lanes > kMaxItems) return false;
         lv.w_off = w_off;
         w_off += l > 0 ? boxes * s * lv.ldw : 0;
         s_size[l] = (int64_t)b * lv.lds;
@@ -484,6 +496,7 @@ bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t) {
         n = m;
         std::copy(nxt, nxt + m, cur);
     }
+    if (t->depth > 0 && (blocks << (t->depth <= kDownOne ? 1 : kDownCut)) * 512 > kMaxItems) return false;
     // a box's Schur complement takes the place of its children's
     t->s_off = w_off;
     t->s_leaf = 0;
@@ -518,15 +531,13 @@ hipError_t nd_solve(const NdTree &t, const NdArgs &a, int blocks, hipStream_t s)
         const int ln = nd_lanes(fronts, f);
         if ((e = nd_launch(ln, (f + ln - 1) / ln, t, a, (unsigned)fronts, l, s)) != hipSuccess) return e;
     }
-    // down: the upper levels by one workgroup per sub-domain, the boxes
-    // below them one workgroup each
-    const int cut = std::min(t.depth, 4);
     if (t.depth > 0) {
-        const int mid = t.depth <= 5 ? t.depth : cut - 1;
+        const int mid = t.depth <= kDownOne ? t.depth : kDownCut - 1;
         hipLaunchKernelGGL(nd_down_kernel, dim3((unsigned)blocks << 1), dim3(512), 0, s, a, t, 1, mid);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (mid < t.depth) {
-            hipLaunchKernelGGL(nd_down_kernel, dim3((unsigned)blocks << cut), dim3(512), 0, s, a, t, cut, t.depth);
+            hipLaunchKernelGGL(nd_down_kernel, dim3((unsigned)blocks << kDownCut), dim3(512), 0, s, a, t, kDownCut,
+                               t.depth);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }

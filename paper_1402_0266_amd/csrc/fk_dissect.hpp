@@ -44,7 +44,8 @@ struct NdArgs {
 inline int nd_lanes(int64_t fronts, int f) { return fronts > 256 && f <= 64 ? 8 : f <= 144 ? 16 : 32; }
 
 // The tree of a qx x qy grid of unknowns in each of `blocks` sub-domains;
-// false where a front would be larger than kNdMaxFront.
+// false where a front would be larger than kNdMaxFront, a launch would have
+// 2^32 work-items, or a side has 32768 unknowns.
 bool nd_tree(int qx, int qy, int64_t blocks, NdTree *t);
 // Factorises and solves every sub-domain (Dirichlet data in the output grids,
 // cf and rh assembled): interior values of xi_out, eta_out.

@@ -26,7 +26,7 @@ static bool compiled(int lanes, int tile) {
 static bool check(const NdTree &t, int64_t qx, int64_t qy, int64_t blocks) {
     const int64_t limit = (int64_t)1 << 32;
     bool ok = qx < 32768 && qy < 32768 && blocks * qx * qy < limit - 256;
-    ok = ok && (t.depth == 0 || ((blocks << 1) * 512 < limit && (blocks << std::min(t.depth, 4)) * 512 < limit));
+    ok = ok && (t.depth == 0 || (blocks << (t.depth <= 5 ? 1 : 4)) * 512 < limit);
     std::set<Box> boxes{Box{(int)qx, (int)qy, 0, 0, 0, 0}};
     for (int l = 0; l <= t.depth; ++l) {
         const NdLevel &lv = t.lv[l];

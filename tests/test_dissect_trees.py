@@ -48,3 +48,23 @@ def test_every_accepted_tree_can_be_launched(trees, blocks):
     bad = r[r[:, 4] == 0]
     assert len(bad) == 0, bad[:8]
     assert (r[:, 3] == 1).sum() > 10000 and r[r[:, 3] == 1, 6].max() == 192
+
+
+# (cells a side, sub-domains in x and y, cells of a sub-domain) of large grids: leaves, boxes of level 1 or unknowns
+# by the 2^32, and strips with more than 2^15 unknowns a side.
+LARGE = [(27456, 8, 11), (16384, 8, 8), (16380, 9, 10), (24576, 12, 12), (65535, 3, 5), (32768, 4, 32768),
+         (32768, 32768, 4), (40000, 4, 40000), (32767, 31, 32767)]
+
+
+@pytest.mark.parametrize("N,mx,my", LARGE)
+def test_large_grids(trees, N, mx, my):
+    """Accepted only with every launch below 2^32 work-items and unknowns that pack (others take the banded LU)."""
+    blocks = (N // mx) * (N // my)
+    r = trees([(mx - 1, my - 1, blocks), (my - 1, mx - 1, blocks)])
+    assert (r[:, 4] == 1).all(), r
+
+
+def test_large_grids_that_fit_are_accepted(trees):
+    # 8191^2 sub-domains' leaves of 64 work-items; 2^15 - 1 unknowns in a strip
+    r = trees([(3, 3, 8191 * 4096), (3, 32767, 128), (7, 7, 2 ** 21)])
+    assert (r[:, 3] == 1).all() and (r[:, 4] == 1).all(), r
