@@ -176,14 +176,17 @@ __device__ __forceinline__ void acc_direct(NodeAcc *const *acc, uint32_t out, co
 template <int NV>
 __device__ __forceinline__ bool acc_path(AccSlot<NV> *slots, NodeAcc *const *acc, uint32_t tag, uint32_t out,
                                          const float (&v)[NV], uint32_t steps) {
-    float amax = 0.f;
+    // a comparison per value: false for NaN, which a maximum would drop
+    bool small = true, finite = true;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    const bool finite = amax < kGlobalBound;      // false for NaN and infinities too
+    for (int i = 0; i < NV; ++i) {
+        small = small && fabsf(v[i]) < kLdsBound;
+        finite = finite && fabsf(v[i]) < kGlobalBound;
+    }
     AccSlot<NV> &S = slots[tag & (uint32_t)(kAccSlots - 1)];
     lds_order();
     const bool mine = tag != kNoSlot && S.tag == tag;
-    const bool in_lds = mine && amax < kLdsBound;
+    const bool in_lds = mine && small;
     if (in_lds) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
