@@ -226,7 +226,7 @@ int build_tables(const LevelSpec *lv, int n_levels, const double *pts, int64_t n
         const int l = level_of[(size_t)g];
         NodeDev &nd = T.nodes[(size_t)s];
         // Start point as an FP32 (hi, lo) pair holding the FP64 node to ~2^-48.
-        nd.x = (float)pts[2 * g] + 0.f;   // + 0: no -0 (the path kernels' exit test)
+        nd.x = (float)pts[2 * g] + 0.f;   // + 0: no -0, whose sign bit the path kernels would look at
         nd.y = (float)pts[2 * g + 1] + 0.f;
         nd.xlo = (float)(pts[2 * g] - (double)nd.x);
         nd.ylo = (float)(pts[2 * g + 1] - (double)nd.y);

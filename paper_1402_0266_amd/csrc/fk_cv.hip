@@ -705,12 +705,12 @@ __global__ void __launch_bounds__(256, 2) fk_cv_path_kernel(const PathArgs a, co
             --until_eval;
         } while (fin == 0ull && until_eval != 0);
         if (fin == 0ull) continue;
-        const int with = pair_ends<KIND>(L, P, p);
+        const int with = pair_ends(L, P, p);
         fin &= ballot(with != 0);
         if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
             // the last interval is closed at the next evaluation point, where
             // u_hat and the integrand at the end state are known
-            out = pair_end<KIND, false>(L, P, p, with);
+            out = pair_end<false>(L, P, p, with);
             score_path(a, L, out, plx, ply);
             my_steps += (uint32_t)L.k;
             ex = L.xh;
@@ -909,7 +909,7 @@ __global__ void __launch_bounds__(256, SPLIT ? 2 : 3) fk_mg_path_kernel(const Pa
             --until_eval;
         } while (fin == 0ull && until_eval != 0);
         if (fin == 0ull) continue;
-        const int with = pair_ends<KIND>(L, P, p);
+        const int with = pair_ends(L, P, p);
         fin &= ballot(with != 0);
         bool closed = false;     // the lane's path closed its chunk's slot
         if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
@@ -918,7 +918,7 @@ __global__ void __launch_bounds__(256, SPLIT ? 2 : 3) fk_mg_path_kernel(const Pa
                 dby = d1y;
             }
             if (L.K <= 0) dbx = dby = 0.f;
-            const bool out = pair_end<KIND, BRIDGE>(L, P, p, with);
+            const bool out = pair_end<BRIDGE>(L, P, p, with);
             float plx, ply;
             score_path(a, L, out, plx, ply);
             mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
@@ -1041,7 +1041,7 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
             dby = d1y + p.w2y;
             fin = ballot(may) & act;
         } while (fin == 0ull);
-        const int with = pair_ends<KIND>(L, P, p);
+        const int with = pair_ends(L, P, p);
         fin &= ballot(with != 0);
         bool closed = false;         // the lane's path closed its chunk's slot
         if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
@@ -1050,7 +1050,7 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
                 dby = d1y;
             }
             if (L.K <= 0) dbx = dby = 0.f;
-            const bool out = pair_end<KIND, BRIDGE>(L, P, p, with);
+            const bool out = pair_end<BRIDGE>(L, P, p, with);
             float plx, ply;
             score_path(a, L, out, plx, ply);
             mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));

@@ -162,7 +162,7 @@ __global__ void table_scatter_kernel(const TableArgs t) {
     if (!take) return;
     NodeDev nd{};
     // the start point as an FP32 (hi, lo) pair holding the FP64 node to ~2^-48
-    nd.x = (float)x + 0.f;   // + 0: no -0 (the path kernels' exit test)
+    nd.x = (float)x + 0.f;   // + 0: no -0, whose sign bit the path kernels would look at
     nd.y = (float)y + 0.f;
     nd.xlo = (float)(x - (double)nd.x);
     nd.ylo = (float)(y - (double)nd.y);
@@ -217,7 +217,7 @@ __global__ void short_table_kernel(const TableArgs t, unsigned long long *total_
     if (t.mask) slot = wave_bucket_add(t.counters + kCtrActive, take, 0);
     if (!take) return;
     NodeDev nd{};
-    nd.x = ok ? (float)x + 0.f : 0.5f;   // + 0: no -0 (the kernel's exit test)
+    nd.x = ok ? (float)x + 0.f : 0.5f;   // + 0: no -0, whose sign bit the kernel would look at
     nd.y = ok ? (float)y + 0.f : 0.5f;
     nd.xlo = ok ? (float)(x - (double)nd.x) : __builtin_nanf("");
     nd.ylo = ok ? (float)(y - (double)nd.y) : 0.f;
@@ -339,11 +339,11 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
         } while (fin == 0ull);
 
         // ---- score (eq. (7b)) and the node's sums ------------------------------
-        const int with = pair_ends<KIND>(L, P, p);
+        const int with = pair_ends(L, P, p);
         fin &= ballot(with != 0);
         bool closed = false;      // the lane's path closed its chunk's slot
         if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
-            const bool out = pair_end<KIND, BRIDGE>(L, P, p, with);
+            const bool out = pair_end<BRIDGE>(L, P, p, with);
             float v[2];
             score_path(a, L, out, v[0], v[1]);
             closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);

@@ -41,19 +41,14 @@ __device__ __forceinline__ void comp_add(float &hi, float &lo, float inc) {
     hi = s;
 }
 
-// Negative if the point is outside the closed unit square: x, y, 1 - x or
-// 1 - y negative.  hi is the rounded position; (1 - hi) is exact near 1, so
-// the tests against 1 see the lo part too.  No value is -0 (a sum that cancels
-// is +0, and the start points hold no -0), so the sign bits decide: two bit
-// operations and a compare instead of a minimum, a three-way maximum and a
-// compare.  A grid density's drift may be NaN, which is never outside.
-template <int KIND>
-__device__ __forceinline__ int32_t outside(float xh, float xl, float yh, float yl) {
-    const float x1 = (1.f - xh) - xl, y1 = (1.f - yh) - yl;
-    if constexpr (KIND == KIND_GRID) return fminf(fminf(xh, yh), fminf(x1, y1)) < 0.f ? -1 : 0;
-    uint32_t s;
-    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xfe" : "=v"(s) : "v"(xh), "v"(yh), "v"(x1));
-    return (int32_t)(s | __float_as_uint(y1));
+// Outside the closed unit square: -x, -y, x - 1 or y - 1 positive.  hi is the
+// rounded position; (hi - 1) is exact near 1, so the tests against 1 see the
+// lo part too.  The maximum drops NaN: a position that is not a number (a
+// grid density's drift, or an analytic one's beyond FP32's range) is outside
+// only where its other coordinate is.  (The sign bits of x, y, 1 - x and 1 - y
+// take two cheaper instructions, but a NaN has a sign bit too.)
+__device__ __forceinline__ bool outside(float xh, float xl, float yh, float yl) {
+    return fmaxf(fmaxf(-xh, -yh), fmaxf((xh - 1.f) + xl, (yh - 1.f) + yl)) > 0.f;
 }
 
 // One Euler-Maruyama step of length D (cb = -4 ln2 D) of the position with
@@ -68,15 +63,6 @@ __device__ __forceinline__ void em_move(float &xh, float &xl, float &yh, float &
     drift<KIND>(dens, ox, oy, xh, yh, bx, by);
     comp_add(xh, xl, fmaf(bx, D, dwx));
     comp_add(yh, yl, fmaf(by, D, dwy));
-}
-
-// em_move, and its outcome (outside).
-template <int KIND>
-__device__ __forceinline__ int32_t em_update(float &xh, float &xl, float &yh, float &yl, const DensityRegs &dens,
-                                             uint32_t ra, uint32_t rb, float ox, float oy, float D, float cb,
-                                             uint32_t m, float &dwx, float &dwy) {
-    em_move<KIND>(xh, xl, yh, yl, dens, ra, rb, ox, oy, D, cb, m, dwx, dwy);
-    return outside<KIND>(xh, xl, yh, yl);
 }
 
 // Distances of the lane's position to the sides 0 (x = 0), 1 (x = 1),
@@ -277,7 +263,7 @@ __device__ __forceinline__ void lane_level(Lane &L, const LevelDev &lv) {
 template <int KIND, int TMODE>
 __device__ __forceinline__ void lane_start(Lane &L, const NodeDev &nd, const LevelDev *levels, uint32_t path) {
     L.path = path;
-    L.xh = nd.x;   // not -0 (em_update's exit test)
+    L.xh = nd.x;
     L.yh = nd.y;
     L.xl = nd.xlo;
     L.yl = nd.ylo;
@@ -410,16 +396,15 @@ __device__ __forceinline__ bool pair_step(Lane &L, PairLane &P, const PhiloxKeys
 
 // How a path ends in the pair just taken: not (0), with its first step (1) or
 // with its second one (2).
-template <int KIND>
 __device__ __forceinline__ int pair_ends(const Lane &L, const PairLane &P, const Pair &p) {
     const int32_t k0 = 2 * P.half - 2;
-    if (outside<KIND>(p.xh, p.xl, p.yh, p.yl) < 0 || p.side1 >= 0 || k0 + 1 >= L.K) return 1;
-    return outside<KIND>(L.xh, L.xl, L.yh, L.yl) < 0 || p.side2 >= 0 || k0 + 2 >= L.K ? 2 : 0;
+    if (outside(p.xh, p.xl, p.yh, p.yl) || p.side1 >= 0 || k0 + 1 >= L.K) return 1;
+    return outside(L.xh, L.xl, L.yh, L.yl) || p.side2 >= 0 || k0 + 2 >= L.K ? 2 : 0;
 }
 
 // The end state of a path that ended with step `with` of the pair: its
 // position, its steps in L.k; true if it left the square.
-template <int KIND, bool BRIDGE>
+template <bool BRIDGE>
 __device__ __forceinline__ bool pair_end(Lane &L, const PairLane &P, const Pair &p, int with) {
     const bool first = with == 1;
     if (first) {
@@ -428,7 +413,7 @@ __device__ __forceinline__ bool pair_end(Lane &L, const PairLane &P, const Pair 
         L.yh = p.yh;
         L.yl = p.yl;
     }
-    const bool cross = outside<KIND>(L.xh, L.xl, L.yh, L.yl) < 0;
+    const bool cross = outside(L.xh, L.xl, L.yh, L.yl);
     const int side = first ? p.side1 : p.side2;
     const bool out = L.K > 0 && (cross || side >= 0);
     if (L.K <= 0) {

@@ -309,7 +309,7 @@ __device__ __forceinline__ void short_paths(const PathArgs &a, const MggArgs &c,
         uint32_t m = max(max(__float_as_uint(x1h), __float_as_uint(y1h)), __float_as_uint(xh));
         m = max(m, __float_as_uint(yh));
         if ((ballot(m >= 0x3f800000u) & held) != 0ull) {
-            const bool o1 = outside<KIND>(x1h, x1l, y1h, y1l) < 0, o2 = outside<KIND>(xh, xl, yh, yl) < 0;
+            const bool o1 = outside(x1h, x1l, y1h, y1l), o2 = outside(xh, xl, yh, yl);
             if ((ballot(o1 || o2) & held) != 0ull) {
                 if (has && o1) {
                     xh = x1h;
@@ -349,12 +349,12 @@ __device__ __forceinline__ void short_paths(const PathArgs &a, const MggArgs &c,
         }
         float wx, wy;
         if (alive) {
-            const bool out = em_update<KIND>(xh, xl, yh, yl, S.L.dens, r.r0, r.r1, ox, oy, D, cb, S.mask, wx, wy) < 0;
+            em_move<KIND>(xh, xl, yh, yl, S.L.dens, r.r0, r.r1, ox, oy, D, cb, S.mask, wx, wy);
             if constexpr (MESH) {
                 dbx += wx;
                 dby += wy;
             }
-            if (out) {
+            if (outside(xh, xl, yh, yl)) {
                 alive = false;
                 k_end = step_number(k + 1);
             }
@@ -365,12 +365,12 @@ __device__ __forceinline__ void short_paths(const PathArgs &a, const MggArgs &c,
             cb = last_step(S.cbm_last);
         }
         if (alive) {
-            const bool out = em_update<KIND>(xh, xl, yh, yl, S.L.dens, r.r2, r.r3, ox2, oy2, D, cb, S.mask, wx, wy) < 0;
+            em_move<KIND>(xh, xl, yh, yl, S.L.dens, r.r2, r.r3, ox2, oy2, D, cb, S.mask, wx, wy);
             if constexpr (MESH) {
                 dbx += wx;
                 dby += wy;
             }
-            if (out) {
+            if (outside(xh, xl, yh, yl)) {
                 alive = false;
                 k_end = step_number(k + 2);
             }

@@ -79,3 +79,38 @@ def test_grid_density(fk, K, value):
     _check(g, g["scores"])
     spoilt = ~np.isfinite(g["scores"].cpu().numpy()).all(-1)
     assert spoilt.any() and (g["exit_step"].cpu().numpy()[spoilt] == -1).all()
+
+
+DEGENERATE = {
+    # w = 0 at the centre in FP32, and beyond FP32's range: the drift is 0 / 0, 0 inf or inf there
+    "zero": W.Density(W.KIND_BUMP, amp=-1 + 1e-10, width2=0.01, cx=0.5, cy=0.5),
+    "narrow": W.Density(W.KIND_BUMP, amp=1.0, width2=1e-42, cx=0.5, cy=0.5),
+    "steep": W.Density(W.KIND_BUMP, amp=1e38, width2=1e-3, cx=0.5, cy=0.5),
+    "moving": W.Density(W.KIND_MOVING_BUMP, amp=1e38, width2=1e-3, cx=0.5, cy=0.5, orbit_r=0.25, omega=6.25),
+    "two": W.Density(W.KIND_TWO_BUMPS, amp=-0.5, width2=0.01, cx=0.5, cy=0.5),
+    "ridge": W.Density(W.KIND_RIDGE, amp=1e38, width2=1e-3, cx=0.5),
+}
+
+
+@pytest.mark.parametrize("name", sorted(DEGENERATE))
+@pytest.mark.parametrize("K,t", [(20, 1e-3), (48, 1e-2), (100, 1e-2), (1200, 1e-2)])
+def test_degenerate_analytic_density(fk, name, K, t):
+    """A position that is not a number is not an exit (its path runs to the horizon and scores the initial data
+    there): the nodes it reaches get NaN, also with boundary data 0."""
+    import torch
+    data = W.Data(bdry_kind=W.DATA_ZERO)
+    pts = np.array([(0.5, 0.5), (0.5, 0.7), (0.01, 0.5), (0.75, 0.5)])
+    g = fk.fk_interface_solve(DEGENERATE[name], data, pts, t, t / K, 200, seed=3, scores=True, exit_step=True)
+    b = fk.FkBatch([(DEGENERATE[name], t, 0.0, pts, 0)], data, t / K, 200, seed=3)
+    r = b.run(scores=True, exit_step=True)
+    torch.cuda.synchronize()
+    s, e = g["scores"].cpu().numpy(), g["exit_step"].cpu().numpy()
+    # the centre: NaN in both coordinates at the first step
+    if name in ("zero", "two", "narrow"):
+        assert np.isnan(s[0]).all() and (e[0] == -1).all()
+    bad = ~np.isfinite(s).all(axis=(1, 2))
+    assert np.array_equal(np.isnan(g["xi"].cpu().numpy()), bad) and bad.any()
+    assert (s[e >= 0] == 0.0).all()
+    for k in ("xi", "eta", "se_xi", "se_eta", "scores", "exit_step", "total_steps"):
+        assert np.array_equal(g[k].cpu().numpy(), r[k].cpu().numpy(), equal_nan=True), k
+    b.close()
