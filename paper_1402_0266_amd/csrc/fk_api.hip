@@ -215,6 +215,13 @@ int build_tables(const LevelSpec *lv, int n_levels, const double *pts, int64_t n
             cost[(size_t)g] = node_cost(pts[2 * g], pts[2 * g + 1], lv[l].t);
         }
     }
+    double steps = 0.0, steps2 = 0.0;
+    for (int l = 0; l < n_levels; ++l) {
+        const double K = T.levels[(size_t)l].K;
+        steps += (double)lv[l].n_nodes * K;
+        steps2 += (double)lv[l].n_nodes * K * K;
+    }
+    T.steps = steps > 0.0 ? (int64_t)(steps2 / steps) : 0;
     for (int64_t g = 0; g < n_total; ++g)
         if (level_of[(size_t)g] < 0) return fail(FK_E_INVAL, "node %lld belongs to no level", (long long)g);
     std::vector<int64_t> order((size_t)n_total);
@@ -288,8 +295,12 @@ int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
 // 10.9, with the bridge test 19.1 / 18.6 / 17.5, 73920 paths (286 to a lane) 599 /
 // - / 618; 2000 steps 8.30 / 8.02 / 8.05; 500 steps 2.58 / 2.60 / 2.80; 200 steps
 // 1.33 / 1.40 / 1.53.  16 levels of up to 1600 steps 3.94 / 3.85 / 3.98, up to
-// 500 steps 1.63 / 1.66 / 1.83.
-static int long_blocks(int64_t steps, double paths_per_lane, int block) {
+// 500 steps 1.63 / 1.66 / 1.83.  Several levels go by the steps of the level
+// in which a step of the launch is taken on average: one long level of a few nodes among
+// short ones leaves the short ones' paths to fill the chip (15 levels of 200
+// steps at 1521 nodes and one of 10^4 at 29, 512 paths: 3.62 ms at six per CU, 4.14 at
+// three).
+int long_blocks(int64_t steps, double paths_per_lane, int block) {
     if (steps < 1000 || paths_per_lane > 32.0) return 0;
     return std::max(1, (steps < 4000 ? 4 : 3) * 256 / block);
 }

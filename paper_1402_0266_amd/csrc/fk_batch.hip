@@ -50,7 +50,7 @@ static int batch_launch(fk_batch *b, int64_t n_paths, const fk_plan &pl, double 
     S.time_mode = b->T.time_mode;
     S.uniform = b->T.uniform;
     S.plan = pl;
-    for (const LevelDev &l : b->T.levels) S.steps = std::max<int64_t>(S.steps, l.K);
+    S.steps = b->T.steps;
     S.n_nodes = b->n_total;
     S.n_paths = n_paths;
     S.counters = (uint32_t *)ws;

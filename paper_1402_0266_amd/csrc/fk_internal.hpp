@@ -156,6 +156,7 @@ struct Tables {
     int kind = 0, time_mode = 0;
     bool uniform = true;         // every step has length dt
     bool shift = false;          // scores stored relative to the start point
+    int64_t steps = 0;           // of the path that a step belongs to, on average over the levels' steps
 };
 
 // Everything one enqueue of the solve sequence needs.
@@ -166,7 +167,7 @@ struct SolveLaunch {
     bool uniform;
     bool first_by_index;  // few steps: each wavefront's first chunk by its grid index
     bool lockstep;        // short horizons: the kernel of fk_short.hip (lockstep_paths)
-    int64_t steps;        // most steps a path takes
+    int64_t steps;        // a path's steps at most; of several levels, the average over their steps
     const TableArgs *tables;  // device-built tables (filled in by enqueue_solve), or nullptr: host tables
     fk_plan plan;
     int64_t n_nodes, n_paths;
@@ -201,6 +202,9 @@ int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // the largest of 128, 64, 32 paths that leaves at least 64 chunks per CU
 // (few paths per node leave the grid part-empty with larger grabs).
 int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu);
+// Resident workgroups per CU of the refilling path kernel by default (0: all
+// that fit).
+int long_blocks(int64_t steps, double paths_per_lane, int block);
 
 // Launch-plan tuning (fk_plan.hip): a 64-bit FNV-1a hash, the device's
 // signature, the tuned-plan cache (per process; FK_TUNE_CACHE names a file

@@ -1,0 +1,49 @@
+// Prints what the library's launch rules answer.  Reads lines
+//   levels K n [K n ...]        -> steps of Tables (one step size, n nodes a level)
+//   blocks steps per_lane block -> long_blocks
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <iostream>
+#include <sstream>
+#include <string>
+#include <vector>
+
+#include "fk_internal.hpp"
+
+using namespace fk;
+
+static int64_t table_steps(const std::vector<int64_t> &v) {
+    const double dt = 1e-5;
+    std::vector<LevelSpec> lv;
+    int64_t total = 0;
+    for (size_t i = 0; i + 1 < v.size(); i += 2) {
+        LevelSpec s{};
+        s.w.kind = FK_DENSITY_CONST;
+        s.t = (double)v[i] * dt;
+        s.node_offset = total;
+        s.n_nodes = v[i + 1];
+        s.level_id = (uint32_t)(i / 2);
+        total += v[i + 1];
+        lv.push_back(s);
+    }
+    const std::vector<double> pts((size_t)(2 * total), 0.5);
+    fk_data d{};
+    Tables T;
+    if (build_tables(lv.data(), (int)lv.size(), pts.data(), total, &d, dt, T) != FK_OK) return -1;
+    return T.steps;
+}
+
+int main() {
+    std::string line, what;
+    while (std::getline(std::cin, line)) {
+        std::istringstream in(line);
+        in >> what;
+        std::vector<double> v;
+        for (double x; in >> x;) v.push_back(x);
+        long long r = -1;
+        if (what == "levels") r = table_steps(std::vector<int64_t>(v.begin(), v.end()));
+        if (what == "blocks") r = long_blocks((int64_t)v.at(0), v.at(1), (int)v.at(2));
+        std::printf("%lld\n", r);
+    }
+}
