@@ -387,7 +387,7 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
         } else {
             // nobody asked for the count: short horizons skip it (the kernels
             // skip a null count), others keep it in the counters block
-            a.total_steps = S.first_by_index ? nullptr : (unsigned long long *)(S.counters + 2);
+            a.total_steps = S.few_steps ? nullptr : (unsigned long long *)(S.counters + 2);
         }
     }
     a.queue = S.counters;
@@ -401,7 +401,7 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     const int occ = S.lockstep ? short_kernel_max_blocks_per_cu(S.kind, S.time_mode, false, S.plan.block)
                     : expo     ? expo_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.plan.block)
                                : path_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.uniform,
-                                                               a.score_mode == FK_SCORE_BRIDGE, S.first_by_index,
+                                                               a.score_mode == FK_SCORE_BRIDGE, S.few_steps,
                                                                S.plan.block);
     if (bpc == 0 && !S.lockstep && !expo)
         bpc = long_blocks(S.steps, (double)S.n_nodes * (double)S.n_paths / ((double)n_cu * occ * S.plan.block + 1.0),
@@ -411,7 +411,7 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     if ((e = timing_mark(timed, 0, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     e = S.lockstep ? launch_short_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
         : expo     ? launch_expo_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
-                   : launch_paths(S.kind, S.time_mode, S.uniform, S.first_by_index, a, grid, S.plan.block, stream);
+                   : launch_paths(S.kind, S.time_mode, S.uniform, S.few_steps, a, grid, S.plan.block, stream);
     if (e != hipSuccess) return hip_fail(e, "path kernel launch");
     if ((e = timing_mark(timed, 1, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     FinalArgs f = S.fin;
@@ -576,8 +576,8 @@ int fk_interface_solve(const fk_density *w, const fk_data *d, const double *pts,
     // the balance of the tail.
     S.lockstep = lockstep_paths(level.K, t, d->score_mode);
     S.steps = level.K;
-    S.first_by_index = !S.lockstep && level.K <= 64 && d->score_mode != FK_SCORE_EXPONENTIAL;
-    if ((!plan || plan->chunk == 0) && (S.lockstep || S.first_by_index)) {
+    S.few_steps = !S.lockstep && level.K <= 64 && d->score_mode != FK_SCORE_EXPONENTIAL;
+    if ((!plan || plan->chunk == 0) && (S.lockstep || S.few_steps)) {
         int n_cu = 0;
         if ((rc = device_cus(&n_cu)) != FK_OK) return rc;
         S.plan.chunk = S.lockstep ? lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr)
@@ -603,7 +603,7 @@ int fk_interface_solve(const fk_density *w, const fk_data *d, const double *pts,
     tab.outs_out = (OutDev *)(ws + lay.outs);
     tab.acc = S.args.acc;
     tab.shift = shift ? 1 : 0;
-    tab.sort = S.first_by_index ? 0 : 1;   // every node of a short horizon costs about the same
+    tab.sort = S.few_steps ? 0 : 1;   // every node of a short horizon costs about the same
     tab.horizon = (float)t;
     S.tables = &tab;
     S.fin.outs = (const OutDev *)(ws + lay.outs);

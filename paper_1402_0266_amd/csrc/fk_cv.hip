@@ -2204,10 +2204,10 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         P.uniform = uniform;
         P.lockstep = lockstep_paths(level.K, t, d->score_mode);
         P.steps = level.K;
-        P.first_by_index = !P.lockstep && level.K <= 64;
+        P.few_steps = !P.lockstep && level.K <= 64;
         if ((rc = resolve_plan(nullptr, &P.plan)) != FK_OK) return rc;
         if (P.lockstep) P.plan.chunk = lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
-        else if (P.first_by_index) P.plan.chunk = short_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
+        else if (P.few_steps) P.plan.chunk = short_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
         P.n_nodes = n_nodes;
         P.n_paths = n_paths;
         P.counters = counters;
@@ -2221,7 +2221,7 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         TableArgs tp = tab;
         tp.outs_zero_out = nullptr;
         tp.acc2 = nullptr;
-        tp.sort = P.first_by_index ? 0 : 1;
+        tp.sort = P.few_steps ? 0 : 1;
         P.tables = &tp;
         if ((rc = enqueue_solve(P, stream, false)) != FK_OK) return rc;
     }

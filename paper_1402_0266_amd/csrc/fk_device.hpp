@@ -95,6 +95,29 @@ __device__ __forceinline__ PhiloxPath philox_path(uint32_t c1, uint32_t c2, uint
     return PhiloxPath{(uint32_t)p1, (uint32_t)(q0 >> 32), (uint32_t)q0};
 }
 
+// philox4x32_10(c0, c1, c2, c3, k0, k1) with P = philox_path(c1, c2, k0):
+// bitwise the same four words, the round keys in scalar registers.
+__device__ __forceinline__ PhiloxOut philox4x32_10_path(uint32_t c0, uint32_t c3, const PhiloxPath &P, uint32_t k0,
+                                                        uint32_t k1) {
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    const uint64_t p0 = (uint64_t)kM0 * c0;
+    const uint32_t x2 = xor3_uniform((uint32_t)(p0 >> 32), c3, k1), x3 = (uint32_t)p0;
+    const uint64_t p1 = (uint64_t)kM1 * x2;
+    uint32_t v0 = xor3_uniform((uint32_t)(p1 >> 32), P.b, k0 + kW0), v1 = (uint32_t)p1;
+    uint32_t v2 = xor3_uniform(P.h0, x3, k1 + kW1), v3 = P.l0;
+#pragma unroll
+    for (uint32_t r = 2; r < 10; ++r) {
+        const uint64_t a = (uint64_t)kM0 * v0, b = (uint64_t)kM1 * v2;
+        const uint32_t n0 = xor3_uniform((uint32_t)(b >> 32), v1, k0 + r * kW0);
+        const uint32_t n2 = xor3_uniform((uint32_t)(a >> 32), v3, k1 + r * kW1);
+        v1 = (uint32_t)b;
+        v3 = (uint32_t)a;
+        v0 = n0;
+        v2 = n2;
+    }
+    return PhiloxOut{v0, v1, v2, v3};
+}
+
 // The same products with the round keys (and counter word 3) they meet folded
 // in: what a lane keeps of its path.
 struct PhiloxLane {

@@ -165,7 +165,7 @@ struct SolveLaunch {
     FinalArgs fin;       // outputs; sizes filled by enqueue_solve
     int kind, time_mode;
     bool uniform;
-    bool first_by_index;  // few steps: each wavefront's first chunk by its grid index
+    bool few_steps;       // at most 64 steps in the refilling kernel: its few-steps form
     bool lockstep;        // short horizons: the kernel of fk_short.hip (lockstep_paths)
     int64_t steps;        // a path's steps at most; of several levels, the average over their steps
     const TableArgs *tables;  // device-built tables (filled in by enqueue_solve), or nullptr: host tables
@@ -240,7 +240,7 @@ hipError_t timing_record(int i, hipStream_t s);
 
 // Launch helpers implemented in fk_paths.hip.
 hipError_t launch_zero_u32(uint32_t *p, int n_words, hipStream_t s);
-hipError_t launch_paths(int kind, int time_mode, bool uniform, bool first_by_index, const PathArgs &a, int grid,
+hipError_t launch_paths(int kind, int time_mode, bool uniform, bool few_steps, const PathArgs &a, int grid,
                         int block, hipStream_t s);
 hipError_t launch_finalize(const FinalArgs &a, hipStream_t s);
 // Device node tables (three small kernels; after the counters and sums are zeroed).
@@ -259,7 +259,7 @@ int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, int block
 hipError_t launch_counters_init(uint32_t *counters, uint32_t total_chunks, hipStream_t s);
 // Bytes of the per-node estimator sums of n_out rows.
 size_t acc_bytes(int64_t n_out);
-int path_kernel_max_blocks_per_cu(int kind, int time_mode, bool uniform, bool bridge, bool first_by_index, int block);
+int path_kernel_max_blocks_per_cu(int kind, int time_mode, bool uniform, bool bridge, bool few_steps, int block);
 // Exponential time-stepping (FK_SCORE_EXPONENTIAL): its own path kernel.
 hipError_t launch_expo_paths(int kind, int time_mode, const PathArgs &a, int grid, int block, hipStream_t s);
 int expo_kernel_max_blocks_per_cu(int kind, int time_mode, int block);

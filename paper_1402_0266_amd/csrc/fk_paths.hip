@@ -236,13 +236,17 @@ hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_ste
 }
 
 // BRIDGE: the Brownian-bridge crossing test after every step that stays
-// inside (score mode FK_SCORE_BRIDGE).  FIRST_BY_INDEX (short horizons): a
-// wavefront's first chunk is its index in the grid, later ones come from the
-// counter past the first grid-full, so a launch of short paths does not open
-// with every wavefront contending for the counter.  Long horizons keep the
-// counter for every grab (the other form costs their hot loop ~3% in code).
+// inside (score mode FK_SCORE_BRIDGE).  FEW_STEPS (horizons of 33 to 64 steps
+// over which paths leave): steps with a branch after each (two_steps), on seven
+// wavefronts per SIMD, and a wavefront's first chunk is its index in the grid,
+// later ones come from the counter past the first grid-full, so a launch of
+// short paths does not open with every wavefront contending for the counter.
+// Long horizons keep the counter for every grab (the other form costs their
+// hot loop ~3% in code).  Ring and moving bump, 1521 nodes x 4096 paths, 64
+// steps over t = 0.1: 736 and 605 us, in branch-free pairs 785 and 628 us; a
+// path ends every second pair or so of a wavefront there.
 //
-// The inner loop takes step pairs without a branch until some lane's path may
+// The inner loop of the others takes step pairs without a branch until some lane's path may
 // have ended: both steps are taken at once, and one unsigned maximum over the
 // four new coordinates and the pair count finds the wavefronts that have to
 // look closer.  Idle lanes hold a point that stays at (0.5, 0.5).  Scores,
@@ -259,7 +263,7 @@ hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_ste
 // cycles a pair, 2.2 ms for 10^4 steps; while the wavefronts thin out after
 // the queue has run empty ~5 ms pass at six per SIMD and half that at three
 // (the default there: long_blocks, fk_api.hip).
-template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FIRST_BY_INDEX = false>
+template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FEW_STEPS = false>
 __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
     const uint32_t lane = threadIdx.x & 63u;
     __shared__ AccSlot<2> slot_tab[4][kAccSlots];
@@ -271,7 +275,7 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
     uint32_t q_slot = 0, q_next = 0, q_end = 0, q_tag = 0, grabs = 0;
     bool q_done = false;
     const uint32_t total_chunks = launch_chunks(a);
-    if constexpr (FIRST_BY_INDEX) {
+    if constexpr (FEW_STEPS) {
         q_done = !chunk_cursor(a, total_chunks, first_chunk(), q_slot, q_next, q_end);
         if (!q_done) {
             q_tag = slot_open<2>(slots, accs, grabs++, (uint32_t)a.nodes[q_slot].out, q_end - q_next, lane);
@@ -283,17 +287,20 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
 
     Lane L;
     PairLane P{};
+    PhiloxPath pp{};          // the lane's path's fixed Philox products
     uint32_t my_tag = 0;      // accumulation tag of the lane's path's chunk
     uint32_t my_steps = 0;
     uint64_t act = 0;         // the lanes with a path
-    lane_level<KIND, TMODE>(L, a.levels[0]);
-    pair_idle<BRIDGE>(L, P);
+    if constexpr (!FEW_STEPS) {
+        lane_level<KIND, TMODE>(L, a.levels[0]);
+        pair_idle<BRIDGE>(L, P);
+    }
 
     for (;;) {
         // ---- refill idle lanes -------------------------------------------
         while (~act != 0ull && !q_done) {
             if (q_next >= q_end) {
-                if constexpr (FIRST_BY_INDEX) {
+                if constexpr (FEW_STEPS) {
                     // a grid no larger than the chunk count hands out no more
                     // chunks: finish without touching the counter
                     if (gridDim.x * (blockDim.x >> 6) >= total_chunks) {
@@ -304,7 +311,7 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
                 uint32_t c = 0;
                 if (lane == 0) c = atomicAdd(a.queue, 1u);
                 c = __builtin_amdgcn_readfirstlane(c);
-                if constexpr (FIRST_BY_INDEX) c += gridDim.x * (blockDim.x >> 6);
+                if constexpr (FEW_STEPS) c += gridDim.x * (blockDim.x >> 6);
                 if (c >= total_chunks) {
                     q_done = true;
                     break;
@@ -323,7 +330,8 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
             const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
             if (take) {
                 lane_start<KIND, TMODE>(L, a.nodes[q_slot], a.levels, q_next + rank);
-                pair_start<BRIDGE>(L, P, key0, key1);
+                if constexpr (FEW_STEPS) pp = philox_path(L.path, L.nid, key0);
+                else pair_start<BRIDGE>(L, P, key0, key1);
                 my_tag = q_tag;
             }
             act |= ballot(take);
@@ -331,26 +339,40 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
         }
         if (act == 0ull) break;
 
-        // ---- step pairs, until a path ends ---------------------------------
-        Pair p;
-        uint64_t fin;
-        do {
-            fin = ballot(pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p)) & act;
-        } while (fin == 0ull);
-
-        // ---- score (eq. (7b)) and the node's sums ------------------------------
-        const int with = pair_ends(L, P, p);
-        fin &= ballot(with != 0);
         bool closed = false;      // the lane's path closed its chunk's slot
-        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
-            const bool out = pair_end<BRIDGE>(L, P, p, with);
+        // ---- score (eq. (7b)) of an ended path, and the node's sums ------------
+        const auto path_end = [&](bool out) {
             float v[2];
             score_path(a, L, out, v[0], v[1]);
             closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
             my_steps += (uint32_t)L.k;      // the path's steps, counted once at its end
             if (a.scores) a.scores[path_rec(L, a.n_paths)] = make_float2(v[0], v[1]);
             if (a.exit_step) a.exit_step[path_rec(L, a.n_paths)] = out ? L.k : -1;
-            pair_idle<BRIDGE>(L, P);
+        };
+        uint64_t fin;             // the lanes whose path has ended
+        if constexpr (FEW_STEPS) {
+            // ---- two steps ------------------------------------------------------
+            bool end = false;
+            if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+                bool out = false;
+                float dbx = 0.f, dby = 0.f;
+                if (L.k < L.K) out = two_steps<KIND, TMODE, UNIFORM, BRIDGE>(L, pp, key0, key1, dbx, dby);
+                end = out || L.k >= L.K;
+                if (end) path_end(out);
+            }
+            fin = ballot(end);
+        } else {
+            // ---- step pairs, until a path ends ----------------------------------
+            Pair p;
+            do {
+                fin = ballot(pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p)) & act;
+            } while (fin == 0ull);
+            const int with = pair_ends(L, P, p);
+            fin &= ballot(with != 0);
+            if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+                path_end(pair_end<BRIDGE>(L, P, p, with));
+                pair_idle<BRIDGE>(L, P);
+            }
         }
         act &= ~fin;
         if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);
@@ -484,32 +506,33 @@ __global__ void __launch_bounds__(256) fk_expo_path_kernel(const PathArgs a) {
 }
 
 namespace {
-template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FIRST>
+template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FEW_STEPS>
 hipError_t launch_one(const PathArgs &a, int grid, int block, hipStream_t s) {
-    hipLaunchKernelGGL((fk_path_kernel<KIND, TMODE, UNIFORM, BRIDGE, FIRST>), dim3(grid), dim3(block), 0, s, a);
+    hipLaunchKernelGGL((fk_path_kernel<KIND, TMODE, UNIFORM, BRIDGE, FEW_STEPS>), dim3(grid), dim3(block), 0, s, a);
     return hipGetLastError();
 }
 
-template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FIRST>
+template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool FEW_STEPS>
 int max_blocks(int block) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_path_kernel<KIND, TMODE, UNIFORM, BRIDGE, FIRST>, block,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_path_kernel<KIND, TMODE, UNIFORM, BRIDGE, FEW_STEPS>, block,
                                                      0) != hipSuccess)
         return 0;
     return nb;
 }
 
-// Calls F<KIND, TMODE, UNIFORM, BRIDGE, FIRST>::run(args...) for the runtime
-// values; the first-chunk-by-index form only for uniform steps without the
-// bridge test (a mesh step's sub-steps).
+// Calls F<KIND, TMODE, UNIFORM, BRIDGE, FEW_STEPS>::run(args...) for the runtime
+// values; the few-steps form only without the bridge test.
 template <template <int, int, bool, bool, bool> class F, typename... Args>
-auto dispatch(int kind, int time_mode, bool uniform, bool bridge, bool first_by_index, Args &&...args) {
+auto dispatch(int kind, int time_mode, bool uniform, bool bridge, bool few_steps, Args &&...args) {
     const bool frozen = (time_mode == TIME_FROZEN);
 #define FK_CASE(K, T)                                                                          \
     if (bridge)                                                                                \
         return uniform ? F<K, T, true, true, false>::run(std::forward<Args>(args)...)         \
                        : F<K, T, false, true, false>::run(std::forward<Args>(args)...);       \
-    if (uniform && first_by_index) return F<K, T, true, false, true>::run(std::forward<Args>(args)...); \
+    if (few_steps)                                                                             \
+        return uniform ? F<K, T, true, false, true>::run(std::forward<Args>(args)...)         \
+                       : F<K, T, false, false, true>::run(std::forward<Args>(args)...);       \
     return uniform ? F<K, T, true, false, false>::run(std::forward<Args>(args)...)            \
                    : F<K, T, false, false, false>::run(std::forward<Args>(args)...)
     switch (kind) {
@@ -547,17 +570,17 @@ bool kind_known(int kind) {
 }
 }  // namespace
 
-hipError_t launch_paths(int kind, int time_mode, bool uniform, bool first_by_index, const PathArgs &a, int grid,
+hipError_t launch_paths(int kind, int time_mode, bool uniform, bool few_steps, const PathArgs &a, int grid,
                         int block, hipStream_t s) {
     if (!kind_known(kind)) return hipErrorInvalidValue;
-    return dispatch<LaunchF>(kind, time_mode, uniform, a.score_mode == FK_SCORE_BRIDGE, first_by_index, a, grid,
+    return dispatch<LaunchF>(kind, time_mode, uniform, a.score_mode == FK_SCORE_BRIDGE, few_steps, a, grid,
                              block, s);
 }
 
-int path_kernel_max_blocks_per_cu(int kind, int time_mode, bool uniform, bool bridge, bool first_by_index,
+int path_kernel_max_blocks_per_cu(int kind, int time_mode, bool uniform, bool bridge, bool few_steps,
                                   int block) {
     if (!kind_known(kind)) return 0;
-    return dispatch<OccF>(kind, time_mode, uniform, bridge, first_by_index, block);
+    return dispatch<OccF>(kind, time_mode, uniform, bridge, few_steps, block);
 }
 
 namespace {
