@@ -335,6 +335,45 @@ int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
     return 64 * best;
 }
 
+// In pairs a step takes fewer instructions and a path's end more, and four
+// wavefronts per SIMD fit instead of five or six.  Measured against the form
+// with a branch after each step (its time 1; two bumps and moving bump, 41 to
+// 768 cells):
+//  * 65 to 100 steps: 0.85 - 0.98 with few paths, up to 1.25 where many paths
+//    end all the time (10689 nodes x 500 paths), so not below 200 steps; 200
+//    and 400 steps: 0.87 and 0.82 up to 16 wavefronts of paths to a SIMD, up to
+//    1.17 and 1.12 at 80; from 1000 steps on 0.6 - 0.8.
+//  * where few paths leave before the horizon, all that are started together
+//    end together, and where only the other form holds them all at once it is
+//    faster: 1.0 - 1.37 over t = 0.01 at four to six wavefronts of paths to a
+//    SIMD; over t = 0.1, where half of them leave, 0.7 - 0.8.
+//    There on as many workgroups as hold them.
+// With the bridge test, which takes one Philox call in pairs and two otherwise,
+// pairs throughout: 0.75 - 0.9 of the time, up to 1.15 where many paths end all
+// the time and up to 1.25 where few leave and four workgroups just miss holding all.
+// Few long paths do better on fewer workgroups than fit, as in the plain
+// kernel (long_blocks): over t = 0.1 and 10^4 steps, 2 / 3 / 4 per CU in ms,
+// 256 paths at 1521 nodes (u = 5.9) 4.16 / 4.71 / 5.08, 512 paths 6.51 / 6.92 /
+// 7.28, 2952 paths 29.0 / 27.5 / 28.3.  Where few leave, on as many as hold them all
+// (t = 0.01, 4000 steps, u = 1.5: 0.55 / 0.76 / 0.76; 2.4: 0.86 / 0.54 / 0.67;
+// 3.3: 1.08 / 1.18 / 0.72), and else on three (u = 7: 0.72 / 0.68 / 0.77; 1000
+// steps, u = 5.2, bridge: 1.24 / 1.13 / 1.20).
+MggForm mgg_form(int64_t K, double t, double u, bool bridge, int occ_pairs, int occ_other) {
+    const bool few_leave = t <= 0.03, held_by_other = few_leave && u > occ_pairs && u <= occ_other;
+    MggForm f{};
+    f.pairs = bridge || ((K >= 1000 || (K >= 200 && u <= 20.0)) && !held_by_other);
+    if (!f.pairs) {
+        if (held_by_other) f.blocks = (int)std::ceil(u);
+    } else if (few_leave && K >= 4000) {
+        f.blocks = u <= 1.8 ? 2 : u <= 2.8 ? 3 : u <= 3.8 ? 4 : 3;
+    } else if (few_leave && K >= 1000) {
+        f.blocks = u > 5.0 && u <= 6.0 ? 3 : 0;
+    } else if (K >= 4000) {
+        f.blocks = u <= 32.0 ? 2 : 3;
+    }
+    return f;
+}
+
 int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu) {
     // 64 chunks per CU: at least eight per resident wavefront of the
     // network kernels (two waves per SIMD)

@@ -948,15 +948,20 @@ __global__ void __launch_bounds__(256, SPLIT ? 2 : 3) fk_mg_path_kernel(const Pa
 // bilinear interpolant of (grid_xi, grid_eta) at its position, and the score
 // is g - sum_j G_j . dB_j.  No network: lanes need no common evaluation
 // points, so they start new paths at once, and each path's blocks sit at
-// fixed offsets from its start (schedule-independent results).  Step pairs
-// without a branch, as in the other path kernels; four waves per SIMD (106
-// registers; at five it spills and runs 2-10% slower).  Measured (moving bump,
-// 1521 nodes x 512 paths, the identity's gradient, stride 2 / 100 / once per
-// path): 9.5 / 8.2 / 7.4 ms against 13.0 / 10.8 / 10.4 with a branch after
-// each step, with the bridge test 13.4 / 12.0 / 11.5 against 18.0 / 16.0 / 15.2.
-
-template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE>
-__global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, const MggArgs c) {
+// fixed offsets from its start (schedule-independent results).  PAIRS: steps
+// in pairs without a branch, as in the other path kernels; four waves per SIMD
+// (106 registers; at five it spills and runs 2-10% slower).  Otherwise, and
+// not with the bridge test, with a branch after each step on five or six waves:
+// fewer instructions for a path's end, and more wavefronts to wait for its
+// gathers (mgg_form has the rule).
+// Measured (moving bump, 1521 nodes x 512 paths x 10^4 steps, the identity's
+// gradient, stride 2 / 100 / once per path): 9.5 / 8.2 / 7.4 ms in pairs against 13.0 /
+// 10.8 / 10.4, with the bridge test 13.4 / 12.0 / 11.5 against 18.0 / 16.0 /
+// 15.2; two bumps, 768 cells, 10689 nodes x 500 paths x 65 steps over 0.01, stride 20:
+// 1.59 ms in pairs against 1.27.
+template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE, bool PAIRS>
+__global__ void __launch_bounds__(256, PAIRS ? 1 : UNIFORM ? 6 : 5)
+    fk_mgg_path_kernel(const PathArgs a, const MggArgs c) {
     const uint32_t lane = threadIdx.x & 63u;
     __shared__ AccSlot<2> slot_tab[4][kAccSlots];
     AccSlot<2> *slots = slot_tab[threadIdx.x >> 6];
@@ -972,12 +977,14 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
     PairLane P{};
     float gxx = 0.f, gxy = 0.f, gyx = 0.f, gyy = 0.f;
     float dbx = 0.f, dby = 0.f, mx = 0.f, my = 0.f;
-    int32_t next_block = -1;     // the pair before which the path's next block opens
+    int32_t next_block = -1;     // the pair before which the path's next block opens (!PAIRS: pairs to it)
     uint32_t my_tag = 0;         // accumulation tag of the path's chunk
     uint32_t my_steps = 0;
     uint64_t act = 0;            // lanes with a path
-    lane_level<KIND, TMODE>(L, a.levels[0]);
-    pair_idle<BRIDGE>(L, P);
+    if constexpr (PAIRS) {
+        lane_level<KIND, TMODE>(L, a.levels[0]);
+        pair_idle<BRIDGE>(L, P);
+    }
 
     for (;;) {
         while (~act != 0ull && !q_done) {
@@ -995,7 +1002,7 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
             const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < avail;
             if (take) {
                 lane_start<KIND, TMODE>(L, a.nodes[q_slot], a.levels, q_next + rank);
-                pair_start<BRIDGE>(L, P, key0, key1);
+                if constexpr (PAIRS) pair_start<BRIDGE>(L, P, key0, key1);
                 my_tag = q_tag;
                 dbx = dby = mx = my = 0.f;
                 next_block = 0;
@@ -1005,52 +1012,28 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
         }
         if (act == 0ull) break;
 
-        // ---- step pairs, until a path ends ---------------------------------
-        Pair p;
-        float d1x, d1y;              // the block's Brownian part after the pair's first step
-        uint64_t fin;
-        do {
-            if (ballot(P.half == next_block) != 0ull) {
-                if (P.half == next_block) {
-                    // block boundary (a multiple of the stride): close the
-                    // block, take the gradient here
-                    next_block += (int32_t)c.stride_iters;
-                    mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
-                    my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
-                    dbx = dby = 0.f;
-                    if (c.gtab) {
-                        table_gradient(c.gtab, a.grid_n, 0, L.xh, L.yh, gxx, gxy);
-                        table_gradient(c.gtab, a.grid_n, 1, L.xh, L.yh, gyx, gyy);
-                    } else {
-                        grid_gradient(a.grid_xi, a.grid_n, L.xh, L.yh, gxx, gxy);
-                        grid_gradient(a.grid_eta, a.grid_n, L.xh, L.yh, gyx, gyy);
-                    }
-                    if (c.gofs) {
-                        const float4 o = c.gofs[L.out];   // L2-resident, 16 B per node
-                        gxx += o.x;
-                        gxy += o.y;
-                        gyx += o.z;
-                        gyy += o.w;
-                    }
-                }
-            }
-            const bool may = pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p);
-            d1x = dbx + p.w1x;
-            d1y = dby + p.w1y;
-            dbx = d1x + p.w2x;
-            dby = d1y + p.w2y;
-            fin = ballot(may) & act;
-        } while (fin == 0ull);
-        const int with = pair_ends(L, P, p);
-        fin &= ballot(with != 0);
         bool closed = false;         // the lane's path closed its chunk's slot
-        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
-            if (with == 1) {
-                dbx = d1x;
-                dby = d1y;
+        // a block's start: the last one closed, the gradient taken here
+        const auto block_start = [&]() {
+            mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
+            my = fmaf(gyx, dbx, fmaf(gyy, dby, my));
+            dbx = dby = 0.f;
+            if (c.gtab) {
+                table_gradient(c.gtab, a.grid_n, 0, L.xh, L.yh, gxx, gxy);
+                table_gradient(c.gtab, a.grid_n, 1, L.xh, L.yh, gyx, gyy);
+            } else {
+                grid_gradient(a.grid_xi, a.grid_n, L.xh, L.yh, gxx, gxy);
+                grid_gradient(a.grid_eta, a.grid_n, L.xh, L.yh, gyx, gyy);
             }
-            if (L.K <= 0) dbx = dby = 0.f;
-            const bool out = pair_end<BRIDGE>(L, P, p, with);
+            if (c.gofs) {
+                const float4 o = c.gofs[L.out];   // L2-resident, 16 B per node
+                gxx += o.x;
+                gxy += o.y;
+                gyx += o.z;
+                gyy += o.w;
+            }
+        };
+        const auto path_end = [&](bool out) {
             float plx, ply;
             score_path(a, L, out, plx, ply);
             mx = fmaf(gxx, dbx, fmaf(gxy, dby, mx));
@@ -1063,8 +1046,57 @@ __global__ void __launch_bounds__(256) fk_mgg_path_kernel(const PathArgs a, cons
             if (a.scores) a.scores[rec] = make_float2(plx, ply);
             if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
             if (a.exit_step) a.exit_step[rec] = out ? L.k : -1;
-            pair_idle<BRIDGE>(L, P);
-            next_block = -1;
+        };
+        uint64_t fin;                // the lanes whose path has ended
+        if constexpr (!PAIRS) {
+            // ---- two steps ------------------------------------------------------
+            bool end = false;
+            if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+                bool out = false;
+                if (L.k < L.K) {
+                    if (next_block == 0) {
+                        next_block = (int32_t)c.stride_iters;
+                        block_start();
+                    }
+                    --next_block;
+                    // (no per-path products: their registers would cost a wavefront)
+                    const PhiloxOut r = philox4x32_10((uint32_t)L.k >> 1, L.path, L.nid, L.ctr3, key0, key1);
+                    out = two_steps<KIND, TMODE, UNIFORM>(L, r, dbx, dby);
+                }
+                end = out || L.k >= L.K;
+                if (end) path_end(out);
+            }
+            fin = ballot(end);
+        } else {
+            // ---- step pairs, until a path ends ----------------------------------
+            Pair p;
+            float d1x, d1y;          // the block's Brownian part after the pair's first step
+            do {
+                if (ballot(P.half == next_block) != 0ull) {
+                    if (P.half == next_block) {
+                        next_block += (int32_t)c.stride_iters;
+                        block_start();
+                    }
+                }
+                const bool may = pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p);
+                d1x = dbx + p.w1x;
+                d1y = dby + p.w1y;
+                dbx = d1x + p.w2x;
+                dby = d1y + p.w2y;
+                fin = ballot(may) & act;
+            } while (fin == 0ull);
+            const int with = pair_ends(L, P, p);
+            fin &= ballot(with != 0);
+            if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+                if (with == 1) {
+                    dbx = d1x;
+                    dby = d1y;
+                }
+                if (L.K <= 0) dbx = dby = 0.f;
+                path_end(pair_end<BRIDGE>(L, P, p, with));
+                pair_idle<BRIDGE>(L, P);
+                next_block = -1;
+            }
         }
         act &= ~fin;
         if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);
@@ -1637,23 +1669,27 @@ struct MgOccF {
     }
 };
 template <int K, int T, bool U>
+constexpr auto mgg_kernel(bool bridge, bool pairs) {
+    return bridge  ? fk_mgg_path_kernel<K, T, U, true, true>
+           : pairs ? fk_mgg_path_kernel<K, T, U, false, true>
+                   : fk_mgg_path_kernel<K, T, U, false, false>;
+}
+template <int K, int T, bool U>
 struct MggLaunchF {
-    static hipError_t run(const PathArgs &a, const MggArgs &c, int grid, hipStream_t s) {
-        if (a.score_mode == FK_SCORE_BRIDGE)
-            hipLaunchKernelGGL((fk_mgg_path_kernel<K, T, U, true>), dim3(grid), dim3(256), 0, s, a, c);
-        else
-            hipLaunchKernelGGL((fk_mgg_path_kernel<K, T, U, false>), dim3(grid), dim3(256), 0, s, a, c);
+    static hipError_t run(const PathArgs &a, const MggArgs &c, bool pairs, int grid, hipStream_t s) {
+        const auto k = mgg_kernel<K, T, U>(a.score_mode == FK_SCORE_BRIDGE, pairs);
+        hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, a, c);
         return hipGetLastError();
     }
 };
 template <int K, int T, bool U>
 struct MggOccF {
-    static int run(bool bridge) {
+    static int run(bool bridge, bool pairs) {
         int nb = 0;
-        const hipError_t e =
-            bridge ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_mgg_path_kernel<K, T, U, true>, 256, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_mgg_path_kernel<K, T, U, false>, 256, 0);
-        return e == hipSuccess ? nb : 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mgg_kernel<K, T, U>(bridge, pairs), 256, 0) ==
+                       hipSuccess
+                   ? nb
+                   : 0;
     }
 };
 template <int K, int T, bool U>
@@ -2139,18 +2175,20 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         c.acc_cv = acc_cv;
         c.gtab = grid_table(d, workspace, workspace_bytes, lay.total, stream, &e);
         if (e != hipSuccess) return hip_fail(e, "gradient table kernel launch");
+        const auto mgg_occ = [&](bool pairs) {
+            return cv_dispatch<MggOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE, pairs);
+        };
+        const MggForm form = lockstep ? MggForm{}
+                                      : mgg_form(level.K, t, per_lane(1), d->score_mode == FK_SCORE_BRIDGE,
+                                                 mgg_occ(true), mgg_occ(false));
         const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, true, 256)
-                                 : cv_dispatch<MggOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE);
-        // Fewer workgroups than fit over long horizons, as for the plain kernel
-        // (long_blocks).  The identity's gradient, 10^4 steps, 1521 nodes, 2 / 3 / 4
-        // per CU in ms: 256 paths (1.5 to a lane at four) 4.16 / 4.71 / 5.08, 512
-        // paths 6.51 / 6.92 / 7.28, 2952 paths (17) 29.0 / 27.5 / 28.3.
-        if (bpc == 0 && !lockstep && level.K >= 4000) bpc = per_lane(occ) <= 8.0 ? 2 : 3;
+                                 : mgg_occ(form.pairs);
+        if (bpc == 0 && !lockstep) bpc = form.blocks;
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
         const int grid = cap_grid(n_cu * bpc, a.total_chunks, 256);
         a.masked = mask ? 1u : 0u;
         e = lockstep ? launch_short_mesh_paths(w->kind, w->time_mode, a, c, t, level.K, n_nodes, n_cu, grid, 256, stream)
-                     : cv_dispatch<MggLaunchF>(w->kind, w->time_mode, uniform, a, c, grid, stream);
+                     : cv_dispatch<MggLaunchF>(w->kind, w->time_mode, uniform, a, c, form.pairs, grid, stream);
         if (e != hipSuccess) return hip_fail(e, "control-variate path kernel launch");
     } else {
         MgArgs c{};

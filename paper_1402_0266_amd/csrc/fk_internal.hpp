@@ -206,6 +206,17 @@ int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu);
 // that fit).
 int long_blocks(int64_t steps, double paths_per_lane, int block);
 
+// Form and residency of the mesh-gradient control's refilling kernel
+// (fk_mgg_path_kernel): steps in branch-free pairs or not, and the resident
+// workgroups per CU by default (0: all that fit).  K steps over t; u: paths to
+// a lane at one workgroup per CU (wavefronts of paths to a SIMD); with the
+// bridge test or not; workgroups per CU that fit in pairs and otherwise.
+struct MggForm {
+    bool pairs;
+    int blocks;
+};
+MggForm mgg_form(int64_t K, double t, double u, bool bridge, int occ_pairs, int occ_other);
+
 // Launch-plan tuning (fk_plan.hip): a 64-bit FNV-1a hash, the device's
 // signature, the tuned-plan cache (per process; FK_TUNE_CACHE names a file
 // that persists it), and the sweep over candidate plans: `launch` enqueues

@@ -356,7 +356,10 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
             if (__builtin_amdgcn_inverse_ballot_w64(act)) {
                 bool out = false;
                 float dbx = 0.f, dby = 0.f;
-                if (L.k < L.K) out = two_steps<KIND, TMODE, UNIFORM, BRIDGE>(L, pp, key0, key1, dbx, dby);
+                if (L.k < L.K) {
+                    const PhiloxOut r = philox4x32_10_path((uint32_t)L.k >> 1, L.ctr3, pp, key0, key1);
+                    out = two_steps<KIND, TMODE, UNIFORM>(L, r, dbx, dby);
+                }
                 end = out || L.k >= L.K;
                 if (end) path_end(out);
             }

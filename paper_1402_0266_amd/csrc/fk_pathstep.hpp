@@ -282,54 +282,30 @@ __device__ __forceinline__ void lane_start(Lane &L, const NodeDev &nd, const Lev
 // ends; 12 to 25 registers fewer keep more wavefronts resident).
 // ---------------------------------------------------------------------------
 
-// The Brownian-bridge test (FK_SCORE_BRIDGE) of step L.k - 1, just taken from
-// a point at the distances d0: its uniform is word k & 1 of Philox(k/2, path,
-// node, ctr3 | 4).  A path that crossed is moved onto the side.
-template <bool UNIFORM>
-__device__ __forceinline__ bool bridge_exit(Lane &L, const SideDist &d0, uint32_t key0, uint32_t key1) {
-    const int32_t k = L.k - 1;
-    float D = L.dt;
-    if constexpr (!UNIFORM) D = (k == L.K - 1) ? L.dt_last : D;
-    int side;
-    const float p = bridge_prob(d0, side_dist(L), 1.f / D, side);
-    if (side < 0) return false;
-    const PhiloxOut r = philox4x32_10((uint32_t)k >> 1, L.path, L.nid, L.ctr3 | 4u, key0, key1);
-    if (!(bridge_uniform((k & 1) ? r.r1 : r.r0) < p)) return false;
-    move_to_side(L, side);
-    return true;
-}
-
 // One step; its Brownian part is added to (dbx, dby).  True if the path left.
-template <int KIND, bool UNIFORM, bool BRIDGE>
-__device__ __forceinline__ bool one_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, uint32_t key0,
-                                         uint32_t key1, float &dbx, float &dby) {
+template <int KIND, bool UNIFORM>
+__device__ __forceinline__ bool one_step(Lane &L, uint32_t ra, uint32_t rb, float ox, float oy, float &dbx,
+                                         float &dby) {
     float D = L.dt, cb = L.cbm;
     if constexpr (!UNIFORM) {
         const bool last = (L.k == L.K - 1);
         D = last ? L.dt_last : D;
         cb = last ? L.cbm_last : cb;
     }
-    SideDist d0{};
-    if constexpr (BRIDGE) d0 = side_dist(L);
     float wx, wy;
     em_move<KIND>(L.xh, L.xl, L.yh, L.yl, L.dens, ra, rb, ox, oy, D, cb, kUnitMask, wx, wy);
     L.k += 1;
-    bool out = outside(L.xh, L.xl, L.yh, L.yl);
-    if constexpr (BRIDGE) {
-        if (!out) out = bridge_exit<UNIFORM>(L, d0, key0, key1);
-    }
+    const bool out = outside(L.xh, L.xl, L.yh, L.yl);
     dbx += wx;
     dby += wy;
     return out;
 }
 
-// The two steps of one Philox call (pp: philox_path of the lane's path), the
-// second one if the path is still inside and under way.  True if it left.
-template <int KIND, int TMODE, bool UNIFORM, bool BRIDGE>
-__device__ __forceinline__ bool two_steps(Lane &L, const PhiloxPath &pp, uint32_t key0, uint32_t key1, float &dbx,
-                                          float &dby) {
+// The two steps of one Philox call r, the second one if the path is still
+// inside and under way.  True if it left.
+template <int KIND, int TMODE, bool UNIFORM>
+__device__ __forceinline__ bool two_steps(Lane &L, const PhiloxOut &r, float &dbx, float &dby) {
     constexpr bool kMovingBackward = moving_kind(KIND) && TMODE == TIME_BACKWARD;
-    const PhiloxOut r = philox4x32_10_path((uint32_t)L.k >> 1, L.ctr3, pp, key0, key1);
     float ox = L.ox, oy = L.oy, cr = 0.f, sr = 0.f;
     if constexpr (kMovingBackward) {
         // orbit angle at PDE time t_init + t - k dt, in revolutions
@@ -339,14 +315,14 @@ __device__ __forceinline__ bool two_steps(Lane &L, const PhiloxPath &pp, uint32_
         ox = L.dens.orbit_r * cr;
         oy = L.dens.orbit_r * sr;
     }
-    if (one_step<KIND, UNIFORM, BRIDGE>(L, r.r0, r.r1, ox, oy, key0, key1, dbx, dby)) return true;
+    if (one_step<KIND, UNIFORM>(L, r.r0, r.r1, ox, oy, dbx, dby)) return true;
     if (L.k >= L.K) return false;
     if constexpr (kMovingBackward) {
         // one step later it is smaller by omega dt: rotate (cos, sin)
         ox = L.dens.orbit_r * fmaf(cr, L.cos_d, sr * L.sin_d);
         oy = L.dens.orbit_r * fmaf(sr, L.cos_d, -cr * L.sin_d);
     }
-    return one_step<KIND, UNIFORM, BRIDGE>(L, r.r2, r.r3, ox, oy, key0, key1, dbx, dby);
+    return one_step<KIND, UNIFORM>(L, r.r2, r.r3, ox, oy, dbx, dby);
 }
 
 // ---------------------------------------------------------------------------

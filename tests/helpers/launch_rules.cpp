@@ -1,6 +1,7 @@
 // Prints what the library's launch rules answer.  Reads lines
 //   levels K n [K n ...]        -> steps of Tables (one step size, n nodes a level)
 //   blocks steps per_lane block -> long_blocks
+//   mgg K t u bridge            -> mgg_form where four and six workgroups fit: 10 pairs + blocks
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -44,6 +45,10 @@ int main() {
         long long r = -1;
         if (what == "levels") r = table_steps(std::vector<int64_t>(v.begin(), v.end()));
         if (what == "blocks") r = long_blocks((int64_t)v.at(0), v.at(1), (int)v.at(2));
+        if (what == "mgg") {
+            const MggForm f = mgg_form((int64_t)v.at(0), v.at(1), v.at(2), v.at(3) != 0.0, 4, 6);
+            r = 10 * f.pairs + f.blocks;
+        }
         std::printf("%lld\n", r);
     }
 }
