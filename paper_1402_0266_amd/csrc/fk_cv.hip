@@ -1759,12 +1759,14 @@ static CvWs cv_ws_layout(int64_t n_nodes) {
 // The per-cell gradient table of the grid initial data, built on the stream
 // in the workspace past `used` bytes when it has room (NULL otherwise: the
 // kernels then read the grids).
+static bool table_fits(const fk_data *d, size_t workspace_bytes, size_t used) {
+    return workspace_bytes >= align256(used) + (size_t)d->grid_n * d->grid_n * 2 * sizeof(float4);
+}
 static const float4 *grid_table(const fk_data *d, void *workspace, size_t workspace_bytes, size_t used,
                                 hipStream_t stream, hipError_t *err) {
     *err = hipSuccess;
-    const size_t tab_off = align256(used), tab_bytes = (size_t)d->grid_n * d->grid_n * 2 * sizeof(float4);
-    if (workspace_bytes < tab_off + tab_bytes) return nullptr;
-    float4 *tab = (float4 *)((char *)workspace + tab_off);
+    if (!table_fits(d, workspace_bytes, used)) return nullptr;
+    float4 *tab = (float4 *)((char *)workspace + align256(used));
     const int64_t cells = (int64_t)d->grid_n * d->grid_n;
     hipLaunchKernelGGL(grad_table_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, stream, d->grid_xi,
                        d->grid_eta, d->grid_n, tab);
@@ -2071,7 +2073,9 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     // same arithmetic as the network kernel, without its evaluation points).
     const bool base_at_start = grid_base && (int64_t)stride >= (int64_t)level.K;
     // the mesh-gradient control over a short horizon
-    const bool lockstep = (grid_ctl || base_at_start) && lockstep_paths(level.K, t, d->score_mode);
+    const bool lockstep = (grid_ctl || base_at_start) && lockstep_paths(level.K, t, d->score_mode) &&
+                          lockstep_mesh(table_fits(d, workspace_bytes, lay.total), d->grid_n, n_paths, stride, t,
+                                        level.K, n_nodes, n_cu);
     // network forms on short paths (a mesh step's sub-steps): 256 per grab
     // by default (the network-control mesh step went from 29.9 to 22.6 ms on
     // the 768-cell run against 128); the grid control keeps 128.  Larger

@@ -195,6 +195,17 @@ int check_chunks(int64_t n_nodes, int64_t n_paths, const fk_plan &pl);
 int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // Whether a solve takes the short-horizon kernel (fk_short.hip).
 bool lockstep_paths(int64_t K, double t, int score_mode);
+// Whether it does with the mesh-gradient control (as well): at most 32 steps,
+// and with the gradient table over at most t = 0.02, or from an LDS tile.  Past 32
+// steps nodes near a side make the lanes wait for paths that have left (1521 nodes
+// within 0.02 of a side x 4096 paths x 64 steps: 1.5 times the refilling
+// kernel's time, elsewhere 0.6); paths that spread over hundreds of cells miss the
+// caches together (768 cells, 32 steps over 0.05: 1.2).  From the grids themselves (a workspace without room for the
+// table) a gradient is eight gathers instead of two, and the lanes of one node's paths, all
+// at the same step, wait for them together: 10689 nodes x 2 paths x 64 steps took
+// 2.1 times as long as in the refilling kernel, 130 paths x 32 steps 1.27.
+bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes,
+                   int n_cu);
 // Its default chunk: 64 r paths for the r that finishes first when every
 // resident wavefront takes an equal number of chunks.
 int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);

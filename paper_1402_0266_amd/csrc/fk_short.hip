@@ -558,20 +558,25 @@ constexpr int64_t kMaxTileChunk = 32768;
 //   stride 4: 1.66 / 0.86, 10: 0.92 / 0.81, 20 (one block): 0.70 / 0.79;
 //   1024 paths at 2048 nodes 0.39 / 0.26, at 512 0.116 / 0.105, at 128 (fewer
 //   chunks than CUs) 0.066 / 0.075, 2048 paths there 0.082 / 0.076.
-uint32_t tile_chunk(const PathArgs &a, const MggArgs &c, double t, int64_t K, int64_t n_nodes, int n_cu) {
-    const double n = a.grid_n;
+uint32_t tile_chunk(int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes, int n_cu) {
+    const double n = grid_n;
     if (n + 1 > kTile && std::sqrt(2.0 * t) * n > 0.6 * kTile) return 0;
-    const int64_t gathers = (K + 2 * (int64_t)c.stride_iters - 1) / (2 * (int64_t)c.stride_iters);   // of a path
+    const int64_t gathers = (K + stride - 1) / stride;   // of a path
     if (gathers < 2) return 0;
     const int64_t least = (kTile * kTile / gathers + 1023) / 1024 * 1024;      // paths that pay for a tile
     const int64_t split = std::max<int64_t>(1, (8 * (int64_t)n_cu + n_nodes - 1) / n_nodes);
     const int64_t chunk = std::min<int64_t>(
-        kMaxTileChunk, std::max(least, (((int64_t)a.n_paths + split - 1) / split + 1023) / 1024 * 1024));
-    const int64_t per_node = ((int64_t)a.n_paths + chunk - 1) / chunk;
-    if ((int64_t)a.n_paths < least || per_node * n_nodes < n_cu) return 0;
+        kMaxTileChunk, std::max(least, ((n_paths + split - 1) / split + 1023) / 1024 * 1024));
+    const int64_t per_node = (n_paths + chunk - 1) / chunk;
+    if (n_paths < least || per_node * n_nodes < n_cu || per_node * n_nodes > 0x7fffffff) return 0;
     return (uint32_t)chunk;
 }
 }  // namespace
+
+bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes,
+                   int n_cu) {
+    return K <= 32 && ((table && t <= 0.02) || tile_chunk(grid_n, n_paths, stride, t, K, n_nodes, n_cu) != 0);
+}
 
 hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, int grid, int block, hipStream_t s) {
     return short_dispatch<ShortLaunchF>(kind, time_mode, CTL_NONE, a, MggArgs{}, grid, block, s);
@@ -579,7 +584,7 @@ hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, int gr
 
 hipError_t launch_short_mesh_paths(int kind, int time_mode, const PathArgs &a, const MggArgs &c, double t, int64_t K,
                                    int64_t n_nodes, int n_cu, int grid, int block, hipStream_t s) {
-    const uint32_t chunk = tile_chunk(a, c, t, K, n_nodes, n_cu);
+    const uint32_t chunk = tile_chunk(a.grid_n, a.n_paths, 2 * (int64_t)c.stride_iters, t, K, n_nodes, n_cu);
     if (chunk == 0) return short_dispatch<ShortLaunchF>(kind, time_mode, CTL_MESH, a, c, grid, block, s);
     PathArgs b = a;
     b.chunk = chunk;

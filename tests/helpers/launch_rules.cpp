@@ -1,6 +1,8 @@
 // Prints what the library's launch rules answer.  Reads lines
 //   levels K n [K n ...]        -> steps of Tables (one step size, n nodes a level)
 //   blocks steps per_lane block -> long_blocks
+//   lockstep K t mode            -> lockstep_paths
+//   mesh table grid_n paths stride t K nodes -> lockstep_mesh on 256 CUs
 //   mgg K t u bridge            -> mgg_form where four and six workgroups fit: 10 pairs + blocks
 #include <hip/hip_runtime.h>
 
@@ -45,6 +47,10 @@ int main() {
         long long r = -1;
         if (what == "levels") r = table_steps(std::vector<int64_t>(v.begin(), v.end()));
         if (what == "blocks") r = long_blocks((int64_t)v.at(0), v.at(1), (int)v.at(2));
+        if (what == "lockstep") r = lockstep_paths((int64_t)v.at(0), v.at(1), (int)v.at(2));
+        if (what == "mesh")
+            r = lockstep_mesh(v.at(0) != 0.0, (int)v.at(1), (int64_t)v.at(2), (int64_t)v.at(3), v.at(4),
+                              (int64_t)v.at(5), (int64_t)v.at(6), 256);
         if (what == "mgg") {
             const MggForm f = mgg_form((int64_t)v.at(0), v.at(1), v.at(2), v.at(3) != 0.0, 4, 6);
             r = 10 * f.pairs + f.blocks;

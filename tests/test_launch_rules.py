@@ -59,3 +59,16 @@ def test_form_of_the_mesh_gradient_control(rules):
     # the bridge test: pairs throughout
     assert ask((33, 0.1, 9), (65, 0.01, 200), (1000, 0.01, 5.2), (4000, 0.01, 4.5), (4000, 0.1, 4.5), b=1) == \
         [(1, 0), (1, 0), (1, 3), (1, 3), (1, 2)]
+
+
+def test_short_horizon_kernel_with_the_mesh_gradient(rules):
+    """From the table or an LDS tile only, and up to 32 steps."""
+    ask = lambda *a: rules(*("mesh " + " ".join(str(v) for v in q) for q in a))
+    #       table, grid, paths, stride, t, K, nodes
+    assert ask((1, 768, 16384, 2, 5e-4, 20, 10689), (1, 40, 130, 2, 1e-3, 32, 77), (0, 768, 16384, 2, 5e-4, 20, 10689),
+               (0, 64, 4096, 2, 0.05, 32, 1521)) == [1] * 4
+    # past 32 steps; paths spread over hundreds of cells; the grids themselves from memory
+    assert ask((1, 768, 16384, 2, 5e-4, 33, 10689), (0, 64, 4096, 2, 0.05, 64, 1521), (1, 768, 64, 2, 0.05, 32, 1521),
+               (0, 768, 130, 2, 1e-3, 20, 10689), (0, 768, 2, 2, 1e-3, 32, 10689)) == [0] * 5
+    assert rules("lockstep 32 3.0 0", "lockstep 64 0.05 2", "lockstep 64 0.06 0", "lockstep 65 0.001 0",
+                 "lockstep 20 0.001 3", "lockstep 20 0.001 4") == [1, 1, 0, 0, 0, 0]
