@@ -23,6 +23,13 @@
 // branch (as pair_step, fk_pathstep.hpp); after the first exit, and for the
 // pair with the last step, lane by lane under a mask.
 //
+// Past 32 steps a node so near a side that most of its paths leave early
+// (short_leaves) has its lanes take other paths instead (short_refill): 1521
+// nodes within 0.02 of a side x 4096 paths x 64 steps over 0.05: 680 us in
+// lockstep, 391 in the refilling kernel, 242 here.  With the mesh's gradient,
+// which has more to fetch for every path, that stays behind the refilling
+// kernel, which takes those horizons.
+//
 // Measured (two bumps frozen, 10689 nodes x 16384 paths x 20 steps): 5.8 ms
 // (6.1 with the masked loop alone) against the refilling kernel's 9.7 ms when
 // it tested after each step; the ring's 77 nodes x 10^4 paths: 36 us for the
@@ -232,6 +239,100 @@ __device__ __forceinline__ void mesh_gradient(const PathArgs &a, const MggArgs &
     }
 }
 
+// The score (eq. (7b)) of an ended path of node nd, at its end point after
+// k_end steps, less the control (mx, my); its moments are added to q.
+template <int CTL>
+__device__ __forceinline__ void short_score(const PathArgs &a, const MggArgs &c, const ShortWave &S, const NodeDev &nd,
+                                            uint32_t out_row, uint32_t path, float xh, float xl, float yh, float yl,
+                                            int32_t k_end, bool out, float mx, float my, unsigned long long (&q)[4],
+                                            uint32_t &steps) {
+    constexpr bool MESH = CTL != CTL_NONE;
+    const uint64_t rec = (uint64_t)out_row * a.n_paths + path;
+    NodeAcc *const accs[1] = {MESH ? c.acc_cv : a.acc};
+    Lane E = S.L;
+    E.xh = xh;
+    E.xl = xl;
+    E.yh = yh;
+    E.yl = yl;
+    E.px = nd.x;
+    E.py = nd.y;
+    E.k = k_end;
+    E.K = S.K;
+    float v[2];
+    score_path(a, E, out, v[0], v[1]);
+    if constexpr (MESH) {
+        const float sx0 = a.shift ? nd.x : 0.f, sy0 = a.shift ? nd.y : 0.f;
+        v[0] = (v[0] + sx0) - mx;
+        v[1] = (v[1] + sy0) - my;
+        if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
+    } else {
+        if (a.scores) a.scores[rec] = make_float2(v[0], v[1]);
+    }
+    if (a.exit_step) a.exit_step[rec] = out ? k_end : -1;
+    steps += (uint32_t)k_end;
+    // (a comparison per value: false for NaN, which a maximum would drop)
+    if (fabsf(v[0]) < kLdsBound && fabsf(v[1]) < kLdsBound) {
+        q[0] += (unsigned long long)q1_small(v[0]);
+        q[1] += (unsigned long long)q2_small(v[0]);
+        q[2] += (unsigned long long)q1_small(v[1]);
+        q[3] += (unsigned long long)q2_small(v[1]);
+    } else {
+        acc_direct<2>(accs, out_row, v, fabsf(v[0]) < kGlobalBound && fabsf(v[1]) < kGlobalBound);
+    }
+}
+
+// Paths next .. end - 1 of node nd without a control, each lane on to another
+// one when its own has ended, step by step.
+template <int KIND, int TMODE>
+__device__ __forceinline__ void short_refill(const PathArgs &a, const ShortWave &S, const NodeDev &nd, uint32_t out_row,
+                                             uint32_t nid, uint32_t next, uint32_t end, unsigned long long (&q)[4],
+                                             uint32_t &steps) {
+    Lane L = S.L;
+    L.K = S.K;
+    PhiloxPath pp{};
+    uint64_t act = 0;
+    for (;;) {
+        const uint64_t need = ~act;
+        if (need != 0ull && next < end) {
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
+            const bool take = __builtin_amdgcn_inverse_ballot_w64(need) && rank < end - next;
+            if (take) {
+                L.path = next + rank;
+                L.xh = nd.x;
+                L.xl = nd.xlo;
+                L.yh = nd.y;
+                L.yl = nd.ylo;
+                L.k = 0;
+                pp = philox_path(L.path, nid, S.key0);
+            }
+            act |= ballot(take);
+            next += min((uint32_t)__popcll(need), end - next);
+        }
+        if (act == 0ull) break;
+        bool done = false;
+        if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+            float dbx = 0.f, dby = 0.f;
+            const PhiloxOut r = philox4x32_10_path((uint32_t)L.k >> 1, S.ctr3, pp, S.key0, S.key1);
+            const bool out = two_steps<KIND, TMODE, false>(L, r, dbx, dby);
+            done = out || L.k >= S.K;
+            if (done)
+                short_score<CTL_NONE>(a, MggArgs{}, S, nd, out_row, L.path, L.xh, L.xl, L.yh, L.yl, L.k, out, 0.f, 0.f, q,
+                                      steps);
+        }
+        act &= ~ballot(done);
+    }
+}
+
+// Whether most of a node's paths leave early: it lies within 0.56 sqrt(t) of a
+// side, where a path takes half of its steps on average (the integral of
+// erf(d / (2 sqrt(s))) over s), and there are enough steps for what the lanes
+// save to pay for taking other paths.
+__device__ __forceinline__ bool short_leaves(const ShortWave &S, const NodeDev &nd) {
+    const float d = fminf(fminf(nd.x, 1.f - nd.x), fminf(nd.y, 1.f - nd.y));
+    return S.K > 32 && d * d < 0.31f * S.L.horizon;
+}
+
 // One path per lane of the wavefront (has: the lane holds one), of node nd;
 // its moments are added to q, its steps to `steps`.
 template <int KIND, int TMODE, int CTL>
@@ -243,8 +344,6 @@ __device__ __forceinline__ void short_paths(const PathArgs &a, const MggArgs &c,
     constexpr bool MESH = CTL != CTL_NONE;
     const int32_t K = S.K;
     const uint32_t nlo = kM1 * nid;
-    const uint64_t rec = (uint64_t)out_row * a.n_paths + path;
-    NodeAcc *const accs[1] = {MESH ? c.acc_cv : a.acc};
     const PhiloxPath pp = philox_path(path, nid, S.key0);
     float xh = nd.x, xl = nd.xlo, yh = nd.y, yl = nd.ylo;
     float g[4] = {0.f, 0.f, 0.f, 0.f}, dbx = 0.f, dby = 0.f, mx = 0.f, my = 0.f;
@@ -377,40 +476,9 @@ __device__ __forceinline__ void short_paths(const PathArgs &a, const MggArgs &c,
         }
     }
     if (!has) return;
-    const bool out = !alive;
-    // ---- score (eq. (7b)) ---------------------------------------------------
-    Lane E = S.L;
-    E.xh = xh;
-    E.xl = xl;
-    E.yh = yh;
-    E.yl = yl;
-    E.px = nd.x;
-    E.py = nd.y;
-    E.k = k_end;
-    E.K = K;
-    float v[2];
-    score_path(a, E, out, v[0], v[1]);
-    if constexpr (MESH) {
-        mx = fmaf(g[0], dbx, fmaf(g[1], dby, mx));
-        my = fmaf(g[2], dbx, fmaf(g[3], dby, my));
-        const float sx0 = a.shift ? nd.x : 0.f, sy0 = a.shift ? nd.y : 0.f;
-        v[0] = (v[0] + sx0) - mx;
-        v[1] = (v[1] + sy0) - my;
-        if (c.cv_scores) c.cv_scores[rec] = make_float2(v[0], v[1]);
-    } else {
-        if (a.scores) a.scores[rec] = make_float2(v[0], v[1]);
-    }
-    if (a.exit_step) a.exit_step[rec] = out ? k_end : -1;
-    steps += (uint32_t)k_end;
-    // (a comparison per value: false for NaN, which a maximum would drop)
-    if (fabsf(v[0]) < kLdsBound && fabsf(v[1]) < kLdsBound) {
-        q[0] += (unsigned long long)q1_small(v[0]);
-        q[1] += (unsigned long long)q2_small(v[0]);
-        q[2] += (unsigned long long)q1_small(v[1]);
-        q[3] += (unsigned long long)q2_small(v[1]);
-    } else {
-        acc_direct<2>(accs, out_row, v, fabsf(v[0]) < kGlobalBound && fabsf(v[1]) < kGlobalBound);
-    }
+    mx = fmaf(g[0], dbx, fmaf(g[1], dby, mx));
+    my = fmaf(g[2], dbx, fmaf(g[3], dby, my));
+    short_score<CTL>(a, c, S, nd, out_row, path, xh, xl, yh, yl, k_end, !alive, mx, my, q, steps);
 }
 
 // A wavefront's sums into its node's: lane 2 v + h adds half h of sum v.
@@ -450,6 +518,12 @@ __global__ void __launch_bounds__(256, CTL == CTL_MESH ? 5 : 6) fk_short_path_ke
         }
         unsigned long long q[4] = {0ull, 0ull, 0ull, 0ull};
         uint32_t steps = 0;
+        if constexpr (CTL == CTL_NONE) {
+            if (__builtin_amdgcn_readfirstlane(short_leaves(S, nd))) {
+                short_refill<KIND, TMODE>(a, S, nd, out_row, nid, next, end, q, steps);
+                next = end;
+            }
+        }
         for (uint32_t p0 = next; p0 < end; p0 += 64)
             short_paths<KIND, TMODE, CTL>(a, c, S, nd, out_row, nid, ofs, nullptr, 0, 0, p0 + lane, p0 + lane < end, q,
                                           steps);

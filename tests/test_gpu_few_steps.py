@@ -21,13 +21,13 @@ def _density(fk, name):
     return fk.GridDensity(fk.fk_density_sample(W.two_bumps(W.TIME_FROZEN, 0.2), 0.2, 40))
 
 
-def _compare(fk, dens, t, K, last, n, data, plans):
+def _compare(fk, dens, t, K, last, n, data, plans, pts=None):
     import torch
-    dt = t / (K - 1 + last)
-    b = fk.FkBatch([(dens, t, data.t_init, _nodes(), 5)], data, dt, n, seed=77)
+    dt, pts = t / (K - 1 + last), _nodes() if pts is None else pts
+    b = fk.FkBatch([(dens, t, data.t_init, pts, 5)], data, dt, n, seed=77)
     ref = b.run(exit_step=True, scores=True)
     for plan in plans:
-        out = fk.fk_interface_solve(dens, data, _nodes(), t, dt, n, seed=77, level_id=5, exit_step=True, scores=True,
+        out = fk.fk_interface_solve(dens, data, pts, t, dt, n, seed=77, level_id=5, exit_step=True, scores=True,
                                     steps=True, plan=plan)
         torch.cuda.synchronize()
         for k in ("xi", "eta", "se_xi", "se_eta", "exit_step", "scores", "total_steps"):
@@ -51,3 +51,18 @@ def test_few_steps_form(fk, name, K, t, last, n):
 @pytest.mark.parametrize("K,t,last", [(1, 5e-4, 1.0), (20, 1e-3, 1.0), (19, 0.2, 0.3), (32, 0.1, 0.7)])
 def test_short_horizons_with_a_grid_density(fk, K, t, last):
     _compare(fk, _density(fk, "grid"), t, K, last, 130, W.Data(init_kind=W.DATA_SIN), (None, {"chunk": 1}))
+
+
+@pytest.mark.parametrize("name", ["const", "moving", "two_frozen", "ring", "grid"])
+@pytest.mark.parametrize("K,t,last,n", [(33, 0.05, 1.0, 2), (33, 0.01, 0.4, 63), (48, 0.02, 1.0, 64), (63, 0.05, 0.7, 65),
+                                        (64, 1e-3, 1.0, 300), (64, 0.05, 0.5, 2100)])
+def test_nodes_near_a_side(fk, name, K, t, last, n):
+    """Past 32 steps the short-horizon kernel lets the lanes of nodes near a side take other paths."""
+    p = W.uniform_points(24, seed=3)
+    d = np.sqrt(0.31 * t)
+    p[:8, 0] = np.linspace(0.0, 1.2 * d, 8)           # around the line where it begins to
+    p[8:16, 1] = 1.0 - np.linspace(0.0, 1.2 * d, 8)
+    p[16:20] = [(0.0, 0.0), (1.0, 0.5), (0.5, 1e-9), (d, 0.5)]
+    for data in (W.Data(t_init=0.1), W.Data(init_kind=W.DATA_SIN, bdry_kind=W.DATA_ZERO)):
+        _compare(fk, _density(fk, name), t, K, last, n, data, (None, {"chunk": 1}, {"chunk": 100, "block": 64},
+                                                              {"chunk": 2048}), p)
