@@ -203,12 +203,14 @@ int fk_plan_autotune(fk_plan_t p, const fk_density *w, const fk_data *d, const d
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(FK_E_NODEVICE, "no HIP device: %s", hipGetErrorString(e));
-    // the key: the device, and the problem's shape (not its values)
+    // the key: the device, and the problem's shape (not its values), with the
+    // kernel that takes it, which a step count alone does not tell
+    const bool lockstep = lockstep_paths(step_count(t, dt), t, d->score_mode);
     struct {
-        int32_t kind, time_mode, score_mode, init_kind, bdry_kind, masked;
+        int32_t kind, time_mode, score_mode, init_kind, bdry_kind, masked_lockstep;
         int64_t n_nodes, probe, K;
-    } shape{w->kind, w->time_mode, d->score_mode, d->init_kind, d->bdry_kind, mask ? 1 : 0, n_nodes, probe_paths,
-            (int64_t)step_count(t, dt)};
+    } shape{w->kind, w->time_mode, d->score_mode, d->init_kind, d->bdry_kind, (mask ? 1 : 0) + (lockstep ? 2 : 0),
+            n_nodes, probe_paths, (int64_t)step_count(t, dt)};
     char hex[32];
     std::snprintf(hex, sizeof hex, "%016llx", (unsigned long long)fnv1a(&shape, sizeof shape, 0xcbf29ce484222325ull));
     const std::string key = "solve/" + device_signature(dev) + "/" + hex;
@@ -222,7 +224,6 @@ int fk_plan_autotune(fk_plan_t p, const fk_density *w, const fk_data *d, const d
         return fail(FK_E_NOMEM, "hipMalloc of probe outputs: %s", hipGetErrorString(e));
     const bool expo = d->score_mode == FK_SCORE_EXPONENTIAL;
     const bool first = step_count(t, dt) <= 64 && !expo;
-    const bool lockstep = lockstep_paths(step_count(t, dt), t, d->score_mode);
     const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, false, 256)
                     : expo ? expo_kernel_max_blocks_per_cu(w->kind, w->time_mode, 256)
                          : path_kernel_max_blocks_per_cu(w->kind, w->time_mode, true,
