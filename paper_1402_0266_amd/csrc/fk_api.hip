@@ -374,6 +374,21 @@ MggForm mgg_form(int64_t K, double t, double u, bool bridge, int occ_pairs, int 
     return f;
 }
 
+// A grab is a wavefront's work from start to end, and two wavefronts per SIMD
+// fit: with fewer grabs than those some stay idle, and the last grabs decide.
+// Smaller ones cost where a path is little work (no evaluation after the start
+// and at most 32 steps).  Against 256 paths, 77 nodes: 400 paths (two grabs a
+// node) Dynkin form, 20 steps, stride 2: 32 paths 0.19, 64: 0.28, 128: 0.52, and
+// martingale form taken once: 64: 0.68; 4096 paths, stride 2: 64: 0.58; 1521
+// nodes x 400 paths, martingale form, 64 steps: 128: 0.85, 20 steps taken once:
+// 128: 1.11.  Many grabs (10689 nodes): all within 4%, so 256 there.
+int network_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked, bool heavy) {
+    if (masked) n_nodes = (n_nodes + 7) / 8;   // (as lockstep_chunk)
+    const int64_t grabs = n_nodes * ((n_paths + 255) / 256);
+    if (heavy) return grabs <= n_cu ? 32 : grabs <= 5LL * n_cu ? 64 : grabs < 16LL * n_cu ? 128 : 256;
+    return grabs <= n_cu ? 64 : grabs <= 2LL * n_cu ? 128 : 256;
+}
+
 int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu) {
     // 64 chunks per CU: at least eight per resident wavefront of the
     // network kernels (two waves per SIMD)

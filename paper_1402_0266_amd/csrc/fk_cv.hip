@@ -2076,15 +2076,16 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     const bool lockstep = (grid_ctl || base_at_start) && lockstep_paths(level.K, t, d->score_mode) &&
                           lockstep_mesh(table_fits(d, workspace_bytes, lay.total), d->grid_n, n_paths, stride, t,
                                         level.K, n_nodes, n_cu);
-    // network forms on short paths (a mesh step's sub-steps): 256 per grab
-    // by default (the network-control mesh step went from 29.9 to 22.6 ms on
-    // the 768-cell run against 128); the grid control keeps 128.  Larger
-    // grabs, which the plain kernel prefers there, cost these kernels 5%.
-    // Longer horizons: 32 to 128 by the path count, so that a solve with a
-    // few hundred paths per node still spreads over every wavefront (the
-    // Dynkin solve at 163 paths per node: 9.7 ms with 32, 11.7 with 128).
+    // Default grabs.  Few steps: the network forms by network_chunk (256 where
+    // nodes and paths are many: the network-control mesh step of the 768-cell
+    // run 22.6 ms against 29.9 with 128), 128 for the mesh's gradient in the
+    // refilling kernel.  Longer horizons: 32 to 128 by the path count, so that
+    // a solve with a few hundred paths per node still spreads over every
+    // wavefront.
     if ((!plan || plan->chunk == 0) && lockstep) pl.chunk = lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr);
-    else if ((!plan || plan->chunk == 0) && !grid_ctl && level.K <= 64) pl.chunk = 256;
+    else if ((!plan || plan->chunk == 0) && base_at_start && level.K <= 64) pl.chunk = 256;
+    else if ((!plan || plan->chunk == 0) && !grid_ctl && level.K <= 64)
+        pl.chunk = network_chunk(n_nodes, n_paths, n_cu, mask != nullptr, !mg || stride < level.K || level.K > 32);
     else if ((!plan || plan->chunk == 0) && level.K > 64) pl.chunk = few_paths_chunk(n_nodes, n_paths, n_cu);
     const int64_t cpn = (n_paths + pl.chunk - 1) / pl.chunk;
     hipError_t e;

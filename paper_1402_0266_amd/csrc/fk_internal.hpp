@@ -213,6 +213,9 @@ int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // the largest of 128, 64, 32 paths that leaves at least 64 chunks per CU
 // (few paths per node leave the grid part-empty with larger grabs).
 int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu);
+// Default grab of the network forms on few steps: 256 paths, or fewer where
+// that leaves few grabs.  heavy: a path is more than a start and at most 32 steps.
+int network_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked, bool heavy);
 // Resident workgroups per CU of the refilling path kernel by default (0: all
 // that fit).
 int long_blocks(int64_t steps, double paths_per_lane, int block);

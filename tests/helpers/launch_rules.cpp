@@ -3,6 +3,7 @@
 //   blocks steps per_lane block -> long_blocks
 //   lockstep K t mode            -> lockstep_paths
 //   mesh table grid_n paths stride t K nodes -> lockstep_mesh on 256 CUs
+//   network nodes paths masked heavy -> network_chunk on 256 CUs
 //   mgg K t u bridge            -> mgg_form where four and six workgroups fit: 10 pairs + blocks
 #include <hip/hip_runtime.h>
 
@@ -51,6 +52,8 @@ int main() {
         if (what == "mesh")
             r = lockstep_mesh(v.at(0) != 0.0, (int)v.at(1), (int64_t)v.at(2), (int64_t)v.at(3), v.at(4),
                               (int64_t)v.at(5), (int64_t)v.at(6), 256);
+        if (what == "network")
+            r = network_chunk((int64_t)v.at(0), (int64_t)v.at(1), 256, v.at(2) != 0.0, v.at(3) != 0.0);
         if (what == "mgg") {
             const MggForm f = mgg_form((int64_t)v.at(0), v.at(1), v.at(2), v.at(3) != 0.0, 4, 6);
             r = 10 * f.pairs + f.blocks;

@@ -72,3 +72,12 @@ def test_short_horizon_kernel_with_the_mesh_gradient(rules):
                (0, 768, 130, 2, 1e-3, 20, 10689), (0, 768, 2, 2, 1e-3, 32, 10689)) == [0] * 5
     assert rules("lockstep 32 3.0 0", "lockstep 64 0.05 2", "lockstep 64 0.06 0", "lockstep 65 0.001 0",
                  "lockstep 20 0.001 3", "lockstep 20 0.001 4") == [1, 1, 0, 0, 0, 0]
+
+
+def test_grabs_of_the_network_forms_on_few_steps(rules):
+    """256 paths a grab where that keeps every wavefront at work."""
+    assert rules("network 77 400 0 1", "network 77 1000 0 1", "network 77 4096 0 1", "network 1521 400 0 1",
+                 "network 10689 173 0 1", "network 1521 1000 0 1") == [32, 64, 64, 128, 256, 256]
+    assert rules("network 77 400 0 0", "network 77 1000 0 0", "network 77 4096 0 0", "network 1521 64 0 0") == \
+        [64, 128, 256, 256]
+    assert rules("network 616 400 1 1", "network 85512 173 1 1") == [32, 256]
