@@ -2214,6 +2214,11 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         // not evaluations, are most of the work: 2 / 3 per CU in ms, stride 100, 173
         // paths (1.3 to a lane at three) 4.76 / 5.38; stride 500, 696 paths 9.55 /
         // 10.12, 2952 paths (23) 33.9 / 32.6; stride 20, 696 paths 28.2 / 26.4.
+        // Three hold all paths but for a few: those start when the others end, so two
+        // (1521 nodes x 150 paths x 1000 steps over 0.01, 3.5 to a lane at one: 0.83
+        // of the time at three; over 0.1 0.9).
+        const double u = per_lane(1);
+        if (bpc == 0 && c.split == 0 && level.K > 64 && u > occ && u <= occ + 1.0) bpc = 2;
         if (bpc == 0 && level.K >= 4000 && stride >= 100 && per_lane(occ) <= 10.0) bpc = 2;
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
         if ((e = cv_dispatch<MgLaunchF>(w->kind, w->time_mode, uniform, a, c, cap_grid(n_cu * bpc, a.total_chunks, 256), stream)) != hipSuccess)
