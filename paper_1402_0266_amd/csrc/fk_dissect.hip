@@ -516,7 +516,7 @@ static hipError_t nd_launch(int ln, int T, const NdTree &t, const NdArgs &a, uns
     switch (16 * ln + T) {
         FK_ND(8, 1) FK_ND(8, 2) FK_ND(8, 3) FK_ND(8, 4) FK_ND(8, 5) FK_ND(8, 6) FK_ND(8, 7) FK_ND(8, 8)
         FK_ND(16, 1) FK_ND(16, 2) FK_ND(16, 3) FK_ND(16, 4) FK_ND(16, 5) FK_ND(16, 6) FK_ND(16, 7) FK_ND(16, 8) FK_ND(16, 9)
-        FK_ND(32, 2) FK_ND(32, 3) FK_ND(32, 4) FK_ND(32, 5) FK_ND(32, 6)
+        FK_ND(32, 5) FK_ND(32, 6)   // (1024 lanes only past 144)
     default: return hipErrorInvalidValue;
     }
 #undef FK_ND
