@@ -146,10 +146,8 @@ __device__ __forceinline__ PhiloxKeys philox_keys(uint32_t key0, uint32_t key1) 
 }
 
 // philox4x32_10(c0, c1, c2, c3, k0, k1) with P = philox_lane(c1, c2, c3, k0,
-// k1), K = philox_keys(k0, k1): bitwise the same four words.  flip: bits of
-// counter word 3 to invert (another stream of the same path).
-__device__ __forceinline__ PhiloxOut philox4x32_10_lane(uint32_t c0, const PhiloxLane &P, const PhiloxKeys &K,
-                                                        uint32_t flip = 0) {
+// k1), K = philox_keys(k0, k1): bitwise the same four words.
+__device__ __forceinline__ PhiloxOut philox4x32_10_lane(uint32_t c0, const PhiloxLane &P, const PhiloxKeys &K) {
     // round 1: words 0 and 1 of the result are fixed (folded into P)
     const uint64_t p0 = (uint64_t)kM0 * c0;
     const uint32_t x2 = (uint32_t)(p0 >> 32) ^ P.ck, x3 = (uint32_t)p0;
