@@ -134,20 +134,23 @@ typedef struct fk_data {
 } fk_data;
 
 /* Launch plan of the path kernel (see fk_plan_autotune).  Zero fields take defaults:
- * block 256; blocks_per_cu the kernel's occupancy, or less where
- * paths of many steps are few to a lane (the grid is cut to no more
- * wavefronts than there are chunks); chunk 128, or for horizons of at most 32
- * steps (64 if t <= 0.05) in fk_interface_solve and the mesh-gradient form of
- * fk_interface_solve_cv 64 r paths for the r that finishes first on a grid of
- * 24 wavefronts per CU; for other horizons of at most 64 steps: in
- * fk_interface_solve (and the plain pass of fk_interface_solve_cv)
- * the largest of 256, 512, 1024, 2048 that leaves at least 8 chunks per
- * resident wavefront (28 per CU), 256 with a node mask, and 256 in the network
- * forms of fk_interface_solve_cv; for longer horizons in the control-variate
- * passes of fk_interface_solve_cv, the largest of 128, 64, 32 that leaves at
- * least 64 chunks per CU; chunk at most 2048 (FK_E_INVAL beyond);
- * node_tile 1.  The plan changes speed
- * only: results depend on the counters alone. */
+ * block 256; blocks_per_cu the kernel's occupancy, or less where paths of many
+ * steps are few to a lane (the grid is cut to no more wavefronts than there
+ * are chunks); chunk 128, or for horizons of at most 32 steps (64 if t <=
+ * 0.05) in fk_interface_solve, and of at most 32 in the mesh-gradient form of
+ * fk_interface_solve_cv, 64 r paths for the r that finishes first on a grid of
+ * 24 wavefronts per CU; for other horizons of at most 64 steps in
+ * fk_interface_solve (and the plain pass of fk_interface_solve_cv) the largest
+ * of 256, 512, 1024, 2048 that leaves at least 8 chunks per resident wavefront
+ * (28 per CU), 256 with a node mask, and in the network forms of
+ * fk_interface_solve_cv 256, or 32 to 128 where that leaves few chunks; for
+ * longer horizons in the control-variate passes of fk_interface_solve_cv, the
+ * largest of 128, 64, 32 that leaves at least 64 chunks per CU; chunk at most
+ * 2048 (FK_E_INVAL beyond); node_tile 1.  The mesh-gradient form of
+ * fk_interface_solve_cv with many paths on a short horizon, which reads the
+ * mesh from LDS tiles, splits its paths by itself: there the plan is checked
+ * and not used.  The plan changes speed only: results depend on the counters
+ * alone. */
 typedef struct fk_plan {
     int32_t block;          /* threads per workgroup: 64, 128, 192 or 256 */
     int32_t blocks_per_cu;  /* resident workgroups per compute unit for the persistent grid */
@@ -163,7 +166,8 @@ typedef struct fk_plan {
  * for each candidate shape -- block 64 / 128 / 256 x chunk 32 / 128 / 512 x
  * full / half occupancy x node tile 1 / 8 -- and keeps the fastest in the
  * handle.  Results are cached per process by the device's signature and a
- * hash of the problem's shape (kinds, modes, node count, paths, steps); with
+ * hash of the problem's shape (kinds, modes, node count, paths, steps, and the
+ * kernel that takes them); with
  * the environment variable FK_TUNE_CACHE naming a file they also persist
  * there.  Synchronous; allocates and frees a probe output buffer.  Every
  * candidate gives the same result: the plan changes the schedule only.

@@ -306,8 +306,9 @@ int long_blocks(int64_t steps, double paths_per_lane, int block) {
 }
 
 // Fixed steps with the discrete exit test, at most 64 of them, and not so
-// long a horizon that lanes whose paths have left wait for most of it.  Both
-// kernels on 1521 nodes x 4096 paths of two bumps (refilling / lockstep, us):
+// long a horizon that lanes whose paths have left wait for most of it (nodes
+// near a side, whose paths leave at any horizon, are seen to by the kernel
+// itself: short_leaves, fk_short.hip).  Both kernels on 1521 nodes x 4096 paths of two bumps (refilling / lockstep, us):
 // 8 steps 332 / 119 at t = 1e-3, 326 / 105 at t = 0.3; 20 steps 369 / 231
 // and 338 / 214; 32 steps 492 / 354 and 348 / 322; 64 steps 874 / 680 at
 // t = 1e-3, 821 / 680 at t = 0.05 (a path takes 59% of the steps), 637 / 679
@@ -359,7 +360,7 @@ int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
 // 3.3: 1.08 / 1.18 / 0.72), and else on three (u = 7: 0.72 / 0.68 / 0.77; 1000
 // steps, u = 5.2, bridge: 1.24 / 1.13 / 1.20).
 MggForm mgg_form(int64_t K, double t, double u, bool bridge, int occ_pairs, int occ_other) {
-    const bool few_leave = t <= 0.03, held_by_other = few_leave && u > occ_pairs && u <= occ_other;
+    const bool few_leave = t <= 0.03, held_by_other = mgg_asks_occupancy(t, u) && u > occ_pairs && u <= occ_other;
     MggForm f{};
     f.pairs = bridge || ((K >= 1000 || (K >= 200 && u <= 20.0)) && !held_by_other);
     if (!f.pairs) {

@@ -2183,9 +2183,12 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         const auto mgg_occ = [&](bool pairs) {
             return cv_dispatch<MggOccF>(w->kind, w->time_mode, uniform, d->score_mode == FK_SCORE_BRIDGE, pairs);
         };
+        // (the two queries, ~2 us each, only where the rule reads their answers)
+        const double u = per_lane(1);
+        const bool fits = !lockstep && mgg_asks_occupancy(t, u);
         const MggForm form = lockstep ? MggForm{}
-                                      : mgg_form(level.K, t, per_lane(1), d->score_mode == FK_SCORE_BRIDGE,
-                                                 mgg_occ(true), mgg_occ(false));
+                                      : mgg_form(level.K, t, u, d->score_mode == FK_SCORE_BRIDGE,
+                                                 fits ? mgg_occ(true) : 0, fits ? mgg_occ(false) : 0);
         const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, true, 256)
                                  : mgg_occ(form.pairs);
         if (bpc == 0 && !lockstep) bpc = form.blocks;

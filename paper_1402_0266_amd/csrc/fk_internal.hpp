@@ -224,11 +224,13 @@ int long_blocks(int64_t steps, double paths_per_lane, int block);
 // (fk_mgg_path_kernel): steps in branch-free pairs or not, and the resident
 // workgroups per CU by default (0: all that fit).  K steps over t; u: paths to
 // a lane at one workgroup per CU (wavefronts of paths to a SIMD); with the
-// bridge test or not; workgroups per CU that fit in pairs and otherwise.
+// bridge test or not; workgroups per CU that fit in pairs and otherwise (0, 0
+// where mgg_asks_occupancy is false).
 struct MggForm {
     bool pairs;
     int blocks;
 };
+inline bool mgg_asks_occupancy(double t, double u) { return t <= 0.03 && u > 1.0 && u <= 8.0; }
 MggForm mgg_form(int64_t K, double t, double u, bool bridge, int occ_pairs, int occ_other);
 
 // Launch-plan tuning (fk_plan.hip): a 64-bit FNV-1a hash, the device's
