@@ -339,43 +339,41 @@ __global__ void __launch_bounds__(256, 5) fk_path_kernel(const PathArgs a) {
         }
         if (act == 0ull) break;
 
-        bool closed = false;      // the lane's path closed its chunk's slot
-        // ---- score (eq. (7b)) of an ended path, and the node's sums ------------
-        const auto path_end = [&](bool out) {
-            float v[2];
-            score_path(a, L, out, v[0], v[1]);
-            closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
-            my_steps += (uint32_t)L.k;      // the path's steps, counted once at its end
-            if (a.scores) a.scores[path_rec(L, a.n_paths)] = make_float2(v[0], v[1]);
-            if (a.exit_step) a.exit_step[path_rec(L, a.n_paths)] = out ? L.k : -1;
-        };
+        // ---- two steps, or step pairs until a path ends -------------------------
+        Pair p;
         uint64_t fin;             // the lanes whose path has ended
+        int with = 0;
+        bool out = false;
         if constexpr (FEW_STEPS) {
-            // ---- two steps ------------------------------------------------------
             bool end = false;
             if (__builtin_amdgcn_inverse_ballot_w64(act)) {
-                bool out = false;
                 float dbx = 0.f, dby = 0.f;
                 if (L.k < L.K) {
                     const PhiloxOut r = philox4x32_10_path((uint32_t)L.k >> 1, L.ctr3, pp, key0, key1);
                     out = two_steps<KIND, TMODE, UNIFORM>(L, r, dbx, dby);
                 }
                 end = out || L.k >= L.K;
-                if (end) path_end(out);
             }
             fin = ballot(end);
         } else {
-            // ---- step pairs, until a path ends ----------------------------------
-            Pair p;
             do {
                 fin = ballot(pair_step<KIND, TMODE, UNIFORM, BRIDGE>(L, P, keys, mask, p)) & act;
             } while (fin == 0ull);
-            const int with = pair_ends(L, P, p);
+            with = pair_ends(L, P, p);
             fin &= ballot(with != 0);
-            if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
-                path_end(pair_end<BRIDGE>(L, P, p, with));
-                pair_idle<BRIDGE>(L, P);
-            }
+        }
+
+        // ---- score (eq. (7b)) and the node's sums ------------------------------
+        bool closed = false;      // the lane's path closed its chunk's slot
+        if (__builtin_amdgcn_inverse_ballot_w64(fin)) {
+            if constexpr (!FEW_STEPS) out = pair_end<BRIDGE>(L, P, p, with);
+            float v[2];
+            score_path(a, L, out, v[0], v[1]);
+            closed = acc_path<2>(slots, accs, my_tag, L.out, v, (uint32_t)L.k);
+            my_steps += (uint32_t)L.k;      // the path's steps, counted once at its end
+            if (a.scores) a.scores[path_rec(L, a.n_paths)] = make_float2(v[0], v[1]);
+            if (a.exit_step) a.exit_step[path_rec(L, a.n_paths)] = out ? L.k : -1;
+            if constexpr (!FEW_STEPS) pair_idle<BRIDGE>(L, P);
         }
         act &= ~fin;
         if (ballot(closed) != 0ull) slots_collect<2>(slots, accs, lane);
