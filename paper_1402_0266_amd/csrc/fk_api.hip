@@ -453,7 +453,8 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     a.tile_shift = (uint32_t)__builtin_ctz((unsigned)S.plan.node_tile);
     int bpc = S.plan.blocks_per_cu;
     const bool expo = a.score_mode == FK_SCORE_EXPONENTIAL;
-    const int occ = S.lockstep ? short_kernel_max_blocks_per_cu(S.kind, S.time_mode, false, S.plan.block)
+    const bool refill = S.lockstep && lockstep_refill(S.steps, S.n_nodes, S.n_paths, n_cu, a.masked != 0);
+    const int occ = S.lockstep ? short_kernel_max_blocks_per_cu(S.kind, S.time_mode, false, refill, S.plan.block)
                     : expo     ? expo_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.plan.block)
                                : path_kernel_max_blocks_per_cu(S.kind, S.time_mode, S.uniform,
                                                                a.score_mode == FK_SCORE_BRIDGE, S.few_steps,
@@ -464,7 +465,7 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
     if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
     const int grid = cap_grid(n_cu * bpc, a.total_chunks, S.plan.block);
     if ((e = timing_mark(timed, 0, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    e = S.lockstep ? launch_short_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
+    e = S.lockstep ? launch_short_paths(S.kind, S.time_mode, refill, a, grid, S.plan.block, stream)
         : expo     ? launch_expo_paths(S.kind, S.time_mode, a, grid, S.plan.block, stream)
                    : launch_paths(S.kind, S.time_mode, S.uniform, S.few_steps, a, grid, S.plan.block, stream);
     if (e != hipSuccess) return hip_fail(e, "path kernel launch");

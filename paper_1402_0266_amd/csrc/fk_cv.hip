@@ -2189,7 +2189,7 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         const MggForm form = lockstep ? MggForm{}
                                       : mgg_form(level.K, t, u, d->score_mode == FK_SCORE_BRIDGE,
                                                  fits ? mgg_occ(true) : 0, fits ? mgg_occ(false) : 0);
-        const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, true, 256)
+        const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, true, false, 256)
                                  : mgg_occ(form.pairs);
         if (bpc == 0 && !lockstep) bpc = form.blocks;
         if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;

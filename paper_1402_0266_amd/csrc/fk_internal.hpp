@@ -206,6 +206,14 @@ bool lockstep_paths(int64_t K, double t, int score_mode);
 // 2.1 times as long as in the refilling kernel, 130 paths x 32 steps 1.27.
 bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes,
                    int n_cu);
+// Whether nodes near a side have its lanes take other paths (short_refill):
+// past 32 steps, and where the rounds of 64 paths are more than the wavefronts
+// that fit (below that the time is a wavefront's, whose lanes then wait for
+// nothing; registers and code for it cost every launch up to 2 us).  1521 nodes within 0.001 to
+// 0.5 of a side, 33 to 64 steps, time in lockstep over the refilling kernel's:
+// up to 256 paths 0.26 - 0.83, 320 and 500 up to 1.09, 2000 1.36, 4096 1.76; 77
+// nodes: 4096 paths 0.70, 16384 1.33.
+bool lockstep_refill(int64_t K, int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // Its default chunk: 64 r paths for the r that finishes first when every
 // resident wavefront takes an equal number of chunks.
 int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
@@ -278,10 +286,11 @@ hipError_t launch_tables(const TableArgs &t, hipStream_t s);
 hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_steps, hipStream_t s);
 // The short-horizon path kernel; with the mesh-gradient control (horizon t in
 // K steps; a's chunks and `grid` hold where the mesh is read from memory).
-hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, int grid, int block, hipStream_t s);
+hipError_t launch_short_paths(int kind, int time_mode, bool refill, const PathArgs &a, int grid, int block,
+                              hipStream_t s);
 hipError_t launch_short_mesh_paths(int kind, int time_mode, const PathArgs &a, const MggArgs &c, double t, int64_t K,
                                    int64_t n_nodes, int n_cu, int grid, int block, hipStream_t s);
-int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, int block);
+int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, bool refill, int block);
 // Zeroes a launch's 64 counter words and sets counters[kCtrTotal] (host tables).
 hipError_t launch_counters_init(uint32_t *counters, uint32_t total_chunks, hipStream_t s);
 // Bytes of the per-node estimator sums of n_out rows.

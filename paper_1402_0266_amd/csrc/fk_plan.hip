@@ -224,7 +224,7 @@ int fk_plan_autotune(fk_plan_t p, const fk_density *w, const fk_data *d, const d
         return fail(FK_E_NOMEM, "hipMalloc of probe outputs: %s", hipGetErrorString(e));
     const bool expo = d->score_mode == FK_SCORE_EXPONENTIAL;
     const bool first = step_count(t, dt) <= 64 && !expo;
-    const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, false, 256)
+    const int occ = lockstep ? short_kernel_max_blocks_per_cu(w->kind, w->time_mode, false, false, 256)
                     : expo ? expo_kernel_max_blocks_per_cu(w->kind, w->time_mode, 256)
                          : path_kernel_max_blocks_per_cu(w->kind, w->time_mode, true,
                                                          d->score_mode == FK_SCORE_BRIDGE, first, 256);

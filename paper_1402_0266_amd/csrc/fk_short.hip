@@ -23,12 +23,12 @@
 // branch (as pair_step, fk_pathstep.hpp); after the first exit, and for the
 // pair with the last step, lane by lane under a mask.
 //
-// Past 32 steps a node so near a side that most of its paths leave early
-// (short_leaves) has its lanes take other paths instead (short_refill): 1521
-// nodes within 0.02 of a side x 4096 paths x 64 steps over 0.05: 680 us in
-// lockstep, 391 in the refilling kernel, 242 here.  With the mesh's gradient,
-// which has more to fetch for every path, that stays behind the refilling
-// kernel, which takes those horizons.
+// Past 32 steps, and with more paths than fit at once (lockstep_refill), a node
+// so near a side that most of its paths leave early (short_leaves) has its
+// lanes take other paths instead (short_refill): 1521 nodes within 0.02 of a
+// side x 4096 paths x 64 steps over 0.05: 680 us in lockstep, 391 in the
+// refilling kernel, 242 here.  That takes 5 registers more, and a wavefront per
+// SIMD with some densities, so it is a form of its own.
 //
 // Measured (two bumps frozen, 10689 nodes x 16384 paths x 20 steps): 5.8 ms
 // (6.1 with the masked loop alone) against the refilling kernel's 9.7 ms when
@@ -147,8 +147,9 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
 
 // What a path's control needs: nothing (the plain estimate), the mesh's
 // gradient (as fk_mgg_path_kernel, fk_cv.hip) from memory, or the same from
-// the node's tile of the mesh in LDS.
-enum { CTL_NONE = 0, CTL_MESH = 1, CTL_TILE = 2 };
+// the node's tile of the mesh in LDS.  CTL_REFILL: nothing, and nodes near a
+// side by short_refill.
+enum { CTL_NONE = 0, CTL_MESH = 1, CTL_TILE = 2, CTL_REFILL = 3 };
 
 // The launch's constants of a wavefront.
 struct ShortWave {
@@ -326,11 +327,10 @@ __device__ __forceinline__ void short_refill(const PathArgs &a, const ShortWave 
 
 // Whether most of a node's paths leave early: it lies within 0.56 sqrt(t) of a
 // side, where a path takes half of its steps on average (the integral of
-// erf(d / (2 sqrt(s))) over s), and there are enough steps for what the lanes
-// save to pay for taking other paths.
+// erf(d / (2 sqrt(s))) over s).
 __device__ __forceinline__ bool short_leaves(const ShortWave &S, const NodeDev &nd) {
     const float d = fminf(fminf(nd.x, 1.f - nd.x), fminf(nd.y, 1.f - nd.y));
-    return S.K > 32 && d * d < 0.31f * S.L.horizon;
+    return d * d < 0.31f * S.L.horizon;
 }
 
 // One path per lane of the wavefront (has: the lane holds one), of node nd;
@@ -495,8 +495,9 @@ __device__ __forceinline__ void short_sums(NodeAcc &A, const unsigned long long 
     if (lane < 9u && add != 0ull) atomicAdd(lane == 8u ? &A.steps : &A.sum[lane >> 1][lane & 1u], add);
 }
 
-template <int KIND, int TMODE, int CTL>
-__global__ void __launch_bounds__(256, CTL == CTL_MESH ? 5 : 6) fk_short_path_kernel(const PathArgs a, const MggArgs c) {
+template <int KIND, int TMODE, int FORM>
+__global__ void __launch_bounds__(256, FORM == CTL_MESH ? 5 : 6) fk_short_path_kernel(const PathArgs a, const MggArgs c) {
+    constexpr int CTL = FORM == CTL_REFILL ? CTL_NONE : FORM;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t total = a.masked ? __builtin_amdgcn_readfirstlane(a.queue[kCtrActive]) * a.cpn : a.total_chunks;
@@ -518,8 +519,9 @@ __global__ void __launch_bounds__(256, CTL == CTL_MESH ? 5 : 6) fk_short_path_ke
         }
         unsigned long long q[4] = {0ull, 0ull, 0ull, 0ull};
         uint32_t steps = 0;
-        if constexpr (CTL == CTL_NONE) {
-            if (__builtin_amdgcn_readfirstlane(short_leaves(S, nd))) {
+        if constexpr (FORM == CTL_REFILL) {
+            // (a chunk of one round has no other paths to take)
+            if (end - next > 64u && __builtin_amdgcn_readfirstlane(short_leaves(S, nd))) {
                 short_refill<KIND, TMODE>(a, S, nd, out_row, nid, next, end, q, steps);
                 next = end;
             }
@@ -588,7 +590,7 @@ template <int K, int T, int C>
 struct ShortOccF {
     static int run(int block) {
         int nb = 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_short_path_kernel<K, T, C == CTL_NONE ? C : CTL_MESH>,
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk_short_path_kernel<K, T, C == CTL_TILE ? CTL_MESH : C>,
                                                             block, 0) == hipSuccess
                    ? nb
                    : 0;
@@ -599,9 +601,10 @@ template <template <int, int, int> class F, typename... Args>
 auto short_dispatch(int kind, int time_mode, int ctl, Args &&...args) {
     const bool frozen = (time_mode == TIME_FROZEN);
 #define FK_SHORT(K, T)                                                                  \
-    return ctl == CTL_TILE   ? F<K, T, CTL_TILE>::run(std::forward<Args>(args)...)      \
-           : ctl == CTL_MESH ? F<K, T, CTL_MESH>::run(std::forward<Args>(args)...)      \
-                             : F<K, T, CTL_NONE>::run(std::forward<Args>(args)...)
+    return ctl == CTL_TILE     ? F<K, T, CTL_TILE>::run(std::forward<Args>(args)...)    \
+           : ctl == CTL_MESH   ? F<K, T, CTL_MESH>::run(std::forward<Args>(args)...)    \
+           : ctl == CTL_REFILL ? F<K, T, CTL_REFILL>::run(std::forward<Args>(args)...)  \
+                               : F<K, T, CTL_NONE>::run(std::forward<Args>(args)...)
     switch (kind) {
     case KIND_CONST: FK_SHORT(KIND_CONST, TIME_BACKWARD);
     case KIND_BUMP: FK_SHORT(KIND_BUMP, TIME_BACKWARD);
@@ -652,8 +655,14 @@ bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, doub
     return K <= 32 && ((table && t <= 0.02) || tile_chunk(grid_n, n_paths, stride, t, K, n_nodes, n_cu) != 0);
 }
 
-hipError_t launch_short_paths(int kind, int time_mode, const PathArgs &a, int grid, int block, hipStream_t s) {
-    return short_dispatch<ShortLaunchF>(kind, time_mode, CTL_NONE, a, MggArgs{}, grid, block, s);
+bool lockstep_refill(int64_t K, int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
+    if (masked) n_nodes = (n_nodes + 7) / 8;   // (as lockstep_chunk)
+    return K > 32 && n_nodes * ((n_paths + 63) / 64) > 24LL * n_cu;
+}
+
+hipError_t launch_short_paths(int kind, int time_mode, bool refill, const PathArgs &a, int grid, int block,
+                              hipStream_t s) {
+    return short_dispatch<ShortLaunchF>(kind, time_mode, refill ? CTL_REFILL : CTL_NONE, a, MggArgs{}, grid, block, s);
 }
 
 hipError_t launch_short_mesh_paths(int kind, int time_mode, const PathArgs &a, const MggArgs &c, double t, int64_t K,
@@ -669,8 +678,8 @@ hipError_t launch_short_mesh_paths(int kind, int time_mode, const PathArgs &a, c
                                         1024, s);
 }
 
-int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, int block) {
-    return short_dispatch<ShortOccF>(kind, time_mode, mesh ? CTL_MESH : CTL_NONE, block);
+int short_kernel_max_blocks_per_cu(int kind, int time_mode, bool mesh, bool refill, int block) {
+    return short_dispatch<ShortOccF>(kind, time_mode, mesh ? CTL_MESH : refill ? CTL_REFILL : CTL_NONE, block);
 }
 
 }  // namespace fk

@@ -53,16 +53,30 @@ def test_short_horizons_with_a_grid_density(fk, K, t, last):
     _compare(fk, _density(fk, "grid"), t, K, last, 130, W.Data(init_kind=W.DATA_SIN), (None, {"chunk": 1}))
 
 
+def _near_sides(t):
+    p = W.uniform_points(24, seed=3)
+    d = np.sqrt(0.31 * t)
+    p[:8, 0] = np.linspace(0.0, 1.2 * d, 8)           # around the line from which lanes take other paths
+    p[8:16, 1] = 1.0 - np.linspace(0.0, 1.2 * d, 8)
+    p[16:20] = [(0.0, 0.0), (1.0, 0.5), (0.5, 1e-9), (d, 0.5)]
+    return p
+
+
 @pytest.mark.parametrize("name", ["const", "moving", "two_frozen", "ring", "grid"])
 @pytest.mark.parametrize("K,t,last,n", [(33, 0.05, 1.0, 2), (33, 0.01, 0.4, 63), (48, 0.02, 1.0, 64), (63, 0.05, 0.7, 65),
                                         (64, 1e-3, 1.0, 300), (64, 0.05, 0.5, 2100)])
 def test_nodes_near_a_side(fk, name, K, t, last, n):
-    """Past 32 steps the short-horizon kernel lets the lanes of nodes near a side take other paths."""
-    p = W.uniform_points(24, seed=3)
-    d = np.sqrt(0.31 * t)
-    p[:8, 0] = np.linspace(0.0, 1.2 * d, 8)           # around the line where it begins to
-    p[8:16, 1] = 1.0 - np.linspace(0.0, 1.2 * d, 8)
-    p[16:20] = [(0.0, 0.0), (1.0, 0.5), (0.5, 1e-9), (d, 0.5)]
+    p = _near_sides(t)
     for data in (W.Data(t_init=0.1), W.Data(init_kind=W.DATA_SIN, bdry_kind=W.DATA_ZERO)):
         _compare(fk, _density(fk, name), t, K, last, n, data, (None, {"chunk": 1}, {"chunk": 100, "block": 64},
                                                               {"chunk": 2048}), p)
+
+
+@pytest.mark.parametrize("name", ["const", "moving", "two_frozen", "ring", "grid"])
+@pytest.mark.parametrize("K,t,last,n", [(33, 0.05, 1.0, 16385), (64, 0.05, 0.5, 16385), (64, 1e-3, 1.0, 16450),
+                                        (48, 0.02, 1.0, 16384), (32, 0.05, 1.0, 16450)])
+def test_nodes_near_a_side_with_many_paths(fk, name, K, t, last, n):
+    """Past 32 steps, with more rounds of 64 paths than wavefronts fit (24 nodes x 256 on this GPU), the
+    short-horizon kernel lets the lanes of nodes near a side take other paths of a chunk."""
+    _compare(fk, _density(fk, name), t, K, last, n, W.Data(init_kind=W.DATA_SIN, bdry_kind=W.DATA_ZERO),
+             (None, {"chunk": 64}, {"chunk": 65}, {"chunk": 1000, "block": 64}, {"chunk": 2048}), _near_sides(t))
