@@ -2075,7 +2075,7 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
     // the mesh-gradient control over a short horizon
     const bool lockstep = (grid_ctl || base_at_start) && lockstep_paths(level.K, t, d->score_mode) &&
                           lockstep_mesh(table_fits(d, workspace_bytes, lay.total), d->grid_n, n_paths, stride, t,
-                                        level.K, n_nodes, n_cu);
+                                        level.K, n_nodes, n_cu, mask != nullptr);
     // Default grabs.  Few steps: the network forms by network_chunk (256 where
     // nodes and paths are many: the network-control mesh step of the 768-cell
     // run 22.6 ms against 29.9 with 128), 128 for the mesh's gradient in the

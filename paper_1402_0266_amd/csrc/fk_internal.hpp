@@ -195,17 +195,23 @@ int check_chunks(int64_t n_nodes, int64_t n_paths, const fk_plan &pl);
 int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // Whether a solve takes the short-horizon kernel (fk_short.hip).
 bool lockstep_paths(int64_t K, double t, int score_mode);
-// Whether it does with the mesh-gradient control (as well): at most 32 steps,
-// and with the gradient table over at most t = 0.02, or from an LDS tile.  Past 32
-// steps nodes near a side make the lanes wait for paths that have left (1521 nodes
-// within 0.02 of a side x 4096 paths x 64 steps: 1.5 times the refilling
-// kernel's time, elsewhere 0.6); paths that spread over hundreds of cells miss the
-// caches together (768 cells, 32 steps over 0.05: 1.2).  From the grids themselves (a workspace without room for the
-// table) a gradient is eight gathers instead of two, and the lanes of one node's paths, all
-// at the same step, wait for them together: 10689 nodes x 2 paths x 64 steps took
-// 2.1 times as long as in the refilling kernel, 130 paths x 32 steps 1.27.
+// Whether it does with the mesh-gradient control (as well).  Its lanes do not
+// take other paths, and all gather at the same step, one node's paths from
+// the same few cells.  From an LDS tile of the mesh it does up to 32 steps.
+// Otherwise, its time over the refilling kernel's (stride 2 unless stated, nodes
+// over the square and within 0.001 to 0.1 of a side):
+//  * from the gradient table, at most 32 steps: 0.2 - 0.96; 32 steps with
+//    16 gathers and paths spread beyond 100 cells 1.05 - 1.2 (768 cells, 10689 nodes
+//    x 500 paths, 1521 x 4096);
+//  * from the grids (a workspace without room for the table: eight gathers instead
+//    of two), at most 32 steps: at most five gathers 0.15 - 0.96; more, up to 12 rounds of 64
+//    paths to a SIMD 0.5 - 0.97, up to 48 with 20 steps or 8 gathers 0.4 - 0.99,
+//    otherwise 1.14; beyond that 0.3 - 0.9 on small grids, on 768 cells 0.8 - 1.45;
+//  * 33 to 64 steps: up to 12 rounds 0.3 - 0.97 (from the grids of 768 cells, 10689
+//    nodes x 2 paths, 1.06 - 2.1), up to 48 with one gather, or 16 from the table,
+//    0.25 - 0.97, beyond that up to 1.65 near a side.
 bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes,
-                   int n_cu);
+                   int n_cu, bool masked);
 // Whether nodes near a side have its lanes take other paths (short_refill):
 // past 32 steps, and where the rounds of 64 paths are more than the wavefronts
 // that fit (below that the time is a wavefront's, whose lanes then wait for

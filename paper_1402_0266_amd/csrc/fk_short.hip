@@ -651,8 +651,19 @@ uint32_t tile_chunk(int grid_n, int64_t n_paths, int64_t stride, double t, int64
 }  // namespace
 
 bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes,
-                   int n_cu) {
-    return K <= 32 && ((table && t <= 0.02) || tile_chunk(grid_n, n_paths, stride, t, K, n_nodes, n_cu) != 0);
+                   int n_cu, bool masked) {
+    if (K <= 32 && tile_chunk(grid_n, n_paths, stride, t, K, n_nodes, n_cu) != 0) return true;
+    if (masked) n_nodes = (n_nodes + 7) / 8;   // (as lockstep_chunk)
+    const int64_t gathers = stride < K ? (K + stride - 1) / stride : 1;      // of a path
+    const double rounds = (double)n_nodes * (double)((n_paths + 63) / 64) / (4.0 * n_cu);   // of 64 paths, to a SIMD
+    const double spread = std::sqrt(2.0 * t) * grid_n;   // standard deviation of the paths, in cells
+    const double many = 48.0, few = 12.0;
+    if (K > 32)
+        return rounds <= (gathers == 1 || (table && gathers <= 16) ? many : few) &&
+               (table || grid_n <= 256 || gathers <= 16);
+    if (gathers <= 5) return true;
+    if (table) return K <= 20 || gathers <= 8 || rounds <= many || spread <= 100.0;
+    return rounds <= (K <= 20 || gathers <= 8 ? many : few) || grid_n < kTile || (grid_n <= 256 && spread <= 60.0);
 }
 
 bool lockstep_refill(int64_t K, int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {

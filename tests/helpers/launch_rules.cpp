@@ -51,7 +51,7 @@ int main() {
         if (what == "lockstep") r = lockstep_paths((int64_t)v.at(0), v.at(1), (int)v.at(2));
         if (what == "mesh")
             r = lockstep_mesh(v.at(0) != 0.0, (int)v.at(1), (int64_t)v.at(2), (int64_t)v.at(3), v.at(4),
-                              (int64_t)v.at(5), (int64_t)v.at(6), 256);
+                              (int64_t)v.at(5), (int64_t)v.at(6), 256, false);
         if (what == "network")
             r = network_chunk((int64_t)v.at(0), (int64_t)v.at(1), 256, v.at(2) != 0.0, v.at(3) != 0.0);
         if (what == "mgg") {

@@ -62,14 +62,24 @@ def test_form_of_the_mesh_gradient_control(rules):
 
 
 def test_short_horizon_kernel_with_the_mesh_gradient(rules):
-    """From the table or an LDS tile only, and up to 32 steps."""
+    """Where its lanes neither wait for paths that have left nor for gathers that miss the caches."""
     ask = lambda *a: rules(*("mesh " + " ".join(str(v) for v in q) for q in a))
     #       table, grid, paths, stride, t, K, nodes
     assert ask((1, 768, 16384, 2, 5e-4, 20, 10689), (1, 40, 130, 2, 1e-3, 32, 77), (0, 768, 16384, 2, 5e-4, 20, 10689),
-               (0, 64, 4096, 2, 0.05, 32, 1521)) == [1] * 4
-    # past 32 steps; paths spread over hundreds of cells; the grids themselves from memory
-    assert ask((1, 768, 16384, 2, 5e-4, 33, 10689), (0, 64, 4096, 2, 0.05, 64, 1521), (1, 768, 64, 2, 0.05, 32, 1521),
-               (0, 768, 130, 2, 1e-3, 20, 10689), (0, 768, 2, 2, 1e-3, 32, 10689)) == [0] * 5
+               (0, 64, 4096, 2, 0.05, 32, 1521), (1, 768, 64, 2, 0.05, 32, 1521), (1, 768, 4096, 2, 1e-3, 32, 10689)) == \
+        [1] * 6
+    # one gather, at the start
+    assert ask((0, 768, 4096, 1 << 30, 0.1, 32, 10689), (0, 768, 4096, 32, 0.1, 32, 10689),
+               (0, 768, 256, 64, 0.05, 64, 10689), (0, 768, 320, 64, 0.05, 64, 10689)) == [1, 1, 1, 0]
+    # past 32 steps: where all paths are under way at once
+    assert ask((1, 768, 64, 2, 0.05, 64, 10689), (1, 768, 65, 2, 0.05, 64, 10689), (0, 256, 500, 2, 0.05, 64, 1521),
+               (0, 768, 2, 2, 1e-3, 64, 10689), (0, 768, 64, 4, 0.05, 64, 10689), (0, 40, 4096, 2, 0.05, 33, 1521),
+               (1, 768, 130, 4, 0.05, 64, 10689), (0, 768, 130, 4, 0.05, 64, 10689)) == [1, 0, 1, 0, 1, 0, 1, 0]
+    # paths spread over hundreds of cells; the grids themselves from memory
+    assert ask((1, 768, 4096, 2, 0.05, 32, 1521), (1, 768, 4096, 4, 0.05, 32, 1521), (0, 768, 130, 2, 1e-3, 32, 10689),
+               (0, 768, 130, 4, 1e-3, 32, 10689), (0, 768, 130, 2, 1e-3, 20, 10689), (0, 768, 500, 2, 1e-3, 20, 10689),
+               (0, 768, 2, 2, 1e-3, 32, 10689), (0, 256, 130, 2, 1e-3, 32, 10689), (0, 256, 4096, 2, 0.05, 32, 1521)) == \
+        [0, 1, 0, 1, 1, 0, 1, 1, 0]
     assert rules("lockstep 32 3.0 0", "lockstep 64 0.05 2", "lockstep 64 0.06 0", "lockstep 65 0.001 0",
                  "lockstep 20 0.001 3", "lockstep 20 0.001 4") == [1, 1, 0, 0, 0, 0]
 
