@@ -340,10 +340,10 @@ int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
 // wavefronts per SIMD fit instead of five or six.  Measured against the form
 // with a branch after each step (its time 1; two bumps and moving bump, 41 to
 // 768 cells):
-//  * 65 to 100 steps: 0.85 - 0.98 with few paths, up to 1.25 where many paths
-//    end all the time (10689 nodes x 500 paths), so not below 200 steps; 200
-//    and 400 steps: 0.87 and 0.82 up to 16 wavefronts of paths to a SIMD, up to
-//    1.17 and 1.12 at 80; from 1000 steps on 0.6 - 0.8.
+//  * 65 to 199 steps: 0.48 - 1.02 up to 12 wavefronts of paths to a SIMD, up to
+//    1.25 where many paths end all the time (10689 nodes x 500 paths); 200
+//    and 400 steps: 0.87 and 0.82 up to 16 wavefronts, up to 1.17 and 1.12 at
+//    80; from 1000 steps on 0.6 - 0.8; 33 to 64 steps 0.9 - 1.08.
 //  * where few paths leave before the horizon, all that are started together
 //    end together, and where only the other form holds them all at once it is
 //    faster: 1.0 - 1.37 over t = 0.01 at four to six wavefronts of paths to a
@@ -362,7 +362,7 @@ int lockstep_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
 MggForm mgg_form(int64_t K, double t, double u, bool bridge, int occ_pairs, int occ_other) {
     const bool few_leave = t <= 0.03, held_by_other = mgg_asks_occupancy(t, u) && u > occ_pairs && u <= occ_other;
     MggForm f{};
-    f.pairs = bridge || ((K >= 1000 || (K >= 200 && u <= 20.0)) && !held_by_other);
+    f.pairs = bridge || ((K >= 1000 || (K >= 200 && u <= 20.0) || (K > 64 && u <= 12.0)) && !held_by_other);
     if (!f.pairs) {
         if (held_by_other) f.blocks = (int)std::ceil(u);
     } else if (few_leave && K >= 4000) {

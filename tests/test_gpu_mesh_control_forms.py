@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("score", [W.SCORE_EXTEND, W.SCORE_BRIDGE])
 @pytest.mark.parametrize("K,t,last,stride,few,many", [
+    (65, 0.2, 0.7, 2, 70, 48000),
     (200, 0.1, 1.0, 2, 70, 48000),         # pairs at few paths, branches at many
     (301, 0.02, 0.4, 20, 70, 48000),
     (1000, 0.01, 1.0, 1 << 20, 70, 10000),  # branches where all paths are held at once by that form only

@@ -48,11 +48,11 @@ def test_form_of_the_mesh_gradient_control(rules):
     """Branch-free pairs only where they were not slower than a branch after each step."""
     ask = lambda *a, b=0: [divmod(v, 10) for v in rules(*(f"mgg {K} {t} {u} {b}" for K, t, u in a))]
     # few steps; many paths that end all the time
-    assert ask((33, 0.3, 1), (100, 0.1, 5), (100, 0.01, 200), (199, 0.1, 1), (400, 0.1, 82), (999, 0.1, 20.5)) == [(0, 0)] * 6
+    assert ask((33, 0.3, 1), (64, 0.1, 5), (100, 0.01, 200), (199, 0.1, 13), (400, 0.1, 82), (999, 0.1, 20.5)) == [(0, 0)] * 6
     # all paths held at once by the other form only, and few leaving
     assert ask((64, 1e-3, 4.5), (400, 0.01, 5.2), (1000, 0.01, 5.9), (4000, 0.03, 4.1), (10000, 1e-3, 6.0)) == \
         [(0, 5), (0, 6), (0, 6), (0, 5), (0, 6)]
-    assert ask((200, 0.1, 12), (1000, 0.1, 82), (1000, 0.1, 5.2), (2000, 0.01, 3.9), (3999, 0.01, 7)) == [(1, 0)] * 5
+    assert ask((65, 0.1, 12), (1000, 0.1, 82), (1000, 0.1, 5.2), (2000, 0.01, 3.9), (3999, 0.01, 7)) == [(1, 0)] * 5
     # long horizons: on as many workgroups as hold the paths
     assert ask((4000, 0.01, 1.5), (4000, 0.01, 2.4), (10000, 0.01, 3.6), (4000, 0.01, 7), (10000, 0.1, 6),
                (10000, 0.1, 40)) == [(1, 2), (1, 3), (1, 4), (1, 3), (1, 2), (1, 3)]
