@@ -41,14 +41,20 @@ __device__ __forceinline__ void comp_add(float &hi, float &lo, float inc) {
     hi = s;
 }
 
-// Outside the closed unit square: -x, -y, x - 1 or y - 1 positive.  hi is the
-// rounded position; (hi - 1) is exact near 1, so the tests against 1 see the
-// lo part too.  The maximum drops NaN: a position that is not a number (a
+// Outside the closed unit square: x, y, 1 - x or 1 - y negative.  hi is the
+// rounded position; (1 - hi) is exact near 1, so the tests against 1 see the
+// lo part too.  The minimum drops NaN: a position that is not a number (a
 // grid density's drift, or an analytic one's beyond FP32's range) is outside
-// only where its other coordinate is.  (The sign bits of x, y, 1 - x and 1 - y
-// take two cheaper instructions, but a NaN has a sign bit too.)
+// only where its other coordinate is.  (The sign bits take cheaper
+// instructions, but a NaN has a sign bit too.)  Written out: fminf, fmaxf or
+// four comparisons here made the compiler order the loops around it differently
+// (16 levels of up to 200 to 1100 steps 2% slower).
 __device__ __forceinline__ bool outside(float xh, float xl, float yh, float yl) {
-    return fmaxf(fmaxf(-xh, -yh), fmaxf((xh - 1.f) + xl, (yh - 1.f) + yl)) > 0.f;
+    const float x1 = (1.f - xh) - xl, y1 = (1.f - yh) - yl;
+    float m;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(xh), "v"(yh), "v"(x1));
+    asm("v_min_f32 %0, %0, %1" : "+v"(m) : "v"(y1));
+    return m < 0.f;
 }
 
 // One Euler-Maruyama step of length D (cb = -4 ln2 D) of the position with
