@@ -220,6 +220,7 @@ int build_tables(const LevelSpec *lv, int n_levels, const double *pts, int64_t n
         const double K = T.levels[(size_t)l].K;
         steps += (double)lv[l].n_nodes * K;
         steps2 += (double)lv[l].n_nodes * K * K;
+        if (lv[l].n_nodes > 0) T.longest = std::max(T.longest, (int64_t)K);
     }
     T.steps = steps > 0.0 ? (int64_t)(steps2 / steps) : 0;
     for (int64_t g = 0; g < n_total; ++g)
@@ -296,11 +297,15 @@ int short_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked) {
 // - / 618; 2000 steps 8.30 / 8.02 / 8.05; 500 steps 2.58 / 2.60 / 2.80; 200 steps
 // 1.33 / 1.40 / 1.53.  16 levels of up to 1600 steps 3.94 / 3.85 / 3.98, up to
 // 500 steps 1.63 / 1.66 / 1.83.  Several levels go by the steps of the level
-// in which a step of the launch is taken on average: one long level of a few nodes among
-// short ones leaves the short ones' paths to fill the chip (15 levels of 200
-// steps at 1521 nodes and one of 10^4 at 29, 512 paths: 3.62 ms at six per CU, 4.14 at
-// three).
-int long_blocks(int64_t steps, double paths_per_lane, int block) {
+// in which a step of the launch is taken on average: one long level of a few
+// nodes among short ones leaves the short ones' paths to fill the chip (15
+// levels of 200 steps at 1521 nodes and one of 10^4 at 29, 512 paths, 34 to a lane:
+// 3.62 ms at six per CU, 4.14 at three).  With up to 8 paths to a lane there
+// are not enough of them to do so: by the longest level (14 levels of up to
+// 1142 steps, 561 nodes x 288 paths: 1.54 ms at four, 1.65 at six; the 15 and one
+// with 64 paths 0.94 and 0.95).
+int long_blocks(int64_t steps, int64_t longest, double paths_per_lane, int block) {
+    if (paths_per_lane <= 8.0) steps = longest;
     if (steps < 1000 || paths_per_lane > 32.0) return 0;
     return std::max(1, (steps < 4000 ? 4 : 3) * 256 / block);
 }
@@ -460,7 +465,7 @@ int enqueue_solve(const SolveLaunch &S, hipStream_t stream, bool allow_timing) {
                                                                a.score_mode == FK_SCORE_BRIDGE, S.few_steps,
                                                                S.plan.block);
     if (bpc == 0 && !S.lockstep && !expo)
-        bpc = long_blocks(S.steps, (double)S.n_nodes * (double)S.n_paths / ((double)n_cu * occ * S.plan.block + 1.0),
+        bpc = long_blocks(S.steps, S.longest, (double)S.n_nodes * (double)S.n_paths / ((double)n_cu * occ * S.plan.block + 1.0),
                           S.plan.block);
     if (bpc == 0 || (occ > 0 && bpc > occ)) bpc = occ > 0 ? occ : 1;
     const int grid = cap_grid(n_cu * bpc, a.total_chunks, S.plan.block);
@@ -631,7 +636,7 @@ int fk_interface_solve(const fk_density *w, const fk_data *d, const double *pts,
     // which cuts the wavefronts' fixed costs per path.  Otherwise 128, for
     // the balance of the tail.
     S.lockstep = lockstep_paths(level.K, t, d->score_mode);
-    S.steps = level.K;
+    S.steps = S.longest = level.K;
     S.few_steps = !S.lockstep && level.K <= 64 && d->score_mode != FK_SCORE_EXPONENTIAL;
     if ((!plan || plan->chunk == 0) && (S.lockstep || S.few_steps)) {
         int n_cu = 0;

@@ -51,6 +51,7 @@ static int batch_launch(fk_batch *b, int64_t n_paths, const fk_plan &pl, double 
     S.uniform = b->T.uniform;
     S.plan = pl;
     S.steps = b->T.steps;
+    S.longest = b->T.longest;
     S.n_nodes = b->n_total;
     S.n_paths = n_paths;
     S.counters = (uint32_t *)ws;

@@ -2254,7 +2254,7 @@ int fk_interface_solve_cv(const fk_density *w, const fk_data *d, const double *p
         P.time_mode = w->time_mode;
         P.uniform = uniform;
         P.lockstep = lockstep_paths(level.K, t, d->score_mode);
-        P.steps = level.K;
+        P.steps = P.longest = level.K;
         P.few_steps = !P.lockstep && level.K <= 64;
         if ((rc = resolve_plan(nullptr, &P.plan)) != FK_OK) return rc;
         if (P.lockstep) P.plan.chunk = lockstep_chunk(n_nodes, n_paths, n_cu, mask != nullptr);

@@ -157,6 +157,7 @@ struct Tables {
     bool uniform = true;         // every step has length dt
     bool shift = false;          // scores stored relative to the start point
     int64_t steps = 0;           // of the path that a step belongs to, on average over the levels' steps
+    int64_t longest = 0;         // of any level
 };
 
 // Everything one enqueue of the solve sequence needs.
@@ -168,6 +169,7 @@ struct SolveLaunch {
     bool few_steps;       // at most 64 steps in the refilling kernel: its few-steps form
     bool lockstep;        // short horizons: the kernel of fk_short.hip (lockstep_paths)
     int64_t steps;        // a path's steps at most; of several levels, the average over their steps
+    int64_t longest;      // the same of the longest level
     const TableArgs *tables;  // device-built tables (filled in by enqueue_solve), or nullptr: host tables
     fk_plan plan;
     int64_t n_nodes, n_paths;
@@ -200,25 +202,28 @@ bool lockstep_paths(int64_t K, double t, int score_mode);
 // the same few cells.  From an LDS tile of the mesh it does up to 32 steps.
 // Otherwise, its time over the refilling kernel's (stride 2 unless stated, nodes
 // over the square and within 0.001 to 0.1 of a side):
-//  * from the gradient table, at most 32 steps: 0.2 - 0.96; 32 steps with
-//    16 gathers and paths spread beyond 100 cells 1.05 - 1.2 (768 cells, 10689 nodes
-//    x 500 paths, 1521 x 4096);
-//  * from the grids (a workspace without room for the table: eight gathers instead
-//    of two), at most 32 steps: at most five gathers 0.15 - 0.96; more, up to 12 rounds of 64
-//    paths to a SIMD 0.5 - 0.97, up to 48 with 20 steps or 8 gathers 0.4 - 0.99,
-//    otherwise 1.14; beyond that 0.3 - 0.9 on small grids, on 768 cells 0.8 - 1.45;
-//  * 33 to 64 steps: up to 12 rounds 0.3 - 0.97 (from the grids of 768 cells, 10689
-//    nodes x 2 paths, 1.06 - 2.1), up to 48 with one gather, or 16 from the table,
-//    0.25 - 0.97, beyond that up to 1.65 near a side.
+//  * from the gradient table, at most 32 steps: 0.2 - 0.96; 32 steps with 16
+//    gathers and paths spread beyond 100 cells 1.05 - 1.2 (768 cells, 10689
+//    nodes x 500 paths, 1521 x 4096);
+//  * from the grids (a workspace without room for the table: eight gathers
+//    instead of two), at most 32 steps: at most five gathers 0.15 - 0.96; more,
+//    up to 12 rounds of 64 paths to a SIMD 0.5 - 0.97, up to 48 with 20 steps or
+//    8 gathers 0.4 - 0.99, otherwise 1.14; beyond that 0.3 - 0.9 on small grids,
+//    on 768 cells 0.8 - 1.45;
+//  * 33 to 64 steps: up to 12 rounds 0.3 - 0.97 (from the grids of 768 cells,
+//    10689 nodes x 2 paths, 1.06 - 2.1), up to 48 with one gather, or 16 from the
+//    table, 0.25 - 0.97, beyond that up to 1.65 near a side.
+// From the tile with all nodes within 0.02 of a side 1.14 (32 steps).
 bool lockstep_mesh(bool table, int grid_n, int64_t n_paths, int64_t stride, double t, int64_t K, int64_t n_nodes,
                    int n_cu, bool masked);
 // Whether nodes near a side have its lanes take other paths (short_refill):
 // past 32 steps, and where the rounds of 64 paths are more than the wavefronts
-// that fit (below that the time is a wavefront's, whose lanes then wait for
-// nothing; registers and code for it cost every launch up to 2 us).  1521 nodes within 0.001 to
-// 0.5 of a side, 33 to 64 steps, time in lockstep over the refilling kernel's:
-// up to 256 paths 0.26 - 0.83, 320 and 500 up to 1.09, 2000 1.36, 4096 1.76; 77
-// nodes: 4096 paths 0.70, 16384 1.33.
+// that fit (below that the time is one wavefront's, whose lanes wait for
+// nothing then).  1521 nodes within 0.001 to 0.5 of a side, 33 to 64 steps, time
+// in lockstep alone over the refilling kernel's: up to 256 paths 0.26 - 0.83,
+// 320 and 500 up to 1.09, 2000 1.36, 4096 1.76; 77 nodes: 4096 paths 0.70, 16384
+// 1.33.  With it 0.2 - 0.93, and at 1521 x 4096 up to 1.17 (nodes within 0.2 of a
+// side, 64 steps over 0.05).
 bool lockstep_refill(int64_t K, int64_t n_nodes, int64_t n_paths, int n_cu, bool masked);
 // Its default chunk: 64 r paths for the r that finishes first when every
 // resident wavefront takes an equal number of chunks.
@@ -232,7 +237,7 @@ int few_paths_chunk(int64_t n_nodes, int64_t n_paths, int n_cu);
 int network_chunk(int64_t n_nodes, int64_t n_paths, int n_cu, bool masked, bool heavy);
 // Resident workgroups per CU of the refilling path kernel by default (0: all
 // that fit).
-int long_blocks(int64_t steps, double paths_per_lane, int block);
+int long_blocks(int64_t steps, int64_t longest, double paths_per_lane, int block);
 
 // Form and residency of the mesh-gradient control's refilling kernel
 // (fk_mgg_path_kernel): steps in branch-free pairs or not, and the resident

@@ -1,6 +1,6 @@
 // Prints what the library's launch rules answer.  Reads lines
 //   levels K n [K n ...]        -> steps of Tables (one step size, n nodes a level)
-//   blocks steps per_lane block -> long_blocks
+//   blocks steps longest per_lane block -> long_blocks
 //   lockstep K t mode            -> lockstep_paths
 //   mesh table grid_n paths stride t K nodes -> lockstep_mesh on 256 CUs
 //   network nodes paths masked heavy -> network_chunk on 256 CUs
@@ -47,7 +47,7 @@ int main() {
         for (double x; in >> x;) v.push_back(x);
         long long r = -1;
         if (what == "levels") r = table_steps(std::vector<int64_t>(v.begin(), v.end()));
-        if (what == "blocks") r = long_blocks((int64_t)v.at(0), v.at(1), (int)v.at(2));
+        if (what == "blocks") r = long_blocks((int64_t)v.at(0), (int64_t)v.at(1), v.at(2), (int)v.at(3));
         if (what == "lockstep") r = lockstep_paths((int64_t)v.at(0), v.at(1), (int)v.at(2));
         if (what == "mesh")
             r = lockstep_mesh(v.at(0) != 0.0, (int)v.at(1), (int64_t)v.at(2), (int64_t)v.at(3), v.at(4),

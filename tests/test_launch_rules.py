@@ -30,17 +30,20 @@ def rules(tmp_path_factory):
 
 
 def test_one_long_level_does_not_cut_the_residency_of_short_ones(rules):
-    """A batch's residency goes by the steps of the level its steps are in, not by its longest level."""
+    """With many paths, a batch's residency goes by the steps of the level its steps are in, not by its longest level."""
     short = " ".join(["50 1521"] * 15)
     long = " ".join(["200 1521"] * 15)
     steps = rules(f"levels {short} 1000 29", f"levels {short} 1600 77", f"levels {long} 4000 29", f"levels {long} 10000 29")
     assert all(v < 1000 for v in steps), steps
-    assert rules(*(f"blocks {v} 4 256" for v in steps)) == [0] * 4
+    assert rules(*(f"blocks {v} 4000 9 256" for v in steps)) == [0] * 4
+    # few paths leave the wavefronts of any form idle: by the longest level
+    assert rules(*(f"blocks {v} {k} 8 256" for v in steps for k in (900, 3000, 4000))) == [0, 4, 3] * 4
     # one level, levels alike, and a ramp whose later levels take most of the steps
     one, alike, ramp = rules("levels 5000 33", "levels 2000 10 2000 99",
                              "levels " + " ".join(f"{100 * i} 381" for i in range(1, 17)))
     assert (one, alike) == (5000, 2000) and 1000 <= ramp < 1600
-    assert rules("blocks 5000 4 256", "blocks 2000 4 256", f"blocks {ramp} 4 256", "blocks 5000 40 256") == [3, 4, 4, 0]
+    assert rules("blocks 5000 5000 4 256", "blocks 2000 2000 4 256", f"blocks {ramp} 1600 9 256",
+                 "blocks 5000 5000 40 256") == [3, 4, 4, 0]
     assert rules("levels 0 5", "levels 0 5 1000 5") == [0, 1000]
 
 
