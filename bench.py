@@ -95,8 +95,8 @@ CV_PROFILE_PATHS = 2952
 # (scaled by a plain 1 GiB copy: fetch x2.0, write x1.0) on the moving-bump
 # solve at N* = 73920 (1521 x 578 chunks of 128 paths), per path, valid only
 # for the kernel sources it was measured on (hash below); otherwise null.
-TRAFFIC_BYTES_PER_PATH = (2.0 * 245.0 + 1.0 * 475444.96875) * 1024 / (1521 * 73920)
-TRAFFIC_SOURCE_HASH = "bdc48ac49a6782f9"
+TRAFFIC_BYTES_PER_PATH = (2.0 * 245.5 + 1.0 * 479147.1875) * 1024 / (1521 * 73920)
+TRAFFIC_SOURCE_HASH = "26d5a9d0e7ef9e87"
 KERNEL_SOURCES = ["paper_1402_0266_amd/csrc/fk_paths.hip", "paper_1402_0266_amd/csrc/fk_device.hpp",
                   "paper_1402_0266_amd/csrc/fk_internal.hpp", "paper_1402_0266_amd/csrc/fk_pathstep.hpp",
                   "paper_1402_0266_amd/csrc/fk_accum.hpp"]

@@ -383,8 +383,9 @@ void fk_batch_destroy(fk_batch_t b);
  * NULL).
  * Each sub-domain system is solved by Gaussian elimination without pivoting,
  * in FP64: nested dissection, or banded LU where its fronts would be too
- * large (long sub-domains whose shorter side is above 64 cells); xi and eta
- * share the factorisation.  Requires
+ * large (long sub-domains whose shorter side is above 64 cells), where the
+ * grid is too large for its launches and for up to 256 sub-domains of a few
+ * cells a side; xi and eta share the factorisation.  Requires
  * |b| h / 2 < 1 (checked from the density's bound; FK_E_UNSUPPORTED
  * otherwise) and min(mx, my) <= 128 (FK_E_UNSUPPORTED).  A grid density
  * (FK_DENSITY_GRID) must be sampled on this mesh's grid (grid_n == N, else

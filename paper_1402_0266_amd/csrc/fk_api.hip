@@ -312,12 +312,12 @@ int long_blocks(int64_t steps, int64_t longest, double paths_per_lane, int block
 
 // Fixed steps with the discrete exit test, at most 64 of them, and not so
 // long a horizon that lanes whose paths have left wait for most of it (nodes
-// near a side, whose paths leave at any horizon, are seen to by the kernel
-// itself: short_leaves, fk_short.hip).  Both kernels on 1521 nodes x 4096 paths of two bumps (refilling / lockstep, us):
-// 8 steps 332 / 119 at t = 1e-3, 326 / 105 at t = 0.3; 20 steps 369 / 231
-// and 338 / 214; 32 steps 492 / 354 and 348 / 322; 64 steps 874 / 680 at
-// t = 1e-3, 821 / 680 at t = 0.05 (a path takes 59% of the steps), 637 / 679
-// at t = 0.1 (42%), 393 / 612 at t = 0.3.
+// near a side, whose paths leave at any horizon, are seen to by a form of the
+// kernel: lockstep_refill).  Both kernels on 1521 nodes x 4096 paths of two
+// bumps (refilling / lockstep, us): 8 steps 332 / 119 at t = 1e-3, 326 / 105
+// at t = 0.3; 20 steps 369 / 231 and 338 / 214; 32 steps 492 / 354 and 348 /
+// 322; 64 steps 874 / 680 at t = 1e-3, 821 / 680 at t = 0.05 (a path takes 59%
+// of the steps), 637 / 679 at t = 0.1 (42%), 393 / 612 at t = 0.3.
 bool lockstep_paths(int64_t K, double t, int score_mode) {
     return (K <= 32 || (K <= 64 && t <= 0.05)) && score_mode != FK_SCORE_EXPONENTIAL && score_mode != FK_SCORE_BRIDGE;
 }

@@ -244,12 +244,15 @@ hipError_t launch_short_tables(const TableArgs &t, unsigned long long *total_ste
 // Long horizons keep the counter for every grab (the other form costs their
 // hot loop ~3% in code).  Ring and moving bump, 1521 nodes x 4096 paths, 64
 // steps over t = 0.1: 736 and 605 us, in branch-free pairs 785 and 628 us; a
-// path ends every second pair or so of a wavefront there.
+// path ends every second pair or so of a wavefront there.  (With 100 paths a
+// node 79 against 71 us: pairs would be faster where the chip is part-empty.)
 //
-// The inner loop of the others takes step pairs without a branch until some lane's path may
-// have ended: both steps are taken at once, and one unsigned maximum over the
-// four new coordinates and the pair count finds the wavefronts that have to
-// look closer.  Idle lanes hold a point that stays at (0.5, 0.5).  Scores,
+// The inner loop of the others takes step pairs without a branch until some
+// lane's path may have ended: both steps are taken at once, and one unsigned
+// maximum over the four new coordinates and the pair count finds the
+// wavefronts that have to look closer.  The two forms share the scoring below
+// as it stands: in a function or lambda of its own it changes the order of the
+// pair loop's instructions, and 73920 paths per node take 628 ms, not 598.  Idle lanes hold a point that stays at (0.5, 0.5).  Scores,
 // refill and queue stand outside the inner loop: kept in one loop they cost
 // it ~20 register moves a pair.  Five to six wavefronts per SIMD (78 - 96
 // registers, 15 of them Philox round keys): with the keys in scalar registers

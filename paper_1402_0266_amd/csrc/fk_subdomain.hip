@@ -11,8 +11,9 @@
 //
 // MI355X mapping: the unit square's N x N grid is split into px x py
 // sub-domains of mx x my cells.  The systems are solved by nested dissection
-// (fk_dissect.hip); sub-domains too long and wide for its fronts, and
-// workspaces too small for it, take the banded LU of this file: a
+// (fk_dissect.hip).  The banded LU of this file takes the rest: sub-domains too
+// long and wide for its fronts, grids beyond its launches' limits, workspaces too
+// small for it, and at most 256 sub-domains of one leaf.  A
 // sub-domain's interior unknowns are numbered along the shorter side first
 // (the fast index), so its matrix is banded with half-bandwidth q = the
 // number of unknowns on that side, and the fill of the LU stays in the band.
@@ -1538,7 +1539,8 @@ static hipError_t launch_elimination(const SubArgs &a, int blocks, hipStream_t s
     default: break;
     }
 #undef FK_WAVE
-    // any other band: the tile kernel, its window at least q + 16 wide
+    // any other band: the tile kernel, its window at least q + 16 wide (windows of 3
+    // to 5 tiles only for grids beyond the dissection's launch limits)
     const int T = (a.qf + 16 + 15) / 16;
     switch (T) {
     case 2: hipLaunchKernelGGL(subdomain_lu_tile_kernel<2>, dim3(nwg), dim3(256), 0, s, a); break;
@@ -1637,7 +1639,8 @@ int subdomain_solve_rect(const fk_density *w, double t_w, double dt_mesh, int32_
     ws += align256(blocks * sep_stride(geo.qf) * sizeof(double));
     double *edge_cells = (double *)ws;
     // nested dissection, unless its fronts would be too large (long, wide
-    // sub-domains) or the workspace too small for it; a few sub-domains of
+    // sub-domains), the grid too large for its launches (2^32 work-items, 32768
+    // unknowns a side) or the workspace too small for it; a few sub-domains of
     // one leaf take the banded LU, which is one launch fewer (3 x 3 unknowns
     // in 256 sub-domains: 19.5 us against 21.6; in 1024: 38.4 against 20.8)
     NdTree tree;
